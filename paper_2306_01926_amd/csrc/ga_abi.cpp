@@ -131,7 +131,7 @@ int run_cluster(const ga::Dims& d, const void* K, int32_t iters, const float* in
                                 w.nrm64, w.nsplit, st), "update launch");
     } else {
       GA_LAUNCH(ga::launch_bucket(d, belong, w.perm, w.goff, count, st), "bucket launch");
-      GA_LAUNCH(ga::launch_update(d, K, w.perm, w.goff, count, C, w.R, w.nrm64, w.nsplit, st), "update launch");
+      GA_LAUNCH(ga::launch_update(d, (const float*)K, w.perm, w.goff, count, C, (float*)w.R, w.nrm64, st), "update launch");
     }
   }
   return GA_OK;
@@ -145,7 +145,7 @@ int run_valuesum(const ga::Dims& d, const void* V, const int32_t* belong, int32_
                               nullptr, st), "value-sum launch");
   } else {
     GA_LAUNCH(ga::launch_bucket(d, belong, w.perm, w.goff, count, st), "bucket launch");
-    GA_LAUNCH(ga::launch_valuesum(d, V, w.perm, w.goff, count, vsum, st), "value-sum launch");
+    GA_LAUNCH(ga::launch_valuesum(d, (const float*)V, w.perm, w.goff, count, vsum, st), "value-sum launch");
   }
   return GA_OK;
 }
@@ -176,7 +176,7 @@ int run_forward(const ga::Dims& d, const void* Q, const void* K, const void* V, 
     GA_LAUNCH(ga::launch_attend(d, Q, w.R, w.Vt, w.ginit, C, cnt, w.vsum, scale, O, st), "attention launch");
   } else {
     // the last stable bucket pass sorted the keys by the final assignment: reuse it
-    GA_LAUNCH(ga::launch_valuesum(d, V, w.perm, w.goff, cnt, w.vsum, st), "value-sum launch");
+    GA_LAUNCH(ga::launch_valuesum(d, (const float*)V, w.perm, w.goff, cnt, w.vsum, st), "value-sum launch");
     GA_LAUNCH(ga::launch_attend(d, Q, nullptr, nullptr, nullptr, C, cnt, w.vsum, scale, O, st),
               "attention launch");
   }

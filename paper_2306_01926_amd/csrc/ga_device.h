@@ -86,8 +86,8 @@ __device__ void write_nsplit(double nrm, uint16_t* dst) {
 __device__ __forceinline__ int swz(int r, int c) { return r * 64 + 8 * (c ^ ((r >> 1) & 7)); }
 
 // Exact assignment of NK bf16 keys at once by a whole wave, the
-// representatives read from the LDS copy of -2R.  Same definition as
-// exact_argmin_wave (score fma(-2, k.r, |r|^2) with k.r an fp64 fma chain over
+// representatives read from the LDS copy of -2R.  The canonical
+// definition (score fma(-2, k.r, |r|^2) with k.r an fp64 fma chain over
 // c = 0..63, lowest index among minima): x = -2r is exact in bf16 and every
 // partial sum of the chain over k_c x_c is exactly -2 times the one over
 // k_c r_c (the partial sums stay far from the fp64 subnormal range), so the

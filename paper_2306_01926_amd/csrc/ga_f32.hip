@@ -1,0 +1,439 @@
+// fp32 path of the grouping and the attention (gfx950): MFMA scores in fp32
+// whose argmin is certified against the exact fp64 definition, the ordered
+// fp64 member sums, and the fp32 group attention.
+#include <hip/hip_runtime.h>
+
+#include <float.h>
+#include <math.h>
+#include <stdint.h>
+
+#include "ga_internal.h"
+
+namespace ga {
+namespace {
+
+#include "ga_device.h"
+
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+// LDS row stride (floats) of the MFMA A operand: 16 consecutive rows reading
+// one 16-byte chunk then hit all 64 banks once.
+constexpr int kRow = 68;
+constexpr int kAsgChunk = 128;  // groups staged at a time by k_assign_f32
+constexpr int kAttChunk = 64;   // by k_attend_f32
+constexpr int kExactK = 4;      // uncertain keys decided together by one wave
+
+// This lane's half row (features 32 h .. 32 h + 31) times `mul`.
+__device__ __forceinline__ void load_half(const float* __restrict__ row, int h, float mul, f32x4 (&f)[8]) {
+#pragma unroll
+  for (int s = 0; s < 8; ++s) f[s] = *(const f32x4*)(row + 32 * h + 4 * s) * mul;
+}
+
+// acc += A (32 rows of an LDS tile) x B (32 columns held as half rows): 32 MFMA
+// 32x32x2 steps; lanes h = 0 and 1 supply features c and 32 + c on both sides.
+__device__ __forceinline__ f32x16 mfma_rows(const float* rows, int q, int h, const f32x4 (&b)[8], f32x16 acc) {
+#pragma unroll
+  for (int s = 0; s < 8; ++s) {
+    const f32x4 a = *(const f32x4*)(rows + q * kRow + 32 * h + 4 * s);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[e], b[s][e], acc, 0, 0, 0);
+  }
+  return acc;
+}
+
+// ------------------------------------------------------------------ assign
+// The canonical decision of NK keys (rows k[b], wave-uniform) by one wave:
+// lanes take groups lane, lane + 64, ...; the dot product an fp64 fma chain
+// over c = 0..63, the score fma(-2, dot, |r|^2), lowest index among minima.
+template <int NK>
+__device__ __forceinline__ void exact_keys(const float* const (&k)[kExactK], const float* __restrict__ Rbh,
+                                           const double* __restrict__ nrm, int N, int (&jb)[kExactK]) {
+  const int lane = threadIdx.x & 63;
+  double best[NK];
+#pragma unroll
+  for (int b = 0; b < NK; ++b) {
+    best[b] = INFINITY;
+    jb[b] = 0x7fffffff;
+  }
+  for (int j = lane; j < N; j += 64) {
+    const float* r = Rbh + (int64_t)j * 64;
+    const double nj = nrm[j];
+    double dot[NK];
+#pragma unroll
+    for (int b = 0; b < NK; ++b) dot[b] = 0.0;
+#pragma unroll 2
+    for (int c = 0; c < 64; c += 8) {
+      const f32x4 r0 = *(const f32x4*)(r + c), r1 = *(const f32x4*)(r + c + 4);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const double x = (double)(e < 4 ? r0[e & 3] : r1[e & 3]);
+#pragma unroll
+        for (int b = 0; b < NK; ++b) dot[b] = fma((double)k[b][c + e], x, dot[b]);
+      }
+    }
+#pragma unroll
+    for (int b = 0; b < NK; ++b) {
+      const double s = fma(-2.0, dot[b], nj);
+      if (s < best[b]) {
+        best[b] = s;
+        jb[b] = j;
+      }
+    }
+  }
+#pragma unroll
+  for (int b = 0; b < NK; ++b)
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) {
+      const double ob = __shfl_xor(best[b], off);
+      const int oj = __shfl_xor(jb[b], off);
+      if (ob < best[b] || (ob == best[b] && oj < jb[b])) {
+        best[b] = ob;
+        jb[b] = oj;
+      }
+    }
+}
+
+// k_assign_f32: grid (ceil(tiles / (4 tpw)), BH), 256 threads; each wave
+// scores tpw tiles of 32 keys against all groups (staged kAsgChunk at a time)
+// with MFMA 32x32x2 fp32: s^ = |r|^2 + sum r_c (-2 k_c), |r|^2 (rounded to
+// fp32) as the accumulator's start, then the packed top-2 of reduce_block.
+// The bound E of certified decisions is the bf16 path's: each of the 64
+// products and the start added with at most one rounding (truncation
+// included) is within cm M, cm = (d + 4) 2^-23, M = max |r|^2 + 2 |k| max |r|.
+// Keys that it does not certify (0.07% on mixtures of 64 groups), among them
+// every key that a NaN, an infinity or an overflow touches (E is then no
+// finite number) or whose scores underflow (E >= 1e-30), are queued and decided by
+// exact_keys, so the groups are those of the fp64 definition.  Bound by the
+// MFMA rate (157 TFLOP/s in fp32) at full grids: 32 slices of 2000 keys against
+// 64 groups 148 -> 17 us (event times, with about 5 us of event overhead), 128
+// slices of 8000 against 128 groups 163 us (103 TFLOP/s), where an fp64 fma
+// chain for every (key, group) took 148 us and several milliseconds.
+__global__ __launch_bounds__(256) void k_assign_f32(const float* __restrict__ K, const float* __restrict__ R,
+                                                    const double* __restrict__ nrm64, int32_t* __restrict__ belong,
+                                                    int n, int N, int tpw, float cm, float cp) {
+  __shared__ __align__(16) float Rl[kAsgChunk * kRow];
+  __shared__ __align__(16) float Nl[kAsgChunk];
+  __shared__ uint32_t nbits;  // largest |r|^2 as bits (a NaN's are larger than any number's)
+  __shared__ int nq;
+  extern __shared__ int32_t queue[];  // [4 tpw 32] local indices of uncertain keys
+  const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5, q = lane & 31;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int64_t bh = blockIdx.y;
+  const int64_t key0 = (int64_t)blockIdx.x * 4 * tpw * 32;
+  const float* Kbh = K + bh * (int64_t)n * 64;
+  const float* Rbh = R + bh * (int64_t)N * 64;
+  const double* nrm_bh = nrm64 + bh * N;
+  if (tid == 0) {
+    nbits = 0;
+    nq = 0;
+  }
+  for (int t = 0; t < tpw; ++t) {
+    // the waves' tiles of one pass are neighbours; every wave runs every pass (barriers below)
+    const int lk = (t * 4 + wave) * 32 + q;
+    const int64_t key = key0 + lk;
+    if (key0 + (int64_t)t * 128 >= n) break;  // uniform
+    f32x4 kf[8];
+    load_half(Kbh + min(key, (int64_t)n - 1) * 64, h, -2.0f, kf);
+    float M1 = FLT_MAX, M2 = FLT_MAX;
+    int B1 = 0;
+    for (int g0 = 0; g0 < N; g0 += kAsgChunk) {
+      const int ng = min(kAsgChunk, N - g0), nblk = (ng + 31) >> 5;
+      if (t == 0 || N > kAsgChunk) {
+        __syncthreads();
+        for (int x = tid; x < nblk * 32 * 16; x += 256) {
+          const int r = x >> 4, ch = x & 15;
+          *(f32x4*)(Rl + r * kRow + 4 * ch) = *(const f32x4*)(Rbh + (int64_t)(g0 + min(r, ng - 1)) * 64 + 4 * ch);
+        }
+        if (tid < nblk * 32) {
+          const float v = tid < ng ? (float)nrm_bh[g0 + tid] : 3.0e38f;  // a padded group never wins
+          Nl[tid] = v;
+          if (tid < ng) atomicMax(&nbits, __float_as_uint(v));
+        }
+        __syncthreads();
+      }
+      for (int b = 0; b < nblk; ++b) {
+        f32x16 acc;
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+          const f32x4 nv = *(const f32x4*)(Nl + b * 32 + 8 * w + 4 * h);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) acc[4 * w + e] = nv[e];
+        }
+        acc = mfma_rows(Rl + b * 32 * kRow, q, h, kf, acc);
+        reduce_block(acc, (g0 >> 5) + b, M1, M2, B1);
+      }
+    }
+    float ss = 0.f;
+#pragma unroll
+    for (int s = 0; s < 8; ++s)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) ss = fmaf(kf[s][e], kf[s][e], ss);
+    const u32x2 ps = halves(__float_as_uint(ss)), p1 = halves(__float_as_uint(M1)), p2 = halves(__float_as_uint(M2)),
+                pb = halves((uint32_t)B1);
+    const float k2 = sqrtf(__uint_as_float(ps[0]) + __uint_as_float(ps[1])) * (1.0f + 0x1p-16f);  // 2 |k|
+    const float a1 = __uint_as_float(p1[0]), b1 = __uint_as_float(p1[1]);
+    const bool hi_wins = b1 < a1;
+    const uint32_t vw = __float_as_uint(hi_wins ? b1 : a1) & kPackMask;
+    const int jstar = 32 * (int)(hi_wins ? pb[1] : pb[0]) + 8 * (int)(vw >> 2) + (hi_wins ? 4 : 0) + (int)(vw & 3);
+    const float best = min2(a1, b1);
+    const float second = min2(max2(a1, b1), min2(__uint_as_float(p2[0]), __uint_as_float(p2[1])));
+    const float nmaxf = __uint_as_float(nbits) * (1.0f + 0x1p-20f);
+    const float Mk = nmaxf + k2 * (sqrtf(nmaxf) * (1.0f + 0x1p-20f));
+    const float aM1 = fabsf(best);
+    const float E = (cm * Mk + cp * (aM1 + 3.0f * cm * Mk)) * (1.0f + 0x1p-20f) + 0x1p-22f * aM1 + 1e-30f;
+    const bool certain = (second > best + 2.0f * E) && (E < FLT_MAX) && (jstar < N);
+    if (h == 0 && key < n) {
+      if (certain)
+        belong[bh * n + key] = jstar;
+      else
+        queue[atomicAdd(&nq, 1)] = lk;
+    }
+  }
+  __syncthreads();
+  const int nu = nq;
+  for (int u0 = wave * kExactK; u0 < nu; u0 += 4 * kExactK) {
+    const int nb = min(kExactK, nu - u0);
+    int64_t kk[kExactK];
+    const float* rows[kExactK];
+    int jb[kExactK];
+#pragma unroll
+    for (int b = 0; b < kExactK; ++b) {
+      kk[b] = key0 + __builtin_amdgcn_readfirstlane(queue[u0 + min(b, nb - 1)]);
+      rows[b] = Kbh + kk[b] * 64;
+    }
+    if (nb == 1)
+      exact_keys<1>(rows, Rbh, nrm_bh, N, jb);
+    else
+      exact_keys<kExactK>(rows, Rbh, nrm_bh, N, jb);
+    if (lane == 0)
+#pragma unroll
+      for (int b = 0; b < kExactK; ++b)
+        if (b < nb) belong[bh * n + kk[b]] = jb[b];
+  }
+}
+
+// ------------------------------------------------------------------ ordered sums
+// k_segsum: grid (ceil(N/4), BH), 256 threads: one wave per group, lane =
+// feature.  The group's members are perm[goff .. goff + count) in ascending
+// key order and are summed in that order in fp64 (fp32 sums need not be exact,
+// so the order is part of the definition).  Bound by the latency of the row
+// loads: a batch of kSegU rows is in flight while the one before it is added,
+// and the wave loads 64 indices at a time (4 rows in flight and dependent index
+// loads before: 26 -> 13 us at 2048 groups of 31 members, 120 us at 8 groups of
+// 2500, where the ordered chain leaves the chip idle).  UPDATE: centroid = (float)(sum /
+// count) (an empty group keeps its centroid) and its |r|^2; otherwise the fp32
+// rounding of the value sum.
+constexpr int kSegU = 16;
+template <bool UPDATE>
+__global__ __launch_bounds__(256) void k_segsum(const float* __restrict__ X, const int32_t* __restrict__ perm,
+                                                const int32_t* __restrict__ goff, const int32_t* __restrict__ count,
+                                                int n, int N, float* __restrict__ out, float* __restrict__ R,
+                                                double* __restrict__ nrm64) {
+  const int lane = threadIdx.x & 63;
+  const int g = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6));
+  const int64_t bh = blockIdx.y;
+  if (g >= N) return;
+  const int64_t row = bh * N + g;
+  const int st = goff[row], cnt = count[row];
+  const int32_t* P = perm + bh * n + st;
+  const float* Xb = X + bh * (int64_t)n * 64 + lane;
+  double acc = 0.0;
+  if (cnt > 0) {
+    int idx = P[min(lane, cnt - 1)], idx_n = 0;  // members 64 w + lane of this and the next window
+    float va[kSegU], vb[kSegU];
+    auto load = [&](int x, float (&v)[kSegU]) {  // x: first member of a batch inside the window of idx
+#pragma unroll
+      for (int u = 0; u < kSegU; ++u)
+        v[u] = Xb[(int64_t)__builtin_amdgcn_readlane(idx, (x & 63) + u) * 64];
+    };
+    auto add = [&](int x, const float (&v)[kSegU]) {
+      if (x + kSegU <= cnt) {
+#pragma unroll
+        for (int u = 0; u < kSegU; ++u) acc += (double)v[u];
+      } else {
+#pragma unroll
+        for (int u = 0; u < kSegU; ++u)
+          if (x + u < cnt) acc += (double)v[u];
+      }
+    };
+    load(0, va);
+    for (int x = 0; x < cnt; x += 2 * kSegU) {
+      if ((x & 63) == 0) idx_n = P[min(x + 64 + lane, cnt - 1)];
+      load(x + kSegU, vb);  // past the end: the last member again, not added
+      add(x, va);
+      if (((x + 2 * kSegU) & 63) == 0) idx = idx_n;
+      load(x + 2 * kSegU, va);
+      add(x + kSegU, vb);
+    }
+  }
+  if (!UPDATE) {
+    out[row * 64 + lane] = (float)acc;
+    return;
+  }
+  float c;
+  if (cnt > 0) {
+    c = (float)(acc / (double)cnt);
+    out[row * 64 + lane] = c;
+  } else {
+    c = out[row * 64 + lane];
+  }
+  R[row * 64 + lane] = c;
+  const double nrm = canon_nrm_wave(c);
+  if (lane == 0) nrm64[row] = nrm;
+}
+
+// ------------------------------------------------------------------ attention
+// k_attend_f32: grid (ceil(tiles / (4 tpw)), BH), 256 threads; each wave takes
+// tiles of 32 queries (lane l: query l % 32, h = l / 32).  Per 32-group block:
+// scores by MFMA 32x32x2 fp32 (A = centroid rows from LDS, B = the query), the
+// running-maximum softmax, and the combine by MFMA again: the exponentials
+// leave the first product's registers as the second one's B operand (step v
+// contracts groups 8 (v / 4) + v % 4 and + 4, which registers v of lanes h = 0
+// and 1 hold), A = the value sums.  Everything is fp32, as is the denominator;
+// the count enters only there.
+__global__ __launch_bounds__(256) void k_attend_f32(const float* __restrict__ Q, const float* __restrict__ centroid,
+                                                    const int32_t* __restrict__ count,
+                                                    const float* __restrict__ vsum, int n, int N, float scale,
+                                                    int tpw, float* __restrict__ O) {
+  __shared__ __align__(16) float Rs[kAttChunk * kRow];
+  __shared__ __align__(16) float Vs[kAttChunk * 64];
+  __shared__ __align__(16) float Cs[kAttChunk];  // member counts, 0 for an empty or padded group
+  const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5, q = lane & 31;
+  const int wave = tid >> 6;
+  const int64_t bh = blockIdx.y;
+  const int64_t q0 = (int64_t)blockIdx.x * 4 * tpw * 32;
+  const float* Rbh = centroid + bh * (int64_t)N * 64;
+  const float* Vbh = vsum + bh * (int64_t)N * 64;
+  for (int t = 0; t < tpw; ++t) {
+    if (q0 + (int64_t)t * 128 >= n) break;  // uniform
+    const int64_t qi = q0 + (t * 4 + wave) * 32 + q;
+    f32x4 qf[8];
+    load_half(Q + (bh * n + min(qi, (int64_t)n - 1)) * 64, h, 1.0f, qf);
+    f32x16 o0, o1;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) o0[v] = o1[v] = 0.f;
+    float m = -INFINITY, ssum = 0.f;  // ssum: this lane's half of the groups
+    for (int g0 = 0; g0 < N; g0 += kAttChunk) {
+      const int ng = min(kAttChunk, N - g0), nblk = (ng + 31) >> 5;
+      if (t == 0 || N > kAttChunk) {
+        __syncthreads();
+        for (int x = tid; x < nblk * 32 * 16; x += 256) {
+          const int r = x >> 4, ch = x & 15;
+          const int64_t src = (int64_t)(g0 + min(r, ng - 1)) * 64 + 4 * ch;
+          *(f32x4*)(Rs + r * kRow + 4 * ch) = *(const f32x4*)(Rbh + src);
+          const f32x4 vv = *(const f32x4*)(Vbh + src);
+          *(f32x4*)(Vs + r * 64 + 4 * ch) = r < ng && count[bh * N + g0 + r] > 0 ? vv : f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+        if (tid < nblk * 32) Cs[tid] = tid < ng ? (float)max(count[bh * N + g0 + tid], 0) : 0.f;
+        __syncthreads();
+      }
+      for (int b = 0; b < nblk; ++b) {
+        f32x16 p;
+        float cj[16];
+        bool some = false;  // a non-empty group in the block (the same for both halves, below)
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+          const f32x4 cv = *(const f32x4*)(Cs + b * 32 + 8 * w + 4 * h);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            cj[4 * w + e] = cv[e];
+            some |= cv[e] > 0.f;
+            p[4 * w + e] = 0.f;
+          }
+        }
+        if (!__any(some)) continue;
+        p = mfma_rows(Rs + b * 32 * kRow, q, h, qf, p);
+        float bm = -INFINITY;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+          p[v] = cj[v] > 0.f ? scale * p[v] : -INFINITY;
+          bm = fmaxf(bm, p[v]);
+        }
+        const u32x2 pm = halves(__float_as_uint(bm));
+        const float mn = fmaxf(m, fmaxf(__uint_as_float(pm[0]), __uint_as_float(pm[1])));
+        if (__any(mn != m)) {
+          const float alpha = expf(m - mn);
+#pragma unroll
+          for (int v = 0; v < 16; ++v) {
+            o0[v] *= alpha;
+            o1[v] *= alpha;
+          }
+          ssum *= alpha;
+          m = mn;
+        }
+        const float* vr = Vs + (b * 32 + 4 * h) * 64 + q;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+          const float e = cj[v] > 0.f ? expf(p[v] - m) : 0.f;
+          ssum = fmaf(cj[v], e, ssum);
+          const float* vg = vr + (8 * (v >> 2) + (v & 3)) * 64;
+          o0 = __builtin_amdgcn_mfma_f32_32x32x2f32(vg[0], e, o0, 0, 0, 0);
+          o1 = __builtin_amdgcn_mfma_f32_32x32x2f32(vg[32], e, o1, 0, 0, 0);
+        }
+      }
+    }
+    const u32x2 ps = halves(__float_as_uint(ssum));
+    const float stot = __uint_as_float(ps[0]) + __uint_as_float(ps[1]);
+    const float inv = stot > 0.f ? 1.0f / stot : 0.f;
+    if (qi < n) {
+      float* orow = O + (bh * n + qi) * 64 + 4 * h;
+#pragma unroll
+      for (int w = 0; w < 4; ++w) {
+        *(f32x4*)(orow + 8 * w) = f32x4{o0[4 * w], o0[4 * w + 1], o0[4 * w + 2], o0[4 * w + 3]} * inv;
+        *(f32x4*)(orow + 32 + 8 * w) = f32x4{o1[4 * w], o1[4 * w + 1], o1[4 * w + 2], o1[4 * w + 3]} * inv;
+      }
+    }
+  }
+}
+
+// Passes of four 32-row tiles per workgroup: one while the grid has at most
+// about three workgroups per compute unit (the staged groups then cost less
+// than an idle unit), more beyond that.
+int passes(int64_t tiles, int64_t BH, int cap) {
+  const int64_t wgs = ((tiles + 3) / 4) * BH;
+  const int64_t p = (wgs + 767) / 768;
+  return (int)(p < 1 ? 1 : p > cap ? cap : p);
+}
+
+}  // namespace
+
+hipError_t launch_assign_f32(const Dims& d, const float* K, const float* R, const double* nrm64, int32_t* belong,
+                             bool first, hipStream_t st) {
+  TimedLaunch timed(first ? "assign_first" : "assign", st);
+  const int64_t tiles = ((int64_t)d.n + 31) / 32;
+  const int tpw = passes(tiles, d.BH, 16);
+  const float cm = (float)(kD + 4) * 0x1p-23f * (1.0f + 0x1p-10f) * cert_widen();
+  const float cp = 0x1p-19f * (1.0f + 0x1p-10f) * cert_widen();
+  const dim3 grid((unsigned)((tiles + 4 * tpw - 1) / (4 * tpw)), (unsigned)d.BH);
+  hipLaunchKernelGGL(k_assign_f32, grid, dim3(256), (size_t)4 * tpw * 32 * 4, st, K, R, nrm64, belong, d.n, d.N, tpw,
+                     cm, cp);
+  return hipGetLastError();
+}
+
+hipError_t launch_update(const Dims& d, const float* K, const int32_t* perm, const int32_t* goff,
+                         const int32_t* count, float* C, float* R, double* nrm64, hipStream_t st) {
+  TimedLaunch timed("update", st);
+  hipLaunchKernelGGL((k_segsum<true>), dim3((unsigned)((d.N + 3) / 4), (unsigned)d.BH), dim3(256), 0, st, K, perm,
+                     goff, count, d.n, d.N, C, R, nrm64);
+  return hipGetLastError();
+}
+
+hipError_t launch_valuesum(const Dims& d, const float* V, const int32_t* perm, const int32_t* goff,
+                           const int32_t* count, float* vsum, hipStream_t st) {
+  TimedLaunch timed("valuesum", st);
+  hipLaunchKernelGGL((k_segsum<false>), dim3((unsigned)((d.N + 3) / 4), (unsigned)d.BH), dim3(256), 0, st, V, perm,
+                     goff, count, d.n, d.N, vsum, (float*)nullptr, (double*)nullptr);
+  return hipGetLastError();
+}
+
+hipError_t launch_attend_f32(const Dims& d, const float* Q, const float* centroid, const int32_t* count,
+                             const float* vsum, float scale, float* O, hipStream_t st) {
+  TimedLaunch timed("attend", st);
+  const int64_t tiles = ((int64_t)d.n + 31) / 32;
+  const int tpw = passes(tiles, d.BH, 16);
+  hipLaunchKernelGGL(k_attend_f32, dim3((unsigned)((tiles + 4 * tpw - 1) / (4 * tpw)), (unsigned)d.BH), dim3(256), 0,
+                     st, Q, centroid, count, vsum, d.n, d.N, scale, tpw, O);
+  return hipGetLastError();
+}
+
+}  // namespace ga

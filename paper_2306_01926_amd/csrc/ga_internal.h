@@ -117,18 +117,23 @@ hipError_t launch_valuesum_prep(const Dims& d, const void* V, const int32_t* bel
                                 float scale, uint16_t* Vt, float* ginit, hipStream_t st);
 hipError_t launch_bucket(const Dims& d, const int32_t* belong, int32_t* perm, int32_t* goff,
                          int32_t* count, hipStream_t st);
-hipError_t launch_update(const Dims& d, const void* K, const int32_t* perm, const int32_t* goff,
-                         const int32_t* count, float* C, void* R, double* nrm64, uint16_t* nsplit,
-                         hipStream_t st);
-hipError_t launch_valuesum(const Dims& d, const void* V, const int32_t* perm,
-                           const int32_t* goff, const int32_t* count, float* vsum,
-                           hipStream_t st);
 hipError_t launch_attend_prep(const Dims& d, const float* centroid, const int32_t* count,
                               const float* vsum, float scale, uint16_t* Rq, uint16_t* Vt,
                               float* ginit, bool make_rq, hipStream_t st);
 hipError_t launch_attend(const Dims& d, const void* Q, const void* R, const uint16_t* Vt,
                          const float* ginit, const float* centroid, const int32_t* count,
                          const float* vsum, float scale, void* O, hipStream_t st);
+
+// fp32 path (ga_f32.hip): the assignment, the sums of each group's members in
+// ascending key order (centroids and representatives; values), the attention.
+hipError_t launch_assign_f32(const Dims& d, const float* K, const float* R, const double* nrm64, int32_t* belong,
+                             bool first, hipStream_t st);
+hipError_t launch_update(const Dims& d, const float* K, const int32_t* perm, const int32_t* goff,
+                         const int32_t* count, float* C, float* R, double* nrm64, hipStream_t st);
+hipError_t launch_valuesum(const Dims& d, const float* V, const int32_t* perm, const int32_t* goff,
+                           const int32_t* count, float* vsum, hipStream_t st);
+hipError_t launch_attend_f32(const Dims& d, const float* Q, const float* centroid, const int32_t* count,
+                             const float* vsum, float scale, float* O, hipStream_t st);
 
 // Persistent grouping (ga_lloyd.hip): every Lloyd round, the update and (if V
 // is given) the value sums in one launch, for bf16, N <= 128 and shapes whose

@@ -21,10 +21,8 @@
 //                   (transposed) and log2(count) score bias
 //   k_attend_bf16   MFMA scores, block-wise group softmax, MFMA combine
 // Also: k_init, k_assign_bf16 (N <= 1024), k_gsum<0> (first-round sums
-// without partitions), k_gsum<2> (value sums), k_attend_prep; the fp32 path
-// k_assign_exact (fp64 fma-chain scores for every (key, group)), k_bucket
-// (stable counting sort of keys by group), k_segsum (one wave per group sums
-// its members in ascending key order in fp64) and k_attend_f32.
+// without partitions), k_gsum<2> (value sums), k_attend_prep; the fp32 path's k_bucket
+// (stable counting sort of keys by group); its other kernels are in ga_f32.hip.
 #include <hip/hip_runtime.h>
 
 #include <float.h>
@@ -48,51 +46,6 @@ constexpr int kAttDepth = 2;     // query tiles loaded ahead per wave in k_atten
 constexpr int kOs = 72;          // LDS row stride (bf16) of the attention output tiles
 constexpr int kExactB = 4;       // queued keys decided together by one wave in k_assign_reg
 constexpr int kAttMaxN = 256; // groups held in LDS by the bf16 attention kernel
-
-// Representative of one group row from its fp32 centroid value (lane = feature).
-template <class S>
-__device__ void finalize_rep(float c, int64_t row, typename S::T* R, double* nrm64, uint16_t* nsplit) {
-  const int lane = threadIdx.x & 63;
-  const float r = S::rep(c);
-  S::store(R, row * 64 + lane, r);
-  const double nrm = canon_nrm_wave(r);
-  if (lane == 0) {
-    nrm64[row] = nrm;
-    write_nsplit(nrm, nsplit + row * 8);
-  }
-}
-
-// Exact assignment of one key, cooperatively by a whole wave: lanes take
-// groups j = lane, lane + 64, ...; score fma(-2, k.r_j, |r_j|^2) in fp64 with
-// the dot product an fma chain over c = 0..63; lowest index among minima.
-template <class S>
-__device__ int exact_argmin_wave(const typename S::T* __restrict__ krow,
-                                 const typename S::T* __restrict__ Rbh,
-                                 const double* __restrict__ nrm, int N) {
-  const int lane = threadIdx.x & 63;
-  double best = INFINITY;
-  int bj = 0x7fffffff;
-  for (int j = lane; j < N; j += 64) {
-    const typename S::T* r = Rbh + (int64_t)j * 64;
-    double dot = 0.0;
-    for (int c = 0; c < 64; ++c) dot = fma((double)S::load(krow, c), (double)S::load(r, c), dot);
-    const double s = fma(-2.0, dot, nrm[j]);
-    if (s < best) {
-      best = s;
-      bj = j;
-    }
-  }
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) {
-    const double ob = __shfl_xor(best, off);
-    const int oj = __shfl_xor(bj, off);
-    if (ob < best || (ob == best && oj < bj)) {
-      best = ob;
-      bj = oj;
-    }
-  }
-  return bj;
-}
 
 // ------------------------------------------------------------------ init
 // grid (ceil(N/64), BH), 256 threads; groups g0 = 64 x .. g0 + 63.  Each wave
@@ -992,26 +945,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
   }
 }
 
-// ------------------------------------------------------------------ assign (exact)
-// grid (ceil(n / (4 * kpw)), BH), 256 threads; each wave decides kpw keys.
-template <class S>
-__global__ __launch_bounds__(256) void k_assign_exact(const typename S::T* __restrict__ K,
-                                                      const typename S::T* __restrict__ R,
-                                                      const double* __restrict__ nrm64,
-                                                      int32_t* __restrict__ belong, int n, int N,
-                                                      int kpw) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int64_t bh = blockIdx.y;
-  const int64_t key0 = ((int64_t)blockIdx.x * 4 + wave) * kpw;
-  for (int k = 0; k < kpw; ++k) {
-    const int64_t key = key0 + k;
-    if (key >= n) break;
-    const int jb = exact_argmin_wave<S>(K + (bh * n + key) * 64, R + bh * (int64_t)N * 64,
-                                        nrm64 + bh * N, N);
-    if (lane == 0) belong[bh * n + key] = jb;
-  }
-}
-
 // ------------------------------------------------------------------ bucket
 __device__ __forceinline__ int wave_incl_scan(int x) {
   const int lane = threadIdx.x & 63;
@@ -1088,53 +1021,6 @@ __global__ __launch_bounds__(1024) void k_bucket(const int32_t* __restrict__ bel
       wmask[wave * N + g] = 0ull;
     }
     __syncthreads();
-  }
-}
-
-// ------------------------------------------------------------------ segmented sums
-// grid (ceil(N/4), BH), 256 threads: one wave per group, lane = feature.  The
-// group's members are perm[goff .. goff + count) in ascending key order and
-// are summed in that order in fp64.  UPDATE: centroid = (float)(sum / count)
-// (an empty group keeps its centroid) and its representative; otherwise the
-// fp32 rounding of the value sum.
-template <class S, bool UPDATE>
-__global__ __launch_bounds__(256) void k_segsum(const typename S::T* __restrict__ X,
-                                                const int32_t* __restrict__ perm,
-                                                const int32_t* __restrict__ goff,
-                                                const int32_t* __restrict__ count, int n, int N,
-                                                float* __restrict__ out, typename S::T* __restrict__ R,
-                                                double* __restrict__ nrm64, uint16_t* __restrict__ nsplit) {
-  const int lane = threadIdx.x & 63;
-  const int g = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6));
-  const int64_t bh = blockIdx.y;
-  if (g >= N) return;
-  const int64_t row = bh * N + g;
-  const int st = goff[row], cnt = count[row];
-  const int32_t* P = perm + bh * n + st;
-  const typename S::T* Xb = X + bh * (int64_t)n * 64 + lane;
-  double acc = 0.0;
-  int x = 0;
-  for (; x + 4 <= cnt; x += 4) {
-    const int i0 = P[x], i1 = P[x + 1], i2 = P[x + 2], i3 = P[x + 3];
-    const float v0 = S::load(Xb, (int64_t)i0 * 64), v1 = S::load(Xb, (int64_t)i1 * 64);
-    const float v2 = S::load(Xb, (int64_t)i2 * 64), v3 = S::load(Xb, (int64_t)i3 * 64);
-    acc += (double)v0;
-    acc += (double)v1;
-    acc += (double)v2;
-    acc += (double)v3;
-  }
-  for (; x < cnt; ++x) acc += (double)S::load(Xb, (int64_t)P[x] * 64);
-  if (UPDATE) {
-    float c;
-    if (cnt > 0) {
-      c = (float)(acc / (double)cnt);
-      out[row * 64 + lane] = c;
-    } else {
-      c = out[row * 64 + lane];
-    }
-    finalize_rep<S>(c, row, R, nrm64, nsplit);
-  } else {
-    out[row * 64 + lane] = (float)acc;
   }
 }
 
@@ -1831,69 +1717,6 @@ __global__ __launch_bounds__(256) void k_attend_bf16(const uint16_t* __restrict_
   }
 }
 
-// ------------------------------------------------------------------ attention (fp32)
-// grid (ceil(n/256), BH), 256 threads, one query per thread; groups stream
-// through LDS in chunks of 64 (centroid rows and value sums, fp32).  Online
-// softmax with the exact running max over non-empty groups.
-__global__ __launch_bounds__(256) void k_attend_f32(const float* __restrict__ Q,
-                                                    const float* __restrict__ centroid,
-                                                    const int32_t* __restrict__ count,
-                                                    const float* __restrict__ vsum, int n, int N,
-                                                    float scale, float* __restrict__ O) {
-  __shared__ float Rs[64][65];
-  __shared__ float Vs[64][65];
-  __shared__ int cs[64];
-  const int tid = threadIdx.x;
-  const int64_t bh = blockIdx.y;
-  const int64_t qi = (int64_t)blockIdx.x * 256 + tid;
-  const bool valid = qi < n;
-  float qv[64], o[64];
-  const float* qrow = Q + (bh * n + (valid ? qi : 0)) * 64;
-#pragma unroll
-  for (int c = 0; c < 64; ++c) {
-    qv[c] = valid ? qrow[c] : 0.f;
-    o[c] = 0.f;
-  }
-  float m = -INFINITY, ssum = 0.f;
-  for (int base = 0; base < N; base += 64) {
-    __syncthreads();
-    for (int x = tid; x < 64 * 64; x += 256) {
-      const int j = x >> 6, c = x & 63;
-      const bool in = base + j < N;
-      Rs[j][c] = in ? centroid[(bh * N + base + j) * 64 + c] : 0.f;
-      Vs[j][c] = in ? vsum[(bh * N + base + j) * 64 + c] : 0.f;
-    }
-    if (tid < 64) cs[tid] = base + tid < N ? count[bh * N + base + tid] : 0;
-    __syncthreads();
-    const int lim = min(64, N - base);
-    for (int j = 0; j < lim; ++j) {
-      const int cj = cs[j];
-      if (cj <= 0) continue;
-      float dot = 0.f;
-#pragma unroll
-      for (int c = 0; c < 64; ++c) dot = fmaf(qv[c], Rs[j][c], dot);
-      const float p = scale * dot;
-      if (p > m) {
-        const float alpha = expf(m - p);
-#pragma unroll
-        for (int c = 0; c < 64; ++c) o[c] *= alpha;
-        ssum *= alpha;
-        m = p;
-      }
-      const float e = expf(p - m);
-      ssum = fmaf((float)cj, e, ssum);
-#pragma unroll
-      for (int c = 0; c < 64; ++c) o[c] = fmaf(e, Vs[j][c], o[c]);
-    }
-  }
-  if (valid) {
-    const float inv = ssum > 0.f ? 1.0f / ssum : 0.f;
-    float* orow = O + (bh * n + qi) * 64;
-#pragma unroll
-    for (int c = 0; c < 64; ++c) orow[c] = o[c] * inv;
-  }
-}
-
 constexpr size_t kAssignLdsMax = 160 * 1024 - 3 * 1024;  // dynamic LDS budget (static arrays use the rest)
 
 size_t assign_lds(int N, int tpw = 12, bool fused = false) {  // see assign_lds_layout
@@ -2090,29 +1913,23 @@ hipError_t launch_assign(const Dims& d, const void* K, const void* R, const uint
                          const double* nrm64, float* knorm, int32_t* belong, int32_t* mcount,
                          unsigned long long* mrec, bool first, const FusedUpdate& fu, int* parts_out,
                          hipStream_t st) {
+  *parts_out = 0;
+  if (d.dtype != 1) return launch_assign_f32(d, (const float*)K, (const float*)R, nrm64, belong, first, st);
   TimedLaunch timed(first ? "assign_first" : "assign", st);
   set_lds_limits();
-  *parts_out = 0;
-  if (d.dtype == 1) {
-    // |MFMA fp32 accumulation error| <= (d + 4) 2^-24 * 2 * sum|terms| (each of the
-    // d products and the three |r|^2 terms added with at most one rounding,
-    // sequential model, 2x margin; the split itself is within 2^-24 |r|^2);
-    // packing the register index into the low 4 mantissa bits moves a value by
-    // < 2^(4 - 23) of its magnitude.
-    const float cm = (float)(kD + 4) * 0x1p-23f * (1.0f + 0x1p-10f) * cert_widen();
-    const float cp = 0x1p-19f * (1.0f + 0x1p-10f) * cert_widen();
-    const AssignPlan p = plan_assign(d, first);
-    if (p.fused) *parts_out = (int)p.parts;
-    const dim3 grid((unsigned)p.parts, (unsigned)d.BH), block(256);
-    const size_t lds = assign_lds(d.N, (int)p.tpw, p.fused);
-    hipLaunchKernelGGL(p.kern, grid, block, lds, st, (const uint16_t*)K, (const uint16_t*)R, nsplit, nrm64, knorm,
-                       belong, mcount, mrec, d.n, d.N, (int)p.tpw, cm, cp, fu);
-  } else {
-    const int kpw = 4;
-    const dim3 grid(cdiv(d.n, 4 * kpw), (unsigned)d.BH), block(256);
-    hipLaunchKernelGGL(k_assign_exact<F32>, grid, block, 0, st, (const float*)K, (const float*)R, nrm64,
-                       belong, d.n, d.N, kpw);
-  }
+  // |MFMA fp32 accumulation error| <= (d + 4) 2^-24 * 2 * sum|terms| (each of the
+  // d products and the three |r|^2 terms added with at most one rounding,
+  // sequential model, 2x margin; the split itself is within 2^-24 |r|^2);
+  // packing the register index into the low 4 mantissa bits moves a value by
+  // < 2^(4 - 23) of its magnitude.
+  const float cm = (float)(kD + 4) * 0x1p-23f * (1.0f + 0x1p-10f) * cert_widen();
+  const float cp = 0x1p-19f * (1.0f + 0x1p-10f) * cert_widen();
+  const AssignPlan p = plan_assign(d, first);
+  if (p.fused) *parts_out = (int)p.parts;
+  const dim3 grid((unsigned)p.parts, (unsigned)d.BH), block(256);
+  const size_t lds = assign_lds(d.N, (int)p.tpw, p.fused);
+  hipLaunchKernelGGL(p.kern, grid, block, lds, st, (const uint16_t*)K, (const uint16_t*)R, nsplit, nrm64, knorm,
+                     belong, mcount, mrec, d.n, d.N, (int)p.tpw, cm, cp, fu);
   return hipGetLastError();
 }
 
@@ -2177,34 +1994,6 @@ hipError_t launch_valuesum_prep(const Dims& d, const void* V, const int32_t* bel
   return hipGetLastError();
 }
 
-hipError_t launch_update(const Dims& d, const void* K, const int32_t* perm, const int32_t* goff,
-                         const int32_t* count, float* C, void* R, double* nrm64, uint16_t* nsplit,
-                         hipStream_t st) {
-  TimedLaunch timed("update", st);
-  const dim3 grid(cdiv(d.N, 4), (unsigned)d.BH), block(256);
-  if (d.dtype == 1)
-    hipLaunchKernelGGL((k_segsum<BF16, true>), grid, block, 0, st, (const uint16_t*)K, perm, goff, count,
-                       d.n, d.N, C, (uint16_t*)R, nrm64, nsplit);
-  else
-    hipLaunchKernelGGL((k_segsum<F32, true>), grid, block, 0, st, (const float*)K, perm, goff, count, d.n,
-                       d.N, C, (float*)R, nrm64, nsplit);
-  return hipGetLastError();
-}
-
-hipError_t launch_valuesum(const Dims& d, const void* V, const int32_t* perm, const int32_t* goff,
-                           const int32_t* count, float* vsum, hipStream_t st) {
-  TimedLaunch timed("valuesum", st);
-  const dim3 grid(cdiv(d.N, 4), (unsigned)d.BH), block(256);
-  if (d.dtype == 1)
-    hipLaunchKernelGGL((k_segsum<BF16, false>), grid, block, 0, st, (const uint16_t*)V, perm, goff, count,
-                       d.n, d.N, vsum, (uint16_t*)nullptr, (double*)nullptr, (uint16_t*)nullptr);
-  else
-    hipLaunchKernelGGL((k_segsum<F32, false>), grid, block, 0, st, (const float*)V, perm, goff, count, d.n,
-                       d.N, vsum, (float*)nullptr, (double*)nullptr, (uint16_t*)nullptr);
-  return hipGetLastError();
-}
-
-
 hipError_t launch_attend_prep(const Dims& d, const float* centroid, const int32_t* count,
                               const float* vsum, float scale, uint16_t* Rq, uint16_t* Vt, float* ginit,
                               bool make_rq, hipStream_t st) {
@@ -2219,27 +2008,22 @@ hipError_t launch_attend_prep(const Dims& d, const float* centroid, const int32_
 hipError_t launch_attend(const Dims& d, const void* Q, const void* R, const uint16_t* Vt,
                          const float* ginit, const float* centroid, const int32_t* count,
                          const float* vsum, float scale, void* O, hipStream_t st) {
+  if (d.dtype != 1) return launch_attend_f32(d, (const float*)Q, centroid, count, vsum, scale, (float*)O, st);
   TimedLaunch timed("attend", st);
   set_lds_limits();
-  if (d.dtype == 1) {
-    if (d.N > kAttMaxN) return hipErrorInvalidValue;
-    const int64_t tiles = (d.n + 31) / 32;
-    const uint32_t rsign = scale < 0.f ? 0x80008000u : 0u;
-    using AttendFn = void (*)(const uint16_t*, const uint16_t*, const uint16_t*, const float*, int, int, int, float,
-                              uint32_t, int, uint16_t*);
-    static const AttendFn fns[8] = {k_attend_bf16<1>, k_attend_bf16<2>, k_attend_bf16<3>, k_attend_bf16<4>,
-                                    k_attend_bf16<5>, k_attend_bf16<6>, k_attend_bf16<7>, k_attend_bf16<8>};
-    const AttendFn fn = fns[((d.N + 31) >> 5) - 1];
-    // one round of resident workgroups, the same number per slice
-    const int64_t tpw = tiles_per_wave(tiles, d.BH, resident_wgs((const void*)fn, attend_lds(d.N)), 64);
-    const dim3 grid(cdiv(tiles, 4 * tpw), (unsigned)d.BH), block(256);
-    hipLaunchKernelGGL(fn, grid, block, attend_lds(d.N), st, (const uint16_t*)Q, (const uint16_t*)R, Vt, ginit, d.n,
-                       d.N, vt_stride(d.N), clamp_sl2e(scale), rsign, (int)tpw, (uint16_t*)O);
-  } else {
-    const dim3 grid(cdiv(d.n, 256), (unsigned)d.BH), block(256);
-    hipLaunchKernelGGL(k_attend_f32, grid, block, 0, st, (const float*)Q, centroid, count, vsum, d.n, d.N,
-                       scale, (float*)O);
-  }
+  if (d.N > kAttMaxN) return hipErrorInvalidValue;
+  const int64_t tiles = (d.n + 31) / 32;
+  const uint32_t rsign = scale < 0.f ? 0x80008000u : 0u;
+  using AttendFn = void (*)(const uint16_t*, const uint16_t*, const uint16_t*, const float*, int, int, int, float,
+                            uint32_t, int, uint16_t*);
+  static const AttendFn fns[8] = {k_attend_bf16<1>, k_attend_bf16<2>, k_attend_bf16<3>, k_attend_bf16<4>,
+                                  k_attend_bf16<5>, k_attend_bf16<6>, k_attend_bf16<7>, k_attend_bf16<8>};
+  const AttendFn fn = fns[((d.N + 31) >> 5) - 1];
+  // one round of resident workgroups, the same number per slice
+  const int64_t tpw = tiles_per_wave(tiles, d.BH, resident_wgs((const void*)fn, attend_lds(d.N)), 64);
+  const dim3 grid(cdiv(tiles, 4 * tpw), (unsigned)d.BH), block(256);
+  hipLaunchKernelGGL(fn, grid, block, attend_lds(d.N), st, (const uint16_t*)Q, (const uint16_t*)R, Vt, ginit, d.n,
+                     d.N, vt_stride(d.N), clamp_sl2e(scale), rsign, (int)tpw, (uint16_t*)O);
   return hipGetLastError();
 }
 
