@@ -127,8 +127,8 @@ int run_cluster(const ga::Dims& d, const void* K, int32_t iters, const float* in
     if (parts > 0) {
       GA_LAUNCH(ga::launch_part_finish(d, parts, fu, w.S64, count, C, w.R, w.nrm64, w.nsplit, st), "update launch");
     } else if (d.dtype == GA_BF16) {
-      GA_LAUNCH(ga::launch_gsum(d, t == 0 ? 0 : 1, K, belong, w.mrec, mc_cur, mc_next, w.S64, count, C, w.R,
-                                w.nrm64, w.nsplit, st), "update launch");
+      GA_LAUNCH(t == 0 ? ga::launch_sums_full(d, K, belong, w, count, C, st)
+                       : ga::launch_sums_delta(d, K, mc_cur, mc_next, w, count, C, st), "update launch");
     } else {
       GA_LAUNCH(ga::launch_bucket(d, belong, w.perm, w.goff, count, st), "bucket launch");
       GA_LAUNCH(ga::launch_update(d, (const float*)K, w.perm, w.goff, count, C, (float*)w.R, w.nrm64, st), "update launch");
@@ -141,8 +141,7 @@ int run_cluster(const ga::Dims& d, const void* K, int32_t iters, const float* in
 int run_valuesum(const ga::Dims& d, const void* V, const int32_t* belong, int32_t* count, float* vsum,
                  const ga::Workspace& w, hipStream_t st) {
   if (d.dtype == GA_BF16) {
-    GA_LAUNCH(ga::launch_gsum(d, 2, V, belong, nullptr, nullptr, nullptr, nullptr, nullptr, vsum, nullptr, nullptr,
-                              nullptr, st), "value-sum launch");
+    GA_LAUNCH(ga::launch_valuesum_bf16(d, V, belong, w, vsum, st), "value-sum launch");
   } else {
     GA_LAUNCH(ga::launch_bucket(d, belong, w.perm, w.goff, count, st), "bucket launch");
     GA_LAUNCH(ga::launch_valuesum(d, (const float*)V, w.perm, w.goff, count, vsum, st), "value-sum launch");
@@ -172,7 +171,7 @@ int run_forward(const ga::Dims& d, const void* Q, const void* K, const void* V, 
   GA_TRY(run_cluster(d, K, iters, nullptr, a, cnt, C, w, st));
   if (d.dtype == GA_BF16) {
     // the value sums go straight into the attention's transposed means and bias
-    GA_LAUNCH(ga::launch_valuesum_prep(d, V, a, cnt, scale, w.Vt, w.ginit, st), "value-sum launch");
+    GA_LAUNCH(ga::launch_valuesum_prep(d, V, a, cnt, scale, w, st), "value-sum launch");
     GA_LAUNCH(ga::launch_attend(d, Q, w.R, w.Vt, w.ginit, C, cnt, w.vsum, scale, O, st), "attention launch");
   } else {
     // the last stable bucket pass sorted the keys by the final assignment: reuse it

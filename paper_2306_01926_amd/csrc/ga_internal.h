@@ -106,15 +106,19 @@ hipError_t launch_assign(const Dims& d, const void* K, const void* R, const uint
 hipError_t launch_part_finish(const Dims& d, int parts, const FusedUpdate& fu, double* S64,
                               int32_t* count, float* C, void* R, double* nrm64, uint16_t* nsplit,
                               hipStream_t st);
-// bf16 path: exact fp64 group sums, each workgroup finishing its own groups (see ga_kernels.hip)
-hipError_t launch_gsum(const Dims& d, int mode, const void* X, const int32_t* belong,
-                       const unsigned long long* mrec, const int32_t* mcount_cur, int32_t* mcount_next,
-                       double* S64, int32_t* count, float* out, void* R, double* nrm64, uint16_t* nsplit,
-                       hipStream_t st);
-// bf16 forward: value sums straight into the attention inputs (Vt, ginit), in
-// place of launch_gsum(mode 2) + launch_attend_prep
-hipError_t launch_valuesum_prep(const Dims& d, const void* V, const int32_t* belong, const int32_t* count,
-                                float scale, uint16_t* Vt, float* ginit, hipStream_t st);
+// bf16 path, exact fp64 group sums (see ga_kernels.hip): of every key (first
+// round) and of the round's moved keys, each with the update of C, R, |r|^2;
+// and of the values.  The first and the last keep partial sums in w.lxs / lxc.
+hipError_t launch_sums_full(const Dims& d, const void* K, const int32_t* belong, const Workspace& w, int32_t* count,
+                            float* C, hipStream_t st);
+hipError_t launch_sums_delta(const Dims& d, const void* K, const int32_t* mcount_cur, int32_t* mcount_next,
+                             const Workspace& w, int32_t* count, float* C, hipStream_t st);
+hipError_t launch_valuesum_bf16(const Dims& d, const void* V, const int32_t* belong, const Workspace& w, float* vsum,
+                                hipStream_t st);
+// bf16 forward: value sums straight into the attention inputs (w.Vt, w.ginit),
+// in place of launch_valuesum_bf16 + launch_attend_prep
+hipError_t launch_valuesum_prep(const Dims& d, const void* V, const int32_t* belong, int32_t* count, float scale,
+                                const Workspace& w, hipStream_t st);
 hipError_t launch_bucket(const Dims& d, const int32_t* belong, int32_t* perm, int32_t* goff,
                          int32_t* count, hipStream_t st);
 hipError_t launch_attend_prep(const Dims& d, const float* centroid, const int32_t* count,

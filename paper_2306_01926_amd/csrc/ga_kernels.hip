@@ -1091,26 +1091,112 @@ __device__ __forceinline__ void run_sums(const uint32_t* ent, const uint8_t* eg,
 // The member sums of the bf16 path are exact in fp64 (see above), so they can
 // be accumulated in any order and split any way: no global bucketing.
 //
-// k_gsum: grid (ceil(N / 32), BH), 256 threads.  Workgroup x owns groups
-// g0 = 32 x .. g0 + 31 of slice bh and finishes them itself:
+// k_gsum: grid (ceil(N / 32), BH, Z), 256 threads.  Workgroup (x, bh, z) sums
+// the rows of the keys [z ck, (z + 1) ck) of slice bh that belong to groups
+// g0 = 32 x .. g0 + 31 and, with Z = 1, finishes the groups itself:
 //   MODE 0 (first round): S = sum of the member key rows, count = members
 //   MODE 2 (value sums):  vsum = (float) sum of the member value rows
 //   MODE 3 (value sums for the attention): the bf16 value means, transposed,
 //           and the log2(count) score bias, as k_attend_prep forms them
 // MODE 0 then sets C = (float)(S / count) (an empty group keeps C), R =
 // bf16(C), the canonical fp64 |r|^2 (fma chain over c = 0..63, one lane per
-// group) and its split.  (The later rounds' update is k_gdelta.)
+// group) and its split.  (The later rounds' update is k_gdelta.)  With Z > 1
+// every workgroup writes its partial fp64 sums (and MODE 0's counts) and
+// k_gsum_finish adds the Z parts: the sums are exact, so the split cannot
+// change a bit.
 //
 // Per chunk of keys, all loaded at once:
 // 1. count the keys of every owned group and scatter them into an LDS list
 //    sorted by group (a local counting sort; one LDS atomic per key);
 // 2. run_sums adds the rows into the LDS sums;
-// 3. finish the owned groups.
+// 3. finish the owned groups, or write the partial sums.
 constexpr int kGsumG = 32;
 constexpr int kGsumList = 8192;  // entry capacity of the sorted chunk list
+
+// Finishes groups g0 .. g0 + ng - 1 of slice bh from their fp64 sums
+// acc[kGsumG][64] and (MODE 0) counts dcnt; scratch: kGsumG * 65 words of LDS.
+template <int MODE>
+__device__ __forceinline__ void gsum_finish(const double* acc, const int* dcnt, uint32_t* scratch, int64_t bh, int g0,
+                                            int ng, int N, double* __restrict__ S64, int32_t* __restrict__ count,
+                                            float* __restrict__ out, uint16_t* __restrict__ R,
+                                            double* __restrict__ nrm64, uint16_t* __restrict__ nsplit,
+                                            float inv_sl2e, int vts) {
+  const int tid = threadIdx.x;
+  float* rsh = (float*)scratch;  // [32][65] bf16 representatives
+  // element (g, c) = (idx / 64, idx % 64), 8 per thread
+  constexpr int EPT = kGsumG * 64 / 256;
+  int pc[EPT];
+#pragma unroll
+  for (int u = 0; u < EPT; ++u) {
+    const int idx = tid + 256 * u, g = idx >> 6;
+    const int64_t row = bh * N + g0 + min(g, ng - 1);
+    pc[u] = MODE == 3 ? count[row] : 0;
+  }
+  if (MODE == 3) {
+    // value means mu = (float) sum / count (0 for an empty or padded group)
+    // as bf16, transposed through LDS into Vt[feature][group] (R, 8-byte
+    // segments), and the score bias log2(count) / sl2e (-inf if empty) into
+    // out[bh][Npad]
+    uint16_t* mt = (uint16_t*)scratch;  // [64][36]
+#pragma unroll
+    for (int u = 0; u < EPT; ++u) {
+      const int idx = tid + 256 * u, g = idx >> 6, c = idx & 63;
+      const float vs = g < ng ? (float)acc[g * 64 + c] : 0.f;
+      const int cnt = g < ng ? pc[u] : 0;
+      mt[c * 36 + g] = (uint16_t)f32_to_bf16(cnt > 0 ? vs / (float)cnt : 0.f);
+      if (c == 0) out[bh * ((N + 31) & ~31) + g0 + g] = cnt > 0 ? log2f((float)cnt) * inv_sl2e : -INFINITY;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const int x = tid + 256 * u, f = x >> 3, q4 = x & 7;  // 64 features x 8 segments of 4 groups
+      *(uint2*)(R + (bh * 64 + f) * (int64_t)vts + g0 + 4 * q4) = *(const uint2*)(mt + f * 36 + 4 * q4);
+    }
+    return;
+  }
+#pragma unroll
+  for (int u = 0; u < EPT; ++u) {
+    const int idx = tid + 256 * u, g = idx >> 6, c = idx & 63;
+    if (g >= ng) continue;
+    const int64_t row = bh * N + g0 + g;
+    const double s = acc[g * 64 + c];
+    if (MODE == 2) {
+      out[row * 64 + c] = (float)s;
+      continue;
+    }
+    const int cnt = dcnt[g];
+    S64[row * 64 + c] = s;
+    if (c == 0) count[row] = cnt;
+    float cf;
+    if (cnt > 0) {
+      cf = (float)(s / (double)cnt);
+      out[row * 64 + c] = cf;
+    } else {
+      cf = out[row * 64 + c];
+    }
+    const float r = BF16::rep(cf);
+    BF16::store(R, row * 64 + c, r);
+    rsh[g * 65 + c] = r;
+  }
+  if (MODE == 2) return;
+  __syncthreads();
+  if (tid < ng) {
+    const int64_t row = bh * N + g0 + tid;
+    double nrm = 0.0;
+#pragma unroll 8
+    for (int c = 0; c < 64; ++c) {
+      const double rc = (double)rsh[tid * 65 + c];
+      nrm = fma(rc, rc, nrm);
+    }
+    nrm64[row] = nrm;
+    write_nsplit(nrm, nsplit + row * 8);
+  }
+}
+
 template <int MODE>
 __global__ __launch_bounds__(256) void k_gsum(const uint16_t* __restrict__ X, const int32_t* __restrict__ belong,
-                                              int n, int N, double* __restrict__ S64,
+                                              int n, int N, int ck, double* __restrict__ part,
+                                              int32_t* __restrict__ pcnt, double* __restrict__ S64,
                                               int32_t* __restrict__ count, float* __restrict__ out, uint16_t* __restrict__ R,
                                               double* __restrict__ nrm64, uint16_t* __restrict__ nsplit,
                                               float inv_sl2e, int vts) {
@@ -1118,25 +1204,23 @@ __global__ __launch_bounds__(256) void k_gsum(const uint16_t* __restrict__ X, co
   __shared__ uint8_t eg[kGsumList];    // their groups, relative to g0
   __shared__ double acc[kGsumG * 64];  // [g][c] sums of this workgroup's groups
   __shared__ int ecnt[kGsumG], eoff[kGsumG + 1], ecur[kGsumG], dcnt[kGsumG];
-  float* rsh = (float*)ent;            // [32][65] bf16 representatives, after the sums
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int64_t bh = blockIdx.y;
   const int g0 = blockIdx.x * kGsumG, ng = min(kGsumG, N - g0);
   for (int i = tid; i < kGsumG * 64; i += 256) acc[i] = 0.0;
   if (tid < kGsumG) dcnt[tid] = 0;
 
-  const int64_t total = n;
+  const int64_t begin = (int64_t)blockIdx.z * ck, total = min((int64_t)n, begin + ck);
   constexpr int CH = kGsumList;  // keys per chunk
   constexpr int PER = CH / 256;
   const uint16_t* Xb = X + bh * (int64_t)n * 64;
-  for (int64_t c0 = 0; c0 < total; c0 += CH) {
-    int kv[PER], gj[PER];
+  for (int64_t c0 = begin; c0 < total; c0 += CH) {
+    int gj[PER];
     // every lane loads (index clamped into the chunk) so that the loads overlap
 #pragma unroll
     for (int u = 0; u < PER; ++u) {
-      const int64_t e = c0 + tid + 256 * u, ec = min(e, total - 1);
-      kv[u] = (int)e;
-      gj[u] = belong[bh * n + ec] - g0;
+      const int64_t e = c0 + tid + 256 * u;
+      gj[u] = belong[bh * n + min(e, total - 1)] - g0;
     }
 #pragma unroll
     for (int u = 0; u < PER; ++u)
@@ -1173,7 +1257,7 @@ __global__ __launch_bounds__(256) void k_gsum(const uint16_t* __restrict__ X, co
       const int g = gj[u];
       if ((unsigned)g < (unsigned)ng) {
         const int pos = atomicAdd(&ecur[g], 1);
-        ent[pos] = (uint32_t)kv[u];
+        ent[pos] = (uint32_t)(c0 + tid + 256 * u);
         eg[pos] = (uint8_t)g;
       }
     }
@@ -1183,76 +1267,52 @@ __global__ __launch_bounds__(256) void k_gsum(const uint16_t* __restrict__ X, co
     __syncthreads();
   }
 
-  // 3. finish the owned groups: element (g, c) = (idx / 64, idx % 64), 8 per thread
-  constexpr int EPT = kGsumG * 64 / 256;
-  int pc[EPT];
-#pragma unroll
-  for (int u = 0; u < EPT; ++u) {
-    const int idx = tid + 256 * u, g = idx >> 6;
-    const int64_t row = bh * N + g0 + min(g, ng - 1);
-    pc[u] = MODE == 3 ? count[row] : 0;
-  }
-  __syncthreads();  // (total == 0: dcnt, acc initialised above)
-  if (MODE == 3) {
-    // value means mu = (float) sum / count (0 for an empty or padded group)
-    // as bf16, transposed through LDS into Vt[feature][group] (R, 8-byte
-    // segments), and the score bias log2(count) / sl2e (-inf if empty) into
-    // out[bh][Npad]
-    uint16_t* mt = (uint16_t*)ent;  // [64][36]
-#pragma unroll
-    for (int u = 0; u < EPT; ++u) {
-      const int idx = tid + 256 * u, g = idx >> 6, c = idx & 63;
-      const float vs = g < ng ? (float)acc[g * 64 + c] : 0.f;
-      const int cnt = g < ng ? pc[u] : 0;
-      mt[c * 36 + g] = (uint16_t)f32_to_bf16(cnt > 0 ? vs / (float)cnt : 0.f);
-      if (c == 0) out[bh * ((N + 31) & ~31) + g0 + g] = cnt > 0 ? log2f((float)cnt) * inv_sl2e : -INFINITY;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      const int x = tid + 256 * u, f = x >> 3, q4 = x & 7;  // 64 features x 8 segments of 4 groups
-      *(uint2*)(R + (bh * 64 + f) * (int64_t)vts + g0 + 4 * q4) = *(const uint2*)(mt + f * 36 + 4 * q4);
-    }
+  // 3. finish the owned groups, or hand the sums on
+  if (gridDim.z == 1) {
+    gsum_finish<MODE>(acc, dcnt, ent, bh, g0, ng, N, S64, count, out, R, nrm64, nsplit, inv_sl2e, vts);
     return;
   }
+  const int64_t row0 = (bh * gridDim.z + blockIdx.z) * (int64_t)((N + 31) & ~31) + g0;
+  for (int i = 2 * tid; i < kGsumG * 64; i += 512) *(double2*)(part + row0 * 64 + i) = *(const double2*)(acc + i);
+  if (MODE == 0 && tid < kGsumG) pcnt[row0 + tid] = dcnt[tid];
+}
+
+// k_gsum_finish: grid (ceil(N / 32), BH), 256 threads: adds the Z partial
+// sums (and MODE 0's counts) of k_gsum in order and finishes the groups.
+template <int MODE>
+__global__ __launch_bounds__(256) void k_gsum_finish(const double* __restrict__ part, const int32_t* __restrict__ pcnt,
+                                                     int Z, int N, double* __restrict__ S64,
+                                                     int32_t* __restrict__ count, float* __restrict__ out,
+                                                     uint16_t* __restrict__ R, double* __restrict__ nrm64,
+                                                     uint16_t* __restrict__ nsplit, float inv_sl2e, int vts) {
+  __shared__ __align__(16) double acc[kGsumG * 64];
+  __shared__ int dcnt[kGsumG];
+  __shared__ uint32_t scratch[kGsumG * 65];
+  const int tid = threadIdx.x;
+  const int64_t bh = blockIdx.y, Npad = (N + 31) & ~31;
+  const int g0 = blockIdx.x * kGsumG, ng = min(kGsumG, N - g0);
+  const double* p = part + (bh * Z * Npad + g0) * 64 + 2 * tid;
+  double2 sum[4];
 #pragma unroll
-  for (int u = 0; u < EPT; ++u) {
-    const int idx = tid + 256 * u, g = idx >> 6, c = idx & 63;
-    if (g >= ng) continue;
-    const int64_t row = bh * N + g0 + g;
-    const double s = acc[g * 64 + c];
-    if (MODE == 2) {
-      out[row * 64 + c] = (float)s;
-      continue;
-    }
-    const double S = s;
-    const int cnt = dcnt[g];
-    S64[row * 64 + c] = S;
-    if (c == 0) count[row] = cnt;
-    float cf;
-    if (cnt > 0) {
-      cf = (float)(S / (double)cnt);
-      out[row * 64 + c] = cf;
-    } else {
-      cf = out[row * 64 + c];
-    }
-    const float r = BF16::rep(cf);
-    BF16::store(R, row * 64 + c, r);
-    rsh[g * 65 + c] = r;
-  }
-  if (MODE == 2) return;
-  __syncthreads();
-  if (tid < ng) {
-    const int64_t row = bh * N + g0 + tid;
-    double nrm = 0.0;
+  for (int u = 0; u < 4; ++u) sum[u] = double2{0.0, 0.0};
 #pragma unroll 8
-    for (int c = 0; c < 64; ++c) {
-      const double rc = (double)rsh[tid * 65 + c];
-      nrm = fma(rc, rc, nrm);
+  for (int z = 0; z < Z; ++z) {
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const double2 v = *(const double2*)(p + z * Npad * 64 + 512 * u);
+      sum[u].x += v.x;
+      sum[u].y += v.y;
     }
-    nrm64[row] = nrm;
-    write_nsplit(nrm, nsplit + row * 8);
   }
+#pragma unroll
+  for (int u = 0; u < 4; ++u) *(double2*)(acc + 2 * tid + 512 * u) = sum[u];
+  if (MODE == 0 && tid < kGsumG) {
+    int c = 0;
+    for (int z = 0; z < Z; ++z) c += pcnt[(bh * Z + z) * Npad + g0 + tid];
+    dcnt[tid] = c;
+  }
+  __syncthreads();
+  gsum_finish<MODE>(acc, dcnt, scratch, bh, g0, ng, N, S64, count, out, R, nrm64, nsplit, inv_sl2e, vts);
 }
 
 // ------------------------------------------------------------------ later-round update (bf16)
@@ -1957,25 +2017,60 @@ hipError_t launch_bucket(const Dims& d, const int32_t* belong, int32_t* perm, in
   return hipGetLastError();
 }
 
-hipError_t launch_gsum(const Dims& d, int mode, const void* X, const int32_t* belong,
-                       const unsigned long long* mrec, const int32_t* mcount_cur, int32_t* mcount_next,
-                       double* S64, int32_t* count, float* out, void* R, double* nrm64, uint16_t* nsplit,
-                       hipStream_t st) {
-  TimedLaunch timed(mode == 0 ? "sums_full" : mode == 1 ? "sums_delta" : "valuesum", st);
-  const dim3 grid(cdiv(d.N, kGsumG), (unsigned)d.BH), block(256);
-  const size_t lds = 0;
-  const uint16_t* Xb = (const uint16_t*)X;
-  uint16_t* Rb = (uint16_t*)R;
-  if (mode == 0)
-    hipLaunchKernelGGL(k_gsum<0>, grid, block, lds, st, Xb, belong, d.n, d.N, S64, count, out, Rb, nrm64, nsplit,
-                       0.f, 0);
-  else if (mode == 1)
-    hipLaunchKernelGGL(k_gdelta, grid, block, 0, st, Xb, mrec, mcount_cur, mcount_next, d.n, d.N, S64, count, out,
-                       Rb, nrm64, nsplit);
-  else
-    hipLaunchKernelGGL(k_gsum<2>, grid, block, lds, st, Xb, belong, d.n, d.N, S64, count, out, Rb, nrm64, nsplit,
-                       0.f, 0);
+// Parts that a launch of k_gsum splits each slice's keys into.  A second launch
+// and the partial sums cost about 5 us, so a slice is split only where the
+// launch has at most half as many workgroups as compute units and each part
+// keeps at least 1024 rows of a 32-group block: 64 workgroups (32 slices of
+// 20000 rows, 64 groups) 84 -> 28 + 6 us with 8 parts, one workgroup (a slice of
+// 20000 rows, 10 groups) about 100 -> 20 us with 16; 256 workgroups (32 slices,
+// 256 groups) 44 us whole, 47 + 9 in two parts.  The partial sums live in the
+// exchange buffer (w.lxs, w.lxc; idle outside a persistent grouping), whose
+// rows bound the parts too.
+static int gsum_parts(const Dims& d) {
+  const int64_t Npad = (d.N + 31) & ~31, wgs = Npad / 32 * d.BH;
+  if (wgs < 1 || wgs > 128) return 1;
+  const int64_t cap = (int64_t)lloyd_exchange_rows(d) / (d.BH * Npad);
+  const int64_t z = min(min(512 / wgs, (int64_t)d.n * 32 / Npad / 1024), cap);
+  return (int)max((int64_t)1, z);
+}
+
+template <int MODE>
+static hipError_t run_gsum(const Dims& d, const uint16_t* X, const int32_t* belong, double* part, int32_t* pcnt,
+                           double* S64, int32_t* count, float* out, uint16_t* R, double* nrm64, uint16_t* nsplit,
+                           float inv_sl2e, int vts, hipStream_t st) {
+  const int Z = gsum_parts(d), ck = (int)cdiv(d.n, Z);
+  const dim3 grid(cdiv(d.N, kGsumG), (unsigned)d.BH, (unsigned)Z), block(256);
+  {
+    TimedLaunch timed(MODE == 0 ? "sums_full" : "valuesum", st);
+    hipLaunchKernelGGL(k_gsum<MODE>, grid, block, 0, st, X, belong, d.n, d.N, ck, part, pcnt, S64, count, out, R,
+                       nrm64, nsplit, inv_sl2e, vts);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess || Z == 1) return e;
+  }
+  TimedLaunch timed("sums_finish", st);
+  hipLaunchKernelGGL(k_gsum_finish<MODE>, dim3(grid.x, grid.y), block, 0, st, part, pcnt, Z, d.N, S64, count, out, R,
+                     nrm64, nsplit, inv_sl2e, vts);
   return hipGetLastError();
+}
+
+hipError_t launch_sums_full(const Dims& d, const void* K, const int32_t* belong, const Workspace& w, int32_t* count,
+                            float* C, hipStream_t st) {
+  return run_gsum<0>(d, (const uint16_t*)K, belong, w.lxs, w.lxc, w.S64, count, C, (uint16_t*)w.R, w.nrm64, w.nsplit,
+                     0.f, 0, st);
+}
+
+hipError_t launch_sums_delta(const Dims& d, const void* K, const int32_t* mcount_cur, int32_t* mcount_next,
+                             const Workspace& w, int32_t* count, float* C, hipStream_t st) {
+  TimedLaunch timed("sums_delta", st);
+  hipLaunchKernelGGL(k_gdelta, dim3(cdiv(d.N, kGsumG), (unsigned)d.BH), dim3(256), 0, st, (const uint16_t*)K, w.mrec,
+                     mcount_cur, mcount_next, d.n, d.N, w.S64, count, C, (uint16_t*)w.R, w.nrm64, w.nsplit);
+  return hipGetLastError();
+}
+
+hipError_t launch_valuesum_bf16(const Dims& d, const void* V, const int32_t* belong, const Workspace& w, float* vsum,
+                                hipStream_t st) {
+  return run_gsum<2>(d, (const uint16_t*)V, belong, w.lxs, w.lxc, nullptr, nullptr, vsum, nullptr, nullptr, nullptr,
+                     0.f, 0, st);
 }
 
 static float clamp_sl2e(float scale) {
@@ -1983,15 +2078,10 @@ static float clamp_sl2e(float scale) {
   return s < 1e-30f ? 1e-30f : s;
 }
 
-hipError_t launch_valuesum_prep(const Dims& d, const void* V, const int32_t* belong, const int32_t* count,
-                                float scale, uint16_t* Vt, float* ginit, hipStream_t st) {
-  TimedLaunch timed("valuesum", st);
-  if (d.dtype != 1) return hipErrorInvalidValue;
-  const dim3 grid(cdiv(d.N, kGsumG), (unsigned)d.BH), block(256);
-  hipLaunchKernelGGL(k_gsum<3>, grid, block, 0, st, (const uint16_t*)V, belong, d.n, d.N, (double*)nullptr,
-                     (int32_t*)count, ginit, Vt, (double*)nullptr, (uint16_t*)nullptr, 1.0f / clamp_sl2e(scale),
-                     vt_stride(d.N));
-  return hipGetLastError();
+hipError_t launch_valuesum_prep(const Dims& d, const void* V, const int32_t* belong, int32_t* count, float scale,
+                                const Workspace& w, hipStream_t st) {
+  return run_gsum<3>(d, (const uint16_t*)V, belong, w.lxs, w.lxc, nullptr, count, w.ginit, w.Vt, nullptr, nullptr,
+                     1.0f / clamp_sl2e(scale), vt_stride(d.N), st);
 }
 
 hipError_t launch_attend_prep(const Dims& d, const float* centroid, const int32_t* count,
