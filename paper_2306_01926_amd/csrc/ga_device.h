@@ -45,11 +45,19 @@ __device__ __forceinline__ float min2(float a, float b) { return __builtin_amdgc
 __device__ __forceinline__ float max2(float a, float b) { return __builtin_amdgcn_fmed3f(a, b, FLT_MAX); }
 
 // v_min3_f32 without the NaN canonicalisation the compiler adds around
-// fminf-based min3 (the operands are finite scores).
+// fminf-based min3 (the operands are finite scores).  Never an MFMA's result
+// itself: the wait states between an MFMA and a VALU read of its registers are
+// not kept for inline assembly (the packed scores are VALU results); min3m is
+// for those.
 __device__ __forceinline__ float min3f(float a, float b, float c) {
   float r;
   asm("v_min3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
   return r;
+}
+
+// v_minimum3_f32 (no NaN canonicalisation either).
+__device__ __forceinline__ float min3m(float a, float b, float c) {
+  return __builtin_elementwise_minimum(__builtin_elementwise_minimum(a, b), c);
 }
 
 __device__ __forceinline__ float readlane_f(float x, int l) {
@@ -189,6 +197,51 @@ __device__ __forceinline__ void reduce_block(const f32x16& acc, int blk, float& 
   }
   B1 = M1 < prev ? blk : B1;
 }
+
+// The two smallest of K class minima, ranked as packed floats: the low 3
+// mantissa bits are replaced by the class (K <= 8), so one min / med3 chain keeps
+// the best's value and class and the second best's value.
+constexpr uint32_t kClassMask = 7u;
+template <int K>
+__device__ __forceinline__ void top2_classes(const float (&m)[K], float& M1, float& M2) {
+  float x[K];
+#pragma unroll
+  for (int k = 0; k < K; ++k) x[k] = __uint_as_float((__float_as_uint(m[k]) & ~kClassMask) | (uint32_t)k);
+  M1 = min2(x[0], x[1]);
+  M2 = max2(x[0], x[1]);
+#pragma unroll
+  for (int k = 2; k + 1 < K; k += 2) {
+    const float t = __builtin_amdgcn_fmed3f(M1, x[k], x[k + 1]);
+    M1 = min3m(M1, x[k], x[k + 1]);
+    M2 = min2(M2, t);
+  }
+}
+
+// Two partitions of a lane's scores, one running minimum per class, in place of
+// a top-2 chain over all of them: 8 classes by accumulator register % 8 (over
+// all blocks) and one class per half block (registers 0-7 and 8-15).  A class of
+// the first and a class of the second share exactly one group, so any group but
+// the best differs from it in one of the two, and the smaller of the two
+// partitions' second best bounds every other group's score.  Certification: the
+// packed minima of the 8 classes are off by at most 2^-20 relative, half of the
+// bound's cp (the half blocks are not packed); a best group outside the winning
+// class of a partition would need that partition's second best within
+// 2 (cm M + packing) of its best, which differs from the packed best by at most the
+// packing error, so the bound E with cp = 2^-19 covers all of it.  1.4 VALU
+// operations per score, 2.4 for the packed chain of reduce_block.
+//
+// fold_block: one block's 16 scores into the 8 classes, and the minima of its
+// two halves.
+__device__ __forceinline__ void fold_block(const f32x16& x, float (&mA)[8], float& lo, float& hi) {
+#pragma unroll
+  for (int k = 0; k < 8; ++k) mA[k] = min3m(mA[k], x[k], x[k + 8]);
+  lo = min3m(min3m(min3m(min3m(x[0], x[1], x[2]), x[3], x[4]), x[5], x[6]), x[7], x[7]);
+  hi = min3m(min3m(min3m(min3m(x[8], x[9], x[10]), x[11], x[12]), x[13], x[14]), x[15], x[15]);
+}
+
+// The lane-local group index (without the lane half's 4 h) of register v of
+// block b: 32 b + 8 (v / 4) + v % 4.
+__device__ __forceinline__ int local_group(int b, int v) { return 32 * b + v + (v & 12); }
 
 // Bounds shared by every tile of a slice: the largest |r|^2 and |r| (with
 // margins for their fp32 evaluation) and the error constants of the launch.

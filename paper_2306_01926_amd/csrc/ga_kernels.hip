@@ -123,8 +123,8 @@ struct AssignLists {
 };
 
 
-// Decision for the keys of two tiles A and B at once, given each lane's top-2
-// over its half of the groups for both: one lane swap per value leaves lane
+// Decision for the keys of two tiles A and B at once, given each lane's best
+// two over its half of the groups and the best's local_group for both: one lane swap per value leaves lane
 // q < 32 with both halves of key q of A and lane 32 + q with both halves of
 // key q of B, so every lane decides one key.  The lane merges its halves,
 // certifies the packed best against the error bound E, stages the group and
@@ -138,18 +138,17 @@ struct AssignLists {
 // |terms|) and the packing part cp * (|M1| + 3 cm M); the last two terms cover
 // the fp32 evaluation of E and of M1 + 2E.
 template <bool FIRST>
-__device__ __forceinline__ void decide_pair(float M1a, float M2a, int B1a, float M1b, float M2b, int B1b, float knv,
+__device__ __forceinline__ void decide_pair(float M1a, float M2a, int Ja, float M1b, float M2b, int Jb, float knv,
                                             int oldv, int lk, bool stage, bool valid, int N, const Certify& cf,
                                             const AssignLists& sh, int wave, int& wn, int& un) {
   const auto p1 = __builtin_amdgcn_permlane32_swap(__float_as_uint(M1a), __float_as_uint(M1b), false, false);
   const auto p2 = __builtin_amdgcn_permlane32_swap(__float_as_uint(M2a), __float_as_uint(M2b), false, false);
-  const auto pb = __builtin_amdgcn_permlane32_swap((uint32_t)B1a, (uint32_t)B1b, false, false);
+  const auto pj = __builtin_amdgcn_permlane32_swap((uint32_t)Ja, (uint32_t)Jb, false, false);
   // [0]: the best over the groups held by lanes 0-31, [1]: by lanes 32-63
   const float a1 = __uint_as_float(p1[0]), b1 = __uint_as_float(p1[1]);
   // the half held by lanes 32-63 wins only with a strictly smaller best
   const bool hi_wins = b1 < a1;
-  const uint32_t vw = __float_as_uint(hi_wins ? b1 : a1) & kPackMask;
-  const int jstar = 32 * (int)(hi_wins ? pb[1] : pb[0]) + 8 * (int)(vw >> 2) + (hi_wins ? 4 : 0) + (int)(vw & 3);
+  const int jstar = hi_wins ? (int)pj[1] + 4 : (int)pj[0];
   const float best = min2(a1, b1);
   const float second = min2(max2(a1, b1), min2(__uint_as_float(p2[0]), __uint_as_float(p2[1])));
   const float Mk = cf.nmaxf + 2.0f * knv * cf.rmaxf;
@@ -696,7 +695,12 @@ __global__ __launch_bounds__(256) void k_part_finish(const double* __restrict__ 
 // 1024 (k_assign_reg covers N <= 128).  Each wave owns tpw consecutive 32-key
 // tiles and scores them two at a time (two independent MFMA / VALU chains
 // sharing the A-operand reads, which come from LDS); the next pair's key
-// fragments are loaded while the current pair is scored.
+// fragments are loaded while the current pair is scored.  The scores fold into
+// class minima (fold_block) instead of the packed top-2 chain: launches of 32
+// slices of 20000 keys against 256 groups 40.5 -> 39 us, 16 slices of 10000
+// against 512 groups 38.5 -> 36 us.  (k_assign_reg and the one-launch grouping
+// keep the chain: there the class minima spill at 128 groups, and the key
+// stream, not the VALU, bounds the loop.)
 template <bool FIRST>
 __global__ __launch_bounds__(256) void k_assign_bf16(
     const uint16_t* __restrict__ K, const uint16_t* __restrict__ R, const uint16_t* __restrict__ nsplit,
@@ -773,8 +777,14 @@ __global__ __launch_bounds__(256) void k_assign_bf16(
       }
     }
 
-    float M1[2] = {FLT_MAX, FLT_MAX}, M2[2] = {FLT_MAX, FLT_MAX};
-    int B1[2] = {0, 0};
+    // per tile: the class minima of the two partitions (fold_block), of the
+    // half blocks only the best two and which the best is
+    float mA[2][8], M1[2], M2[2] = {FLT_MAX, FLT_MAX}, Mb[2] = {FLT_MAX, FLT_MAX};
+    int Jb[2] = {0, 0};
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+      for (int k = 0; k < 8; ++k) mA[u][k] = FLT_MAX;
     for (int blk = 0; blk < nblk; ++blk) {
       // lanes h = 1 read the same split row; their B operand is zero
       const u32x4 an = *(const u32x4*)(Ns + (blk * 32 + q) * 8);
@@ -793,10 +803,25 @@ __global__ __launch_bounds__(256) void k_assign_bf16(
           acc[u] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, af[s2]),
                                                            __builtin_bit_cast(bf16x8, kf[u][s2]), acc[u], 0, 0, 0);
 #pragma unroll
-      for (int u = 0; u < 2; ++u) reduce_block(acc[u], blk, M1[u], M2[u], B1[u]);
+      for (int u = 0; u < 2; ++u) {
+        float lo, hi;
+        fold_block(acc[u], mA[u], lo, hi);
+        M2[u] = min2(M2[u], __builtin_amdgcn_fmed3f(Mb[u], lo, hi));
+        const float m = min3m(Mb[u], lo, hi);
+        Jb[u] = m < Mb[u] ? 2 * blk + (hi < lo ? 1 : 0) : Jb[u];
+        Mb[u] = m;
+      }
+    }
+    int J[2];
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      float M2a;
+      top2_classes(mA[u], M1[u], M2a);
+      M2[u] = min2(M2[u], M2a);
+      J[u] = local_group(Jb[u] >> 1, (int)(__float_as_uint(M1[u]) & kClassMask) + 8 * (Jb[u] & 1));
     }
     // lanes h = 0 decide the keys of tile tt, lanes h = 1 those of tile tt + 1
-    decide_pair<FIRST>(M1[0], M2[0], B1[0], M1[1], M2[1], B1[1], h ? kn[1] : kn[0], h ? old[1] : old[0],
+    decide_pair<FIRST>(M1[0], M2[0], J[0], M1[1], M2[1], J[1], h ? kn[1] : kn[0], h ? old[1] : old[0],
                        h ? lk[1] : lk[0], tt + h < tcount, h ? valid[1] : valid[0], N, cf, L.lists, wv, wn, un);
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
@@ -901,13 +926,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
   if (kHoist) norm_terms<NB>(an, ones, nacc);
 
   int wn = 0, un = 0;  // this wave's moved / uncertain entries (wave-uniform)
-  auto score = [&](const u32x4 (&kf)[4], float& knv, int t, float& M1, float& M2, int& B1)
+  auto score = [&](const u32x4 (&kf)[4], float& knv, int t, float& M1, float& M2, int& J)
                    __attribute__((always_inline)) {
     if (FIRST) {
       knv = key_norm_bound(kf);
       L.lists.kx[(wv * tpw + t) * 32 + q] = __float_as_uint(knv);
     }
+    int B1;
     score_tile<NB, kHoist>(af, an, ones, nacc, kf, M1, M2, B1);
+    J = local_group(B1, (int)(__float_as_uint(M1) & kPackMask));
   };
   // Two register sets used in turn: tile t + 1 is loaded while tile t is
   // scored (deeper rings measured no faster: the loop is bound by the
@@ -916,19 +943,19 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
   // each prefetch ahead of the tile it overlaps.
   for (int t = 0; t < tcount; t += 2) {
     float M1a, M2a, M1b, M2b;
-    int B1a, B1b;
+    int Ja, Jb;
     load_keys<FIRST>(Kbh, knorm_bh, belong_bh, tile0 + min(t + 1, tcount - 1), n, q, h, kb[1], knb[1], oldb[1]);
     __builtin_amdgcn_sched_barrier(0);
-    score(kb[0], knb[0], t, M1a, M2a, B1a);
+    score(kb[0], knb[0], t, M1a, M2a, Ja);
     const float kna = knb[0];
     const int olda = oldb[0];
     load_keys<FIRST>(Kbh, knorm_bh, belong_bh, tile0 + min(t + 2, tcount - 1), n, q, h, kb[0], knb[0], oldb[0]);
     __builtin_amdgcn_sched_barrier(0);
-    score(kb[1], knb[1], min(t + 1, tcount - 1), M1b, M2b, B1b);  // past the last tile: a repeat, not staged
+    score(kb[1], knb[1], min(t + 1, tcount - 1), M1b, M2b, Jb);  // past the last tile: a repeat, not staged
     // lanes h = 0 decide the keys of tile t, lanes h = 1 those of tile t + 1
     const int lk = (wv * tpw + t + h) * 32 + q;
     const bool stage = t + h < tcount;
-    decide_pair<FIRST>(M1a, M2a, B1a, M1b, M2b, B1b, h ? knb[1] : kna, h ? oldb[1] : olda, lk, stage,
+    decide_pair<FIRST>(M1a, M2a, Ja, M1b, M2b, Jb, h ? knb[1] : kna, h ? oldb[1] : olda, lk, stage,
                        stage && key0 + lk < n, N, cf, L.lists, wv, wn, un);
   }
   if (lane == 0) {
