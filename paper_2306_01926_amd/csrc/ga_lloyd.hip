@@ -21,6 +21,9 @@
 //      canonical |r|^2 and its split, published for the slice;
 //   4. barrier B; every rank reads the slice's new representatives.
 //
+// A short slice has one rank (P = 1): nothing is published, and the finished
+// representatives go straight into LDS.
+//
 // The member sums of bf16 keys are exact in fp64 (while (e_max - e_min) +
 // log2 count <= 45, see ga_kernels.hip), so the order in which the ranks and
 // the LDS atomics add them cannot change a bit: groups, counts and centroids
@@ -185,6 +188,33 @@ __device__ __forceinline__ LloydLds lloyd_layout(unsigned char* base, int Npad, 
   return l;
 }
 
+// ------------------------------------------------------------ cross-lane
+// Lane exchanges by DPP (VALU, no LDS round trip): within 8 lanes as the xors
+// 1, 2 and (equal to 4 once the quads agree) the half-row mirror.
+template <int CTRL>
+__device__ __forceinline__ int dpp(int x) {
+  return __builtin_amdgcn_update_dpp(0, x, CTRL, 0xf, 0xf, true);
+}
+template <int CTRL>
+__device__ __forceinline__ double dpp(double x) {
+  const long long b = __double_as_longlong(x);
+  const uint32_t lo = (uint32_t)dpp<CTRL>((int)(uint32_t)b), hi = (uint32_t)dpp<CTRL>((int)(uint32_t)(b >> 32));
+  return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+constexpr int kXor1 = 0xB1, kXor2 = 0x4E, kHalfMirror = 0x141, kMirror = 0x140;
+
+// The largest of the 64 lanes' values, in every lane.
+__device__ __forceinline__ float wave_max(float x) {
+  x = max2(x, __int_as_float(dpp<kXor1>(__float_as_int(x))));
+  x = max2(x, __int_as_float(dpp<kXor2>(__float_as_int(x))));
+  x = max2(x, __int_as_float(dpp<kHalfMirror>(__float_as_int(x))));
+  x = max2(x, __int_as_float(dpp<kMirror>(__float_as_int(x))));
+  const auto p = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  x = max2(__uint_as_float(p[0]), __uint_as_float(p[1]));
+  const u32x2 q = halves(__float_as_uint(x));
+  return max2(__uint_as_float(q[0]), __uint_as_float(q[1]));
+}
+
 // ------------------------------------------------------------ barrier
 // Arrive at barrier number k (0-based) of the slice and wait for all P ranks.
 // Returns false if the wait gave up (spin limit) or another workgroup did.
@@ -244,7 +274,7 @@ __device__ __forceinline__ double lds_row_norm(const LloydLds& L, int g) {
 // k_{floor(j n / N)} (R = C exactly) or the given init (R = bf16(C)); padded
 // groups get zero rows and the largest bf16 as |r|^2 (they never win).  The
 // owners write C for their groups.
-__device__ void lloyd_stage_init(const LloydArgs& a, const LloydLds& L, int Npad, int64_t s, int r, double* red) {
+__device__ __forceinline__ void lloyd_stage_init(const LloydArgs& a, const LloydLds& L, int Npad, int64_t s, int r) {
   const int tid = threadIdx.x;
   const uint16_t* Kbh = a.K + s * (int64_t)a.n * 64;
   const float* ibh = a.init ? a.init + s * (int64_t)a.N * 64 : nullptr;
@@ -288,17 +318,10 @@ __device__ void lloyd_stage_init(const LloydArgs& a, const LloydLds& L, int Npad
       *(u32x4*)(L.Ns + g * 8) = u32x4{0x7f7fu, 0u, 0u, 0u};
     }
   }
-  // the largest |r|^2 (padded groups hold 0), one value per wave of groups
-  if (tid < ((Npad + 63) & ~63)) {  // whole waves; lanes past Npad repeat group Npad - 1
-    double m = L.nrm[min(tid, Npad - 1)];
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) m = fmax(m, __shfl_xor(m, off));
-    if ((tid & 63) == 0) red[tid >> 6] = m;
-  }
 }
 
 // Later rounds: the slice's representatives published by their owners.
-__device__ void lloyd_read_reps(const LloydArgs& a, const LloydLds& L, int64_t s, double* red) {
+__device__ __forceinline__ void lloyd_read_reps(const LloydArgs& a, const LloydLds& L, int64_t s) {
   constexpr int kU = 128 * 8 / kLT;  // 16-byte chunks of R per thread, N <= 128
   const int tid = opaque_tid();
   const uint32_t* Rw = (const uint32_t*)(a.R + s * (int64_t)a.N * 64);
@@ -326,13 +349,6 @@ __device__ void lloyd_read_reps(const LloydArgs& a, const LloydLds& L, int64_t s
   if (tid < a.N) {
     *(u32x4*)(L.Ns + tid * 8) = u32x4{n0, n1, 0u, 0u};
     L.nrm[tid] = nr;
-  }
-  // the largest |r|^2, one value per wave of groups (threads past N hold group N - 1's)
-  if (tid < ((a.N + 63) & ~63)) {
-    double m = nr;
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) m = fmax(m, __shfl_xor(m, off));
-    if ((tid & 63) == 0) red[tid >> 6] = m;
   }
 }
 
@@ -391,15 +407,30 @@ __device__ __forceinline__ void lloyd_decide(float M1a, float M2a, int B1a, floa
   if (un) L.ent[kLCap - 1 - (bu + (int)__popcll(mu & below))] = (uint32_t)lk | ((uint32_t)oldv << 12);
 }
 
+// A wave takes every kLW-th tile of the rank, ascending in even rounds and the
+// same tiles descending (rev) in odd ones, so a round starts on the tile that
+// the wave read last: its rows (k0) stay in registers from round to round and
+// the first tile of a round waits for no load (a wave with one tile never
+// reads it again).
+__device__ __forceinline__ int lloyd_tiles(int nk, int wv) {
+  const int ntl = (nk + 31) >> 5;
+  return wv < ntl ? (ntl - wv + kLW - 1) / kLW : 0;
+}
+// This lane's half of key `lk` of the rank, clamped into the slice.
+__device__ __forceinline__ void lloyd_load(const LloydArgs& a, int64_t s, int key, int h, u32x4 (&f)[4]) {
+  const uint16_t* krow = a.K + (s * (int64_t)a.n + min(key, a.n - 1)) * 64 + h * 32;
+#pragma unroll
+  for (int s2 = 0; s2 < 4; ++s2) f[s2] = *(const u32x4*)(krow + s2 * 8);
+}
+
 template <int NB>
 __device__ __forceinline__ void lloyd_assign(const LloydArgs& a, const LloydLds& L, int64_t s, int k0, int nk,
-                                             bool first, bool rev, const LloydCert& cf, int* s_nmov, int* s_nunc) {
+                                             bool first, bool rev, const LloydCert& cf, u32x4 (&kb0)[4], int* s_nmov,
+                                             int* s_nunc) {
   const int tid = opaque_tid();
   const int lane = tid & 63, h = lane >> 5, q = lane & 31;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int ntl = (nk + 31) >> 5;
-  const int tc = wv < ntl ? (ntl - wv + kLW - 1) / kLW : 0;
-  const uint16_t* Kbh = a.K + s * (int64_t)a.n * 64;
+  const int tc = lloyd_tiles(nk, wv);
   u32x4 af[NB][4], an[NB];
 #pragma unroll
   for (int b = 0; b < NB; ++b) {
@@ -411,16 +442,9 @@ __device__ __forceinline__ void lloyd_assign(const LloydArgs& a, const LloydLds&
   f32x16 nacc[NB];
   norm_terms<NB>(an, ones, nacc);
   if (tc == 0) return;
-  // tile of the wave's j-th step: waves take every kLW-th tile, in ascending
-  // order or (rev) descending, so that a round starts on the keys the previous
-  // round read last
-  auto tile = [&](int j) __attribute__((always_inline)) { return rev ? ntl - 1 - wv - kLW * j : wv + kLW * j; };
-  // key row of tile j (wave-local index) for this lane: clamped into the slice
+  auto tile = [&](int j) __attribute__((always_inline)) { return wv + kLW * (rev ? tc - 1 - j : j); };
   auto load = [&](int j, u32x4 (&f)[4]) __attribute__((always_inline)) {
-    const int key = min(k0 + tile(j) * 32 + q, a.n - 1);
-    const uint16_t* krow = Kbh + (int64_t)key * 64 + h * 32;
-#pragma unroll
-    for (int s2 = 0; s2 < 4; ++s2) f[s2] = *(const u32x4*)(krow + s2 * 8);
+    lloyd_load(a, s, k0 + tile(j) * 32 + q, h, f);
   };
   auto state = [&](int j, const u32x4 (&f)[4], float& knv, int& oldv) __attribute__((always_inline)) {
     const int lk = tile(j) * 32 + q;
@@ -434,24 +458,32 @@ __device__ __forceinline__ void lloyd_assign(const LloydArgs& a, const LloydLds&
       oldv = L.bst[lkc];
     }
   };
-  u32x4 kb[2][4];
-  load(0, kb[0]);
-  for (int j = 0; j < tc; j += 2) {
+  u32x4 kb1[4];
+  int j = 0;
+  for (; j + 1 < tc; j += 2) {
     float M1a, M2a, M1b, M2b, kna, knb;
     int B1a, B1b, olda, oldb;
-    load(min(j + 1, tc - 1), kb[1]);
+    load(j + 1, kb1);
     __builtin_amdgcn_sched_barrier(0);
-    state(j, kb[0], kna, olda);
-    score_tile<NB, true>(af, an, ones, nacc, kb[0], M1a, M2a, B1a);
-    load(min(j + 2, tc - 1), kb[0]);
+    state(j, kb0, kna, olda);
+    score_tile<NB, true>(af, an, ones, nacc, kb0, M1a, M2a, B1a);
+    load(min(j + 2, tc - 1), kb0);  // past the last tile: the last one, the next round's first
     __builtin_amdgcn_sched_barrier(0);
-    const int jb = min(j + 1, tc - 1);  // past the last tile: a repeat, not decided
-    state(jb, kb[1], knb, oldb);
-    score_tile<NB, true>(af, an, ones, nacc, kb[1], M1b, M2b, B1b);
+    state(j + 1, kb1, knb, oldb);
+    score_tile<NB, true>(af, an, ones, nacc, kb1, M1b, M2b, B1b);
     // lanes h = 0 decide key q of tile j, lanes h = 1 key q of tile j + 1
-    const bool valid = j + h < tc && tile(j + h) * 32 + q < nk;
+    const bool valid = tile(j + h) * 32 + q < nk;
     const int lk = valid ? tile(j + h) * 32 + q : 0;
     lloyd_decide(M1a, M2a, B1a, M1b, M2b, B1b, h ? knb : kna, h ? oldb : olda, lk, valid, first, a.N, cf, L, s_nmov,
+                 s_nunc);
+  }
+  if (j < tc) {  // the last of an odd number of tiles
+    float M1, M2, knv;
+    int B1, oldv;
+    state(j, kb0, knv, oldv);
+    score_tile<NB, true>(af, an, ones, nacc, kb0, M1, M2, B1);
+    const bool valid = h == 0 && tile(j) * 32 + q < nk;
+    lloyd_decide(M1, M2, B1, M1, M2, B1, knv, oldv, valid ? tile(j) * 32 + q : 0, valid, first, a.N, cf, L, s_nmov,
                  s_nunc);
   }
 }
@@ -461,7 +493,7 @@ __device__ __forceinline__ void lloyd_assign(const LloydArgs& a, const LloydLds&
 // first round it adds the rows of those that changed group (fp64, from the
 // LDS copy) into the sums.  The keys are dealt from the last wave down (the
 // moved-key sums, which may run beside this phase, are dealt from wave 0 up).
-__device__ void lloyd_exact(const LloydArgs& a, const LloydLds& L, int64_t s, int k0, int nunc, bool first,
+__device__ __forceinline__ void lloyd_exact(const LloydArgs& a, const LloydLds& L, int64_t s, int k0, int nunc, bool first,
                             int* s_xmov) {
   const int otid = opaque_tid(), lane = otid & 63;
   const int wave = kLW - 1 - __builtin_amdgcn_readfirstlane(otid >> 6);
@@ -608,7 +640,7 @@ __device__ __forceinline__ int lloyd_sort(const LloydLds& L, int Npad, const uin
 // The rows of X (the keys in the first round, the values for the
 // aggregation) of all the rank's keys added into the sums of their groups
 // (from bst), with the member counts if `counts`.
-__device__ void lloyd_sums_all(const uint16_t* X, const LloydArgs& a, const LloydLds& L, int64_t s, int k0, int nk,
+__device__ __forceinline__ void lloyd_sums_all(const uint16_t* X, const LloydArgs& a, const LloydLds& L, int64_t s, int k0, int nk,
                                int Npad, bool counts) {
   const int tid = opaque_tid();
   constexpr int PER = kLSort / kLT;
@@ -633,7 +665,7 @@ __device__ void lloyd_sums_all(const uint16_t* X, const LloydArgs& a, const Lloy
 // summed in registers first.
 constexpr int kLPU = 4;                    // rows per lane group in the direct path
 constexpr int kLDirect = kLW * 8 * kLPU;  // moved keys the direct path takes
-__device__ void lloyd_sums_moved(const LloydArgs& a, const LloydLds& L, int64_t s, int k0, int nmov, int Npad) {
+__device__ __forceinline__ void lloyd_sums_moved(const LloydArgs& a, const LloydLds& L, int64_t s, int k0, int nmov, int Npad) {
   const int tid = opaque_tid();
   if (nmov <= kLDirect) {
     const int lane = tid & 63, wave = tid >> 6, j = lane & 7, sub = lane >> 3;
@@ -699,7 +731,7 @@ __device__ void lloyd_sums_moved(const LloydArgs& a, const LloydLds& L, int64_t 
 // m mod (P-1) of block m / (P-1), skipping member r), one row per wave and
 // step, kLPubB rows per wave read from LDS before any is stored.
 constexpr int kLPubB = 2;
-__device__ void lloyd_publish(const LloydArgs& a, const LloydLds& L, int64_t s, int r) {
+__device__ __forceinline__ void lloyd_publish(const LloydArgs& a, const LloydLds& L, int64_t s, int r) {
   if (a.P == 1) return;
   const int tid = opaque_tid(), lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int Npad = (a.N + 31) & ~31;
@@ -794,17 +826,9 @@ __device__ __forceinline__ int lloyd_gather(const LloydArgs& a, const LloydLds& 
     for (int off = 8; off >= 1; off >>= 1) m += __shfl_xor(m, off);
     moved = __builtin_amdgcn_readfirstlane(m);
   }
-  if (!counts) return moved;
 #pragma unroll
   for (int k = 0; k < kCK; ++k)
     if (cg[k] >= 0) atomicAdd(&L.dcA[cg[k]], cdel[k]);
-  lds_barrier();
-  for (int lg = tid; lg < Go; lg += kLT) {
-    const int g = r + a.P * lg;
-    if (g >= a.N) continue;
-    L.cnt[lg] += L.dcA[g];
-    L.dcA[g] = 0;
-  }
   return moved;
 }
 
@@ -843,26 +867,46 @@ __device__ __forceinline__ void lloyd_prev_c(const LloydArgs& a, int64_t s, int 
   }
 }
 
-__device__ void lloyd_finish(const LloydArgs& a, const LloydLds& L, int64_t s, int r, int Go, bool last,
-                             float2 (&prev)[kLFinU]) {
+// The round's change of a group's member count is in dcA until this folds it
+// into cnt.
+//
+// Bound by latency: 512 threads, two dependent LDS passes and the fp64
+// divisions; the sums over a group's eight lanes go through DPP (through LDS
+// shuffles before: 1.6 -> 1.4 us).
+//
+// With one rank per slice (SOLO) nothing is exchanged: the representatives go
+// straight to their LDS places and R reaches memory in the last round only (a
+// round of a 200-key slice 9.3 -> 3.9 us, with the tile kept in registers by
+// lloyd_assign); the round's key counters are cleared between the two halves,
+// when every thread has read them.
+template <bool SOLO>
+__device__ __forceinline__ void lloyd_finish(const LloydArgs& a, const LloydLds& L, int64_t s, int r, int Go, bool last,
+                                             float2 (&prev)[kLFinU], int* s_nmov, int* s_nunc, int* s_xmov) {
   const int tid = opaque_tid();
   float* Cbh = a.C + s * (int64_t)a.N * 64;
   uint32_t* Rw = (uint32_t*)(a.R + s * (int64_t)a.N * 64);
   uint32_t* rows = L.X;  // [Go][kLRowS] bf16 pairs
+  uint32_t full = 0;     // bit u: the item's group has members
 #pragma unroll
   for (int u = 0; u < kLFinU; ++u) {
     const int idx = tid + kLT * u, lg = idx >> 5, c2 = idx & 31, g = r + a.P * lg;
     if (lg >= Go || g >= a.N) continue;
-    const int cnt = L.cnt[lg];
+    const int cnt = L.cnt[lg] + L.dcA[g];
     float c0 = prev[u].x, c1 = prev[u].y;
     if (cnt > 0) {
       c0 = (float)(L.SA[g * kLSA + lloyd_pi(2 * c2)] / (double)cnt);
       c1 = (float)(L.SA[g * kLSA + lloyd_pi(2 * c2 + 1)] / (double)cnt);
+      full |= 1u << u;
     }
     prev[u] = float2{c0, c1};
     rows[lg * kLRowS + c2] = f32_to_bf16(c0) | (f32_to_bf16(c1) << 16);
   }
   lds_barrier();
+  if (SOLO && tid == 0) {
+    *s_nmov = 0;
+    *s_nunc = 0;
+    *s_xmov = 0;
+  }
   // per group (eight lanes, eight features each): |r|^2, its split, the count
   for (int base = 0; base < Go * 8; base += kLT) {
     const int t = base + tid, lg = t >> 3, j = t & 7, g = r + a.P * lg;
@@ -881,12 +925,16 @@ __device__ void lloyd_finish(const LloydArgs& a, const LloydLds& L, int64_t s, i
         emin = min(emin, sq_exp(q));
       }
     }
-#pragma unroll
-    for (int off = 1; off < 8; off <<= 1) {  // the group's eight lanes are consecutive lanes of one wave
-      acc += __shfl_xor(acc, off);
-      emax = max(emax, __shfl_xor(emax, off));
-      emin = min(emin, __shfl_xor(emin, off));
-    }
+    // the group's eight lanes are consecutive lanes of one wave
+    acc += dpp<kXor1>(acc);
+    acc += dpp<kXor2>(acc);
+    acc += dpp<kHalfMirror>(acc);
+    emax = max(emax, dpp<kXor1>(emax));
+    emin = min(emin, dpp<kXor1>(emin));
+    emax = max(emax, dpp<kXor2>(emax));
+    emin = min(emin, dpp<kXor2>(emin));
+    emax = max(emax, dpp<kHalfMirror>(emax));
+    emin = min(emin, dpp<kHalfMirror>(emin));
     if (!ok || j != 0) continue;
     double nrm = acc;
     if (emin != 4096 && emax - emin > 31) {  // not provably exact: the chain itself
@@ -901,21 +949,31 @@ __device__ void lloyd_finish(const LloydArgs& a, const LloydLds& L, int64_t s, i
         }
       }
     }
-    uint16_t sp[8];
-    write_nsplit(nrm, sp);
-    uint32_t* Nw = (uint32_t*)(a.nsplit + (s * a.N + g) * 8);
-    st_dev(Nw, (uint32_t)sp[0] | ((uint32_t)sp[1] << 16));
-    st_dev(Nw + 1, (uint32_t)sp[2] | ((uint32_t)sp[3] << 16));
-    st_dev64(a.nrm64 + s * a.N + g, nrm);
-    if (last) a.count[s * a.N + g] = L.cnt[lg];
+    if (SOLO) {
+      L.nrm[g] = nrm;
+      write_nsplit(nrm, L.Ns + g * 8);
+    } else {
+      uint16_t sp[8];
+      write_nsplit(nrm, sp);
+      uint32_t* Nw = (uint32_t*)(a.nsplit + (s * a.N + g) * 8);
+      st_dev(Nw, (uint32_t)sp[0] | ((uint32_t)sp[1] << 16));
+      st_dev(Nw + 1, (uint32_t)sp[2] | ((uint32_t)sp[3] << 16));
+      st_dev64(a.nrm64 + s * a.N + g, nrm);
+    }
+    const int cnt = L.cnt[lg] + L.dcA[g];
+    L.cnt[lg] = cnt;
+    L.dcA[g] = 0;
+    if (last) a.count[s * a.N + g] = cnt;
   }
   // C (non-empty groups) and R
 #pragma unroll
   for (int u = 0; u < kLFinU; ++u) {
     const int idx = tid + kLT * u, lg = idx >> 5, c2 = idx & 31, g = r + a.P * lg;
     if (lg >= Go || g >= a.N) continue;
-    if (L.cnt[lg] > 0) *(float2*)(Cbh + g * 64 + 2 * c2) = prev[u];
-    st_dev(Rw + g * 32 + c2, f32_to_bf16(prev[u].x) | (f32_to_bf16(prev[u].y) << 16));
+    if ((full >> u) & 1u) *(float2*)(Cbh + g * 64 + 2 * c2) = prev[u];
+    const uint32_t w = f32_to_bf16(prev[u].x) | (f32_to_bf16(prev[u].y) << 16);
+    if (SOLO) *(uint32_t*)(L.Rs + swz(g, c2 >> 2) + 2 * (c2 & 3)) = neg2_pair(w);
+    if (!SOLO || last) st_dev(Rw + g * 32 + c2, w);
   }
   lds_barrier();
 }
@@ -924,7 +982,7 @@ __device__ void lloyd_finish(const LloydArgs& a, const LloydLds& L, int64_t s, i
 // Outputs of the aggregation for the rank's groups (and the attention's padded
 // groups up to a multiple of 32): vsum = (float) of the exact sum, the bf16
 // means transposed (Vt) and the score bias log2(count) / (|scale| log2 e).
-__device__ void lloyd_value_outputs(const LloydArgs& a, const LloydLds& L, int64_t s, int r, int Go) {
+__device__ __forceinline__ void lloyd_value_outputs(const LloydArgs& a, const LloydLds& L, int64_t s, int r, int Go) {
   const int tid = opaque_tid();
   const int NpA = (a.N + 31) & ~31;
   for (int idx = tid; idx < Go * 64; idx += kLT) {
@@ -946,12 +1004,13 @@ template <int NB>
 __global__ __launch_bounds__(kLT) void k_lloyd(LloydArgs a) {
   extern __shared__ __align__(16) unsigned char smem[];
   __shared__ int s_nmov, s_nunc, s_xmov, s_flag;
-  __shared__ double s_red[kLW];
   constexpr int Npad = NB * 32;
   const int tid = threadIdx.x;
   const int bx = blockIdx.x, idx = bx >> 3;
   const int64_t s = (int64_t)(idx / a.P) * 8 + (bx & 7);
   const int r = idx % a.P;
+  const bool solo = a.P == 1;
+  if (solo && bx == 0 && tid == 0) *a.status = kLloydMark;  // (k_lloyd_reset's part where ranks meet)
   if (s >= a.BH) return;
   const int Go = lloyd_go(Npad, a.P);
   const LloydLds L = lloyd_layout(smem, Npad, a.P);
@@ -959,12 +1018,15 @@ __global__ __launch_bounds__(kLT) void k_lloyd(LloydArgs a) {
   uint32_t* ctr = a.sync + s * 32;
   int bar = 0;
 
-  if (tid == 0) {  // the round's key counters (cleared again after each barrier A)
+  if (tid == 0) {  // the round's key counters (cleared again in every round)
     s_nmov = 0;
     s_nunc = 0;
     s_xmov = 0;
   }
-  lloyd_stage_init(a, L, Npad, s, r, s_red);
+  // the first round's first tile: the rows are requested before the staging
+  u32x4 kb0[4];
+  lloyd_load(a, s, k0 + (tid >> 6) * 32 + (tid & 31), (tid >> 5) & 1, kb0);
+  lloyd_stage_init(a, L, Npad, s, r);
   for (int i = tid; i < Npad * kLSA; i += kLT) L.SA[i] = 0.0;
   for (int i = tid; i < Npad; i += kLT) {
     L.dcA[i] = 0;
@@ -976,17 +1038,19 @@ __global__ __launch_bounds__(kLT) void k_lloyd(LloydArgs a) {
   for (int t = 0; t < a.T; ++t) {
     const bool first = t == 0;
     bool last = t == a.T - 1;
-    // certification constants from the largest |r|^2 of the slice (one value
-    // per wave of groups, left by lloyd_stage_init / lloyd_read_reps)
-    double nmax = s_red[0];
-    if (Npad > 64) nmax = fmax(nmax, s_red[1]);
-    const float nmaxf = (float)nmax * (1.0f + 0x1p-20f);
+    // certification constants from the largest |r|^2 of the slice (padded groups hold 0)
+    const int ol = opaque_tid() & 63;
+    float nm = (float)L.nrm[min(ol, Npad - 1)];
+    if (Npad > 64) nm = max2(nm, (float)L.nrm[min(64 + ol, Npad - 1)]);
+    const float nmaxf = wave_max(nm) * (1.0f + 0x1p-20f);
     const LloydCert cf = lloyd_cert(nmaxf, sqrtf(nmaxf) * (1.0f + 0x1p-20f), a.cm, a.cp);
 
     // 1. assignment of the rank's keys and the sums of those that changed group
-    lloyd_assign<NB>(a, L, s, k0, nk, first, (t & 1) != 0, cf, &s_nmov, &s_nunc);
+    lloyd_assign<NB>(a, L, s, k0, nk, first, (t & 1) != 0, cf, kb0, &s_nmov, &s_nunc);
     lds_barrier();
     const int nunc = s_nunc, nmov = s_nmov;
+    float2 prev[kLFinU];
+    if (solo) lloyd_prev_c(a, s, r, Go, prev);  // (else the loads overlap barrier A)
     // after the first round, with few moved keys (their sums take the direct
     // path, which uses no LDS scratch), the exact fallback and the moved-key
     // sums run side by side: both add exact values into the sums
@@ -999,10 +1063,17 @@ __global__ __launch_bounds__(kLT) void k_lloyd(LloydArgs a) {
       lloyd_sums_all(a.K, a, L, s, k0, nk, Npad, true);
     else if (nmov)
       lloyd_sums_moved(a, L, s, k0, nmov, Npad);
+    // a round in which no key of the slice changed group is a fixed point, so
+    // it is the last
+    if (solo) {
+      if (!first && nmov + s_xmov == 0) last = true;
+      lloyd_finish<true>(a, L, s, r, Go, last, prev, &s_nmov, &s_nunc, &s_xmov);
+      if (last) break;
+      continue;
+    }
     // 2. the deltas of the other ranks' groups, then barrier A
     lloyd_publish(a, L, s, r);
     if (tid == 0) st_dev(a.xm + s * 16 + r, first ? nk : nmov + s_xmov);
-    float2 prev[kLFinU];
     lloyd_prev_c(a, s, r, Go, prev);
     if (!slice_barrier(ctr, a.status, a.P, bar++, &s_flag)) return;
     if (tid == 0) {  // every use of this round's key counters is behind the barrier
@@ -1010,15 +1081,14 @@ __global__ __launch_bounds__(kLT) void k_lloyd(LloydArgs a) {
       s_nunc = 0;
       s_xmov = 0;
     }
-    // 3. update of the rank's groups; a round in which no key of the slice
-    // changed group is a fixed point, so it is the last
+    // 3. update of the rank's groups
     if (lloyd_gather(a, L, s, r, Go, true, !first && !last) == 0) last = true;
     lds_barrier();
-    lloyd_finish(a, L, s, r, Go, last, prev);
+    lloyd_finish<false>(a, L, s, r, Go, last, prev, &s_nmov, &s_nunc, &s_xmov);
     if (last) break;
     // 4. barrier B, then the slice's new representatives
     if (!slice_barrier(ctr, a.status, a.P, bar++, &s_flag)) return;
-    lloyd_read_reps(a, L, s, s_red);
+    lloyd_read_reps(a, L, s);
     lds_barrier();
   }
   // the groups of the rank's keys
@@ -1029,11 +1099,13 @@ __global__ __launch_bounds__(kLT) void k_lloyd(LloydArgs a) {
   for (int i = tid; i < Npad * kLSA; i += kLT) L.SA[i] = 0.0;
   lds_barrier();
   lloyd_sums_all(a.V, a, L, s, k0, nk, Npad, false);
-  if (!slice_barrier(ctr, a.status, a.P, bar++, &s_flag)) return;
-  lloyd_publish(a, L, s, r);
-  if (!slice_barrier(ctr, a.status, a.P, bar++, &s_flag)) return;
-  lloyd_gather(a, L, s, r, Go, false, false);
-  lds_barrier();
+  if (!solo) {
+    if (!slice_barrier(ctr, a.status, a.P, bar++, &s_flag)) return;
+    lloyd_publish(a, L, s, r);
+    if (!slice_barrier(ctr, a.status, a.P, bar++, &s_flag)) return;
+    lloyd_gather(a, L, s, r, Go, false, false);
+    lds_barrier();
+  }
   lloyd_value_outputs(a, L, s, r, Go);
 }
 
@@ -1048,6 +1120,7 @@ __global__ void k_lloyd_reset(uint32_t* sync, int words, uint32_t* status) {
 }  // namespace ga
 
 // ------------------------------------------------------------ host side
+#include <algorithm>
 #include <map>
 #include <mutex>
 #include <tuple>
@@ -1102,9 +1175,18 @@ LloydPlan plan_lloyd(const Dims& d) {
   p.nb = (d.N + 31) / 32;
   const int Npad = 32 * p.nb;
   const int64_t bh8 = (d.BH + 7) / 8;
-  // ranks per slice: about one per 256 keys, at most 16, and every workgroup
-  // of the launch resident at once
+  // Ranks per slice: as many as lloyd_pcap allows, but
+  //  - one for short slices, which then exchange nothing (no barriers, no global
+  //    round trips in a round, no reset launch): up to 1024 keys, or 1536 where
+  //    the alternative is two ranks.  Forwards of 8 slices and 5 rounds, one rank
+  //    against the most (us): 500 keys and 32 groups 52 : 69, 1000 and 64 77 : 80,
+  //    1500 and 64 93 : 87; against two: 1500 and 64 93 : 95, 2000 and 64 111 : 107;
+  //  - no more than 8 below 3584 keys, where the wider exchange costs more than
+  //    the shorter tiles give (3000 keys, 64 groups: 8 ranks 88, 12 ranks 93).
   int P = lloyd_pcap(d);
+  if (d.n < 3584) P = std::min(P, 8);
+  if (d.n <= (P == 2 ? 1536 : 1024)) P = 1;
+  // every workgroup of the launch resident at once
   for (; P >= 1; --P) {
     const size_t lds = lloyd_lds_bytes(Npad, P);
     const auto cap = lloyd_capacity(p.nb, lds);
@@ -1140,7 +1222,7 @@ hipError_t launch_lloyd(const Dims& d, const void* K, const void* V, const float
                         float scale, hipStream_t st) {
   const LloydPlan p = plan_lloyd(d);
   if (!p.ok) return hipErrorInvalidValue;
-  {
+  if (p.P > 1) {
     TimedLaunch timed("lloyd_reset", st);
     const int words = (int)(d.BH * 32);
     hipLaunchKernelGGL(k_lloyd_reset, dim3((unsigned)std::min(64, (words + 255) / 256)), dim3(256), 0, st, w.lsync,
