@@ -130,21 +130,20 @@ int run_cluster(const ga::Dims& d, const void* K, int32_t iters, const float* in
       GA_LAUNCH(t == 0 ? ga::launch_sums_full(d, K, belong, w, count, C, st)
                        : ga::launch_sums_delta(d, K, mc_cur, mc_next, w, count, C, st), "update launch");
     } else {
-      GA_LAUNCH(ga::launch_bucket(d, belong, w.perm, w.goff, count, st), "bucket launch");
-      GA_LAUNCH(ga::launch_update(d, (const float*)K, w.perm, w.goff, count, C, (float*)w.R, w.nrm64, st), "update launch");
+      GA_LAUNCH(ga::launch_update_f32(d, (const float*)K, belong, count, C, (float*)w.R, w.nrm64, st),
+                "update launch");
     }
   }
   return GA_OK;
 }
 
 // Value sums for the current assignment.
-int run_valuesum(const ga::Dims& d, const void* V, const int32_t* belong, int32_t* count, float* vsum,
-                 const ga::Workspace& w, hipStream_t st) {
+int run_valuesum(const ga::Dims& d, const void* V, const int32_t* belong, float* vsum, const ga::Workspace& w,
+                 hipStream_t st) {
   if (d.dtype == GA_BF16) {
     GA_LAUNCH(ga::launch_valuesum_bf16(d, V, belong, w, vsum, st), "value-sum launch");
   } else {
-    GA_LAUNCH(ga::launch_bucket(d, belong, w.perm, w.goff, count, st), "bucket launch");
-    GA_LAUNCH(ga::launch_valuesum(d, (const float*)V, w.perm, w.goff, count, vsum, st), "value-sum launch");
+    GA_LAUNCH(ga::launch_valuesum_f32(d, (const float*)V, belong, vsum, st), "value-sum launch");
   }
   return GA_OK;
 }
@@ -174,8 +173,7 @@ int run_forward(const ga::Dims& d, const void* Q, const void* K, const void* V, 
     GA_LAUNCH(ga::launch_valuesum_prep(d, V, a, cnt, scale, w, st), "value-sum launch");
     GA_LAUNCH(ga::launch_attend(d, Q, w.R, w.Vt, w.ginit, C, cnt, w.vsum, scale, O, st), "attention launch");
   } else {
-    // the last stable bucket pass sorted the keys by the final assignment: reuse it
-    GA_LAUNCH(ga::launch_valuesum(d, (const float*)V, w.perm, w.goff, cnt, w.vsum, st), "value-sum launch");
+    GA_LAUNCH(ga::launch_valuesum_f32(d, (const float*)V, a, w.vsum, st), "value-sum launch");
     GA_LAUNCH(ga::launch_attend(d, Q, nullptr, nullptr, nullptr, C, cnt, w.vsum, scale, O, st),
               "attention launch");
   }
@@ -346,7 +344,7 @@ int ga_aggregate(ga_shape_t s, const void* V, const int32_t* belong, int32_t N, 
   const ga::Dims d = dims_of(s, N);
   ga::Workspace w;
   GA_TRY(check_ws(d, workspace, workspace_bytes, &w));
-  return run_valuesum(d, V, belong, w.count, vsum, w, (hipStream_t)stream);
+  return run_valuesum(d, V, belong, vsum, w, (hipStream_t)stream);
 }
 
 int ga_attend(ga_shape_t s, const void* Q, const float* centroid, const int32_t* count, const float* vsum,

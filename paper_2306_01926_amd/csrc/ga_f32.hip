@@ -214,62 +214,101 @@ __global__ __launch_bounds__(256) void k_assign_f32(const float* __restrict__ K,
 
 // ------------------------------------------------------------------ ordered sums
 // k_segsum: grid (ceil(N/4), BH), 256 threads: one wave per group, lane =
-// feature.  The group's members are perm[goff .. goff + count) in ascending
-// key order and are summed in that order in fp64 (fp32 sums need not be exact,
-// so the order is part of the definition).  Bound by the latency of the row
-// loads: a batch of kSegU rows is in flight while the one before it is added,
-// and the wave loads 64 indices at a time (4 rows in flight and dependent index
-// loads before: 26 -> 13 us at 2048 groups of 31 members, 120 us at 8 groups of
-// 2500, where the ordered chain leaves the chip idle).  UPDATE: centroid = (float)(sum /
-// count) (an empty group keeps its centroid) and its |r|^2; otherwise the fp32
-// rounding of the value sum.
+// feature.  The wave scans the slice's groups 64 keys at a time, appends the
+// keys of its group to a list in LDS (a ballot gives their places, so the list
+// ascends) and, whenever 64 are there and at the end, adds their rows in that
+// order in fp64 (fp32 sums need not be exact, so the order is part of the
+// definition).  UPDATE: count, centroid = (float)(sum / count) (an empty group
+// keeps its centroid), representative and |r|^2; otherwise the fp32 rounding of
+// the value sum.  Entries of belong outside [0, N) are ignored.
+//
+// Bound by latency: kScanU loads of 64 groups are in flight in the scan, and a
+// batch of kSegU rows while the one before it is added (all 64 rows
+// of a full list at once: no faster, and 98 against 78 us at 128 slices of 8000
+// keys, 128 groups, where fewer waves are resident).  Sorting the keys by
+// group in a launch of its own (one workgroup per slice) and reading the sorted
+// list took 7 + 12 us a round at 32 slices of 2000 keys and 64 groups, 35 us for
+// the sort alone at 20000 keys.
 constexpr int kSegU = 16;
+constexpr int kScanU = 8;
 template <bool UPDATE>
-__global__ __launch_bounds__(256) void k_segsum(const float* __restrict__ X, const int32_t* __restrict__ perm,
-                                                const int32_t* __restrict__ goff, const int32_t* __restrict__ count,
-                                                int n, int N, float* __restrict__ out, float* __restrict__ R,
-                                                double* __restrict__ nrm64) {
+__global__ __launch_bounds__(256) void k_segsum(const float* __restrict__ X, const int32_t* __restrict__ belong, int n,
+                                                int N, int32_t* __restrict__ count, float* __restrict__ out,
+                                                float* __restrict__ R, double* __restrict__ nrm64) {
+  __shared__ int32_t list[4][128];
   const int lane = threadIdx.x & 63;
-  const int g = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6));
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int g = blockIdx.x * 4 + wave;
   const int64_t bh = blockIdx.y;
   if (g >= N) return;
   const int64_t row = bh * N + g;
-  const int st = goff[row], cnt = count[row];
-  const int32_t* P = perm + bh * n + st;
+  const int32_t* bel = belong + bh * n;
   const float* Xb = X + bh * (int64_t)n * 64 + lane;
+  int32_t* L = list[wave];
   double acc = 0.0;
-  if (cnt > 0) {
-    int idx = P[min(lane, cnt - 1)], idx_n = 0;  // members 64 w + lane of this and the next window
+  int cnt = 0, held = 0;  // members seen, members in the list
+  // adds the rows of the list's first m (1 .. 64) members in order
+  auto sum = [&](int m) {
+    const int idx = L[min(lane, m - 1)];
     float va[kSegU], vb[kSegU];
-    auto load = [&](int x, float (&v)[kSegU]) {  // x: first member of a batch inside the window of idx
+    auto load = [&](int x, float (&v)[kSegU]) {  // past the end: the last member again, not added
 #pragma unroll
-      for (int u = 0; u < kSegU; ++u)
-        v[u] = Xb[(int64_t)__builtin_amdgcn_readlane(idx, (x & 63) + u) * 64];
+      for (int u = 0; u < kSegU; ++u) v[u] = Xb[(int64_t)__builtin_amdgcn_readlane(idx, x + u) * 64];
     };
     auto add = [&](int x, const float (&v)[kSegU]) {
-      if (x + kSegU <= cnt) {
+      if (x + kSegU <= m) {
 #pragma unroll
         for (int u = 0; u < kSegU; ++u) acc += (double)v[u];
       } else {
 #pragma unroll
         for (int u = 0; u < kSegU; ++u)
-          if (x + u < cnt) acc += (double)v[u];
+          if (x + u < m) acc += (double)v[u];
       }
     };
     load(0, va);
-    for (int x = 0; x < cnt; x += 2 * kSegU) {
-      if ((x & 63) == 0) idx_n = P[min(x + 64 + lane, cnt - 1)];
-      load(x + kSegU, vb);  // past the end: the last member again, not added
-      add(x, va);
-      if (((x + 2 * kSegU) & 63) == 0) idx = idx_n;
-      load(x + 2 * kSegU, va);
-      add(x + kSegU, vb);
+    if (m > kSegU) load(kSegU, vb);
+    add(0, va);
+    if (m <= kSegU) return;
+    if (m > 2 * kSegU) load(2 * kSegU, va);
+    add(kSegU, vb);
+    if (m <= 2 * kSegU) return;
+    if (m > 3 * kSegU) load(3 * kSegU, vb);
+    add(2 * kSegU, va);
+    if (m > 3 * kSegU) add(3 * kSegU, vb);
+  };
+  for (int base = 0; base < n; base += 64 * kScanU) {
+    int b[kScanU];
+#pragma unroll
+    for (int u = 0; u < kScanU; ++u) b[u] = bel[min(base + 64 * u + lane, n - 1)];
+#pragma unroll
+    for (int u = 0; u < kScanU; ++u) {
+      const int key = base + 64 * u + lane;
+      const bool mine = key < n && b[u] == g;
+      const uint64_t mask = __ballot(mine);
+      if (mask == 0) continue;  // uniform
+      if (mine)
+        L[held + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
+                                                __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u))] = key;
+      held += (int)__popcll(mask);
+      if (held >= 64) {
+        cnt += 64;
+        held -= 64;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        sum(64);
+        const int rest = L[64 + lane];  // at most 63 of these are members
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        L[lane] = rest;
+      }
     }
   }
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  cnt += held;
+  if (held > 0) sum(held);
   if (!UPDATE) {
     out[row * 64 + lane] = (float)acc;
     return;
   }
+  if (lane == 0) count[row] = cnt;
   float c;
   if (cnt > 0) {
     c = (float)(acc / (double)cnt);
@@ -410,19 +449,18 @@ hipError_t launch_assign_f32(const Dims& d, const float* K, const float* R, cons
   return hipGetLastError();
 }
 
-hipError_t launch_update(const Dims& d, const float* K, const int32_t* perm, const int32_t* goff,
-                         const int32_t* count, float* C, float* R, double* nrm64, hipStream_t st) {
+hipError_t launch_update_f32(const Dims& d, const float* K, const int32_t* belong, int32_t* count, float* C, float* R,
+                             double* nrm64, hipStream_t st) {
   TimedLaunch timed("update", st);
-  hipLaunchKernelGGL((k_segsum<true>), dim3((unsigned)((d.N + 3) / 4), (unsigned)d.BH), dim3(256), 0, st, K, perm,
-                     goff, count, d.n, d.N, C, R, nrm64);
+  hipLaunchKernelGGL((k_segsum<true>), dim3((unsigned)((d.N + 3) / 4), (unsigned)d.BH), dim3(256), 0, st, K, belong,
+                     d.n, d.N, count, C, R, nrm64);
   return hipGetLastError();
 }
 
-hipError_t launch_valuesum(const Dims& d, const float* V, const int32_t* perm, const int32_t* goff,
-                           const int32_t* count, float* vsum, hipStream_t st) {
+hipError_t launch_valuesum_f32(const Dims& d, const float* V, const int32_t* belong, float* vsum, hipStream_t st) {
   TimedLaunch timed("valuesum", st);
-  hipLaunchKernelGGL((k_segsum<false>), dim3((unsigned)((d.N + 3) / 4), (unsigned)d.BH), dim3(256), 0, st, V, perm,
-                     goff, count, d.n, d.N, vsum, (float*)nullptr, (double*)nullptr);
+  hipLaunchKernelGGL((k_segsum<false>), dim3((unsigned)((d.N + 3) / 4), (unsigned)d.BH), dim3(256), 0, st, V, belong,
+                     d.n, d.N, (int32_t*)nullptr, vsum, (float*)nullptr, (double*)nullptr);
   return hipGetLastError();
 }
 

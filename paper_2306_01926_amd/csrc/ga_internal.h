@@ -19,8 +19,6 @@ struct Workspace {
   uint16_t* nsplit;  // [BH][N][8] bf16 hi, mid, lo with hi + mid + lo ~ nrm64 (rest zero)
   float* knorm;      // [BH][n] upper bound of |k_i| (bf16 path)
   int32_t* belong;   // [BH][n]
-  int32_t* perm;     // [BH][n] keys sorted by group, ascending key index inside a group
-  int32_t* goff;     // [BH][N] first position of each group in perm
   int32_t* count;    // [BH][N]
   float* vsum;       // [BH][N][64]
   uint16_t* Rq;      // [BH][N][64] bf16 representatives for the scores
@@ -119,8 +117,6 @@ hipError_t launch_valuesum_bf16(const Dims& d, const void* V, const int32_t* bel
 // in place of launch_valuesum_bf16 + launch_attend_prep
 hipError_t launch_valuesum_prep(const Dims& d, const void* V, const int32_t* belong, int32_t* count, float scale,
                                 const Workspace& w, hipStream_t st);
-hipError_t launch_bucket(const Dims& d, const int32_t* belong, int32_t* perm, int32_t* goff,
-                         int32_t* count, hipStream_t st);
 hipError_t launch_attend_prep(const Dims& d, const float* centroid, const int32_t* count,
                               const float* vsum, float scale, uint16_t* Rq, uint16_t* Vt,
                               float* ginit, bool make_rq, hipStream_t st);
@@ -132,10 +128,9 @@ hipError_t launch_attend(const Dims& d, const void* Q, const void* R, const uint
 // ascending key order (centroids and representatives; values), the attention.
 hipError_t launch_assign_f32(const Dims& d, const float* K, const float* R, const double* nrm64, int32_t* belong,
                              bool first, hipStream_t st);
-hipError_t launch_update(const Dims& d, const float* K, const int32_t* perm, const int32_t* goff,
-                         const int32_t* count, float* C, float* R, double* nrm64, hipStream_t st);
-hipError_t launch_valuesum(const Dims& d, const float* V, const int32_t* perm, const int32_t* goff,
-                           const int32_t* count, float* vsum, hipStream_t st);
+hipError_t launch_update_f32(const Dims& d, const float* K, const int32_t* belong, int32_t* count, float* C, float* R,
+                             double* nrm64, hipStream_t st);
+hipError_t launch_valuesum_f32(const Dims& d, const float* V, const int32_t* belong, float* vsum, hipStream_t st);
 hipError_t launch_attend_f32(const Dims& d, const float* Q, const float* centroid, const int32_t* count,
                              const float* vsum, float scale, float* O, hipStream_t st);
 

@@ -21,8 +21,8 @@
 //                   (transposed) and log2(count) score bias
 //   k_attend_bf16   MFMA scores, block-wise group softmax, MFMA combine
 // Also: k_init, k_assign_bf16 (N <= 1024), k_gsum<0> (first-round sums
-// without partitions), k_gsum<2> (value sums), k_attend_prep; the fp32 path's k_bucket
-// (stable counting sort of keys by group); its other kernels are in ga_f32.hip.
+// without partitions), k_gsum<2> (value sums), k_attend_prep.  The fp32 path is in
+// ga_f32.hip.
 #include <hip/hip_runtime.h>
 
 #include <float.h>
@@ -972,85 +972,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
   }
 }
 
-// ------------------------------------------------------------------ bucket
-__device__ __forceinline__ int wave_incl_scan(int x) {
-  const int lane = threadIdx.x & 63;
-#pragma unroll
-  for (int d = 1; d < 64; d <<= 1) {
-    const int t = __shfl_up(x, d);
-    if (lane >= d) x += t;
-  }
-  return x;
-}
-
-// Stable counting sort of one slice's keys by group; grid BH, 1024 threads.
-// LDS: per-wave 64-bit lane masks [16][N], counts [N], running offsets [N].
-// Within a 1024-key chunk, a key's rank among same-group keys is the number
-// of lower lanes in its wave with the same group (popcount of the OR-ed lane
-// mask) plus the members of that group in the lower waves of the chunk.
-__global__ __launch_bounds__(1024) void k_bucket(const int32_t* __restrict__ belong, int n, int N,
-                                                 int32_t* __restrict__ perm, int32_t* __restrict__ goff,
-                                                 int32_t* __restrict__ count) {
-  extern __shared__ __align__(16) unsigned char smem[];
-  __shared__ int wsum[16];
-  unsigned long long* wmask = (unsigned long long*)smem;
-  int32_t* cnt = (int32_t*)(wmask + 16 * N);
-  int32_t* run = cnt + N;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int64_t bh = blockIdx.x;
-  const int32_t* a = belong + bh * n;
-
-  for (int g = tid; g < N; g += 1024) cnt[g] = 0;
-  for (int x = tid; x < 16 * N; x += 1024) wmask[x] = 0ull;
-  __syncthreads();
-  for (int i = tid; i < n; i += 1024) {
-    const int g = a[i];
-    if ((unsigned)g < (unsigned)N) atomicAdd(&cnt[g], 1);
-  }
-  __syncthreads();
-  const int v = tid < N ? cnt[tid] : 0;
-  const int incl = wave_incl_scan(v);
-  if (lane == 63) wsum[wave] = incl;
-  __syncthreads();
-  if (wave == 0) {
-    const int t = lane < 16 ? wsum[lane] : 0;
-    const int ti = wave_incl_scan(t);
-    if (lane < 16) wsum[lane] = ti - t;
-  }
-  __syncthreads();
-  if (tid < N) {
-    const int ex = incl - v + wsum[wave];
-    run[tid] = ex;
-    goff[bh * N + tid] = ex;
-    count[bh * N + tid] = v;
-  }
-  __syncthreads();
-
-  const unsigned long long below = (1ull << lane) - 1ull;
-  for (int base = 0; base < n; base += 1024) {
-    const int i = base + tid;
-    const int g = i < n ? a[i] : -1;
-    const bool ok = (unsigned)g < (unsigned)N;
-    if (ok) atomicOr(&wmask[wave * N + g], 1ull << lane);
-    __syncthreads();
-    unsigned long long m = 0ull;
-    int rank = 0;
-    if (ok) {
-      m = wmask[wave * N + g];
-      rank = __popcll(m & below);
-      int pre = 0;
-      for (int w2 = 0; w2 < wave; ++w2) pre += __popcll(wmask[w2 * N + g]);
-      perm[bh * n + run[g] + pre + rank] = i;
-    }
-    __syncthreads();
-    if (ok && rank == 0) {
-      atomicAdd(&run[g], __popcll(m));
-      wmask[wave * N + g] = 0ull;
-    }
-    __syncthreads();
-  }
-}
-
 // ------------------------------------------------------------------ group sums (bf16)
 // run_sums: the rows of a group-sorted entry list (ent: key | leave << 31;
 // eg: the entry's group within the workgroup's block) added into the LDS sums
@@ -1810,7 +1731,6 @@ size_t assign_lds(int N, int tpw = 12, bool fused = false) {  // see assign_lds_
   const int Npad = (N + 31) & ~31, cap4 = 4 * tpw * 32;
   return (size_t)assign_region_a(Npad, cap4, fused) + (size_t)3 * cap4 * 4;
 }
-size_t bucket_lds(int N) { return (size_t)16 * N * 8 + (size_t)2 * N * 4; }
 size_t attend_lds(int N) {
   const int Npad = (N + 31) & ~31;
   return (size_t)Npad * kRs * 2 + (size_t)64 * vt_stride(N) * 2 + (size_t)Npad * 4 + (size_t)4 * 32 * kOs * 2;
@@ -1826,8 +1746,6 @@ void set_lds_limits() {
                               (int)kAssignLdsMax);
     (void)hipFuncSetAttribute((const void*)k_assign_bf16<false>, hipFuncAttributeMaxDynamicSharedMemorySize,
                               (int)kAssignLdsMax);
-    (void)hipFuncSetAttribute((const void*)k_bucket, hipFuncAttributeMaxDynamicSharedMemorySize,
-                              (int)bucket_lds(kMaxGroups));
     for (const void* f : {(const void*)k_attend_bf16<1>, (const void*)k_attend_bf16<2>, (const void*)k_attend_bf16<3>,
                           (const void*)k_attend_bf16<4>, (const void*)k_attend_bf16<5>, (const void*)k_attend_bf16<6>,
                           (const void*)k_attend_bf16<7>, (const void*)k_attend_bf16<8>})
@@ -1891,8 +1809,6 @@ size_t workspace_layout(const Dims& d, Workspace* ws, void* base) {
   w.nsplit = (uint16_t*)take(BH * N * 16);
   w.knorm = (float*)take(BH * n * 4);
   w.belong = (int32_t*)take(BH * n * 4);
-  w.perm = (int32_t*)take(BH * n * 4);
-  w.goff = (int32_t*)take(BH * N * 4);
   w.count = (int32_t*)take(BH * N * 4);
   w.vsum = (float*)take(BH * N * 64 * 4);
   w.Rq = (uint16_t*)take(BH * N * 64 * 2);
@@ -2032,15 +1948,6 @@ hipError_t launch_part_finish(const Dims& d, int parts, const FusedUpdate& fu, d
   const dim3 grid(cdiv(d.N, 32), (unsigned)d.BH), block(256);
   hipLaunchKernelGGL(fns[parts - 1], grid, block, 0, st, fu.Sp, fu.cntp, fu.pbits, d.N, S64, count, C,
                      (uint16_t*)R, nrm64, nsplit);
-  return hipGetLastError();
-}
-
-hipError_t launch_bucket(const Dims& d, const int32_t* belong, int32_t* perm, int32_t* goff,
-                         int32_t* count, hipStream_t st) {
-  TimedLaunch timed("bucket", st);
-  set_lds_limits();
-  hipLaunchKernelGGL(k_bucket, dim3((unsigned)d.BH), dim3(1024), bucket_lds(d.N), st, belong, d.n, d.N,
-                     perm, goff, count);
   return hipGetLastError();
 }
 
