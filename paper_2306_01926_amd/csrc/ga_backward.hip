@@ -28,8 +28,8 @@
 //   k_bwd_prep    per slice: R = bf16(centroid) rows and transposed, bf16
 //                 value means, log2(count) (-inf for an empty group)
 //   k_bwd_query   per 32-query tile (lane = query): the query side as above
-//                 in three passes over the 32-group blocks (shift; sum and
-//                 D; dp and dQ), recomputing the block's MFMAs; stores each
+//                 in two passes over the 32-group blocks (shift, sum and D;
+//                 dp and dQ), recomputing the block's MFMAs; stores each
 //                 query's softmax shift plus log2 of its sum (so that a
 //                 weight is one exp2) and D
 //   k_bwd_group   per (32-group block, query chunk): the same scores and dw
@@ -153,17 +153,17 @@ __global__ __launch_bounds__(256) void k_bwd_prep(const float* __restrict__ cent
 
 // Stage a slice's R rows (A or B operand rows), value-mean rows and the count
 // logarithms in LDS.
-template <int NB>
+template <int NB, int T>
 __device__ __forceinline__ void stage_groups(const uint16_t* __restrict__ R, const uint16_t* __restrict__ MU,
                                              const float* __restrict__ LC, int64_t bh, uint16_t* Rs, uint16_t* Ms,
                                              float* lc) {
   constexpr int Npad = NB * 32;
-  for (int x = threadIdx.x; x < Npad * 8; x += 256) {
+  for (int x = threadIdx.x; x < Npad * 8; x += T) {
     const int row = x >> 3, ch = x & 7;
     *(u32x4*)(Rs + row * kBs + 8 * ch) = *(const u32x4*)(R + (bh * Npad + row) * 64 + 8 * ch);
     *(u32x4*)(Ms + row * kBs + 8 * ch) = *(const u32x4*)(MU + (bh * Npad + row) * 64 + 8 * ch);
   }
-  for (int g = threadIdx.x; g < Npad; g += 256) lc[g] = LC[bh * Npad + g];
+  for (int g = threadIdx.x; g < Npad; g += T) lc[g] = LC[bh * Npad + g];
 }
 
 // lane (row, h) loads features 32 h .. 32 h + 31 of row `row` (clamped): the
@@ -174,29 +174,36 @@ __device__ __forceinline__ void load_row_frags(const uint16_t* __restrict__ X, i
   for (int s = 0; s < 4; ++s) f[s] = *(const u32x4*)(X + row * 64 + 32 * h + 8 * s);
 }
 
-// grid (ceil(tiles / (4 tpw)), BH), 256 threads: wave tiles of 32 queries.
+// grid (ceil(tiles / (nw tpw)), BH), kBqW waves, of which the first nw have
+// wave tiles of 32 queries (all of them stage).
+// The staged group rows (111 KB at 224 groups) leave room for one workgroup per
+// compute unit, so it has eight waves, two per SIMD, and the launch is one round
+// of workgroups: with four waves and two rounds 46 us at 24 slices of 3333
+// queries and 200 groups.
+constexpr int kBqW = 8;
 template <int NB>
-__global__ __launch_bounds__(256) void k_bwd_query(const uint16_t* __restrict__ Q, const uint16_t* __restrict__ G,
+__global__ __launch_bounds__(64 * kBqW) void k_bwd_query(const uint16_t* __restrict__ Q, const uint16_t* __restrict__ G,
                                                    const uint16_t* __restrict__ R, const uint16_t* __restrict__ RT,
                                                    const uint16_t* __restrict__ MU, const float* __restrict__ LC,
-                                                   int n, int rts, float scale, float sl2e, int tpw,
+                                                   int n, int rts, float scale, float sl2e, int nw, int tpw,
                                                    uint16_t* __restrict__ dQ, float2* __restrict__ stats) {
   constexpr int Npad = NB * 32;
   __shared__ __attribute__((aligned(16))) uint16_t Rs[Npad * kBs];
   __shared__ __attribute__((aligned(16))) uint16_t Ms[Npad * kBs];
   __shared__ __attribute__((aligned(16))) uint16_t RTs[64 * (Npad + 4)];
   __shared__ float lc[Npad];
-  __shared__ __attribute__((aligned(16))) uint16_t Ot[4][32 * kBs];
+  __shared__ __attribute__((aligned(16))) uint16_t Ot[kBqW][32 * kBs];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, h = lane >> 5, q = lane & 31;
   const int64_t bh = blockIdx.y;
-  stage_groups<NB>(R, MU, LC, bh, Rs, Ms, lc);
-  for (int x = tid; x < 64 * (Npad / 4); x += 256) {
+  stage_groups<NB, 64 * kBqW>(R, MU, LC, bh, Rs, Ms, lc);
+  for (int x = tid; x < 64 * (Npad / 4); x += 64 * kBqW) {
     const int row = x / (Npad / 4), ch = x % (Npad / 4);
     *(u32x2*)(RTs + row * (Npad + 4) + 4 * ch) = *(const u32x2*)(RT + (bh * 64 + row) * rts + 4 * ch);
   }
   __syncthreads();
   const int64_t ntiles = ((int64_t)n + 31) / 32;
-  const int64_t t0 = ((int64_t)blockIdx.x * 4 + wave) * tpw;
+  if (wave >= nw) return;  // (no barrier below)
+  const int64_t t0 = ((int64_t)blockIdx.x * nw + wave) * tpw;
   const uint16_t* Qb = Q + bh * (int64_t)n * 64;
   const uint16_t* Gb = G + bh * (int64_t)n * 64;
   uint16_t* Ow = Ot[wave];
@@ -247,35 +254,44 @@ __global__ __launch_bounds__(256) void k_bwd_query(const uint16_t* __restrict__ 
     };
     float Ms_, inv, Dq, Lq;  // Lq: the shift plus log2 of the sum (+inf if every group is empty)
     {
-      // more groups than fit in registers: three passes over the blocks
-      // (shift; sum and D; dp and dQ), the MFMAs recomputed in each
-      float M = -INFINITY;
+      // more groups than fit in registers: two passes over the blocks (shift,
+      // sum and D, the sums rescaled when a lane's shift grows; dp and dQ), the
+      // MFMAs recomputed in the second
+      float M = -INFINITY, S = 0.f, SD = 0.f;  // over this lane's half of the groups
+#pragma unroll 1
       for (int b = 0; b < NB; ++b) {
         f32x16 a, d;
         block_mfma(b, a, d);
-#pragma unroll
-        for (int v = 0; v < 16; ++v) M = fmaxf(M, fmaf(a[v], sl2e, lc[32 * b + 8 * (v >> 2) + 4 * h + (v & 3)]));
-      }
-      M = fmaxf(M, __shfl_xor(M, 32));
-      const bool any = M != -INFINITY;
-      Ms_ = any ? M : 0.f;
-      float S = 0.f, SD = 0.f;
-      for (int b = 0; b < NB; ++b) {
-        f32x16 a, d;
-        block_mfma(b, a, d);
+        float x[16], Mn = M;
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
-          const float e =
-              __builtin_amdgcn_exp2f(fmaf(a[v], sl2e, lc[32 * b + 8 * (v >> 2) + 4 * h + (v & 3)]) - Ms_);
+          x[v] = fmaf(a[v], sl2e, lc[32 * b + 8 * (v >> 2) + 4 * h + (v & 3)]);
+          Mn = fmaxf(Mn, x[v]);
+        }
+        const float ref = Mn == -INFINITY ? 0.f : Mn;  // no group so far: every term below is 0
+        const float alpha = __builtin_amdgcn_exp2f(M - ref);
+        S *= alpha;
+        SD *= alpha;
+        M = Mn;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+          const float e = __builtin_amdgcn_exp2f(x[v] - ref);
           S += e;
           SD = fmaf(e, d[v], SD);
         }
       }
+      const float Mo = fmaxf(M, __shfl_xor(M, 32));
+      const bool any = Mo != -INFINITY;
+      Ms_ = any ? Mo : 0.f;
+      const float beta = __builtin_amdgcn_exp2f(M - Ms_);
+      S *= beta;
+      SD *= beta;
       S += __shfl_xor(S, 32);
       SD += __shfl_xor(SD, 32);
       inv = any ? 1.0f / S : 0.f;
       Lq = any ? Ms_ + log2f(S) : INFINITY;
       Dq = SD * inv;
+#pragma unroll 1
       for (int b = 0; b < NB; ++b) {
         f32x16 a, d;
         block_mfma(b, a, d);
@@ -923,15 +939,17 @@ hipError_t launch_backward(const Dims& d, const void* Q, const void* dO, const i
                        Npad, rts, w.R, w.RT, w.MU, w.LC);
   }
   const int64_t ntiles = ((int64_t)d.n + 31) / 32;
-  // about one round of kBwdTargetWgs workgroups: the same number per slice
-  const int64_t per_slice = (kBwdTargetWgs + d.BH - 1) / d.BH;
-  const int tpw = (int)((ntiles + 4 * per_slice - 1) / (4 * per_slice));
-  const unsigned gq = (unsigned)((ntiles + 4 * tpw - 1) / (4 * tpw));
+  // at most one round of 256 workgroups (one per compute unit), the same number
+  // per slice; where four waves of one tile each are enough for that, four
+  const int64_t per_slice = 256 / d.BH > 1 ? 256 / d.BH : 1;
+  const int nw = ntiles <= 4 * per_slice ? 4 : kBqW;
+  const int tpw = (int)((ntiles + nw * per_slice - 1) / (nw * per_slice));
+  const unsigned gq = (unsigned)((ntiles + nw * tpw - 1) / (nw * tpw));
   {
     TimedLaunch tl("bwd_query", st);
 #define GA_BWD_Q(NBV)                                                                                              \
-  hipLaunchKernelGGL(k_bwd_query<NBV>, dim3(gq, (unsigned)d.BH), dim3(256), 0, st, (const uint16_t*)Q,            \
-                     (const uint16_t*)dO, w.R, w.RT, w.MU, w.LC, d.n, rts, scale, sl2e, tpw, (uint16_t*)dQ,       \
+  hipLaunchKernelGGL(k_bwd_query<NBV>, dim3(gq, (unsigned)d.BH), dim3(64 * kBqW), 0, st, (const uint16_t*)Q,            \
+                     (const uint16_t*)dO, w.R, w.RT, w.MU, w.LC, d.n, rts, scale, sl2e, nw, tpw, (uint16_t*)dQ,       \
                      (float2*)w.stats)
     switch (NB) {
       case 5: GA_BWD_Q(5); break;

@@ -1,0 +1,46 @@
+"""GPU parity of the backward's query kernel for more than 128 groups: the
+softmax shift growing from block to block (sums rescaled on the way, one pass),
+blocks without a member, and the wave counts of its launch."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2306_01926_amd import ga, inputs
+
+pytestmark = pytest.mark.gpu
+TOL = 2e-2  # the documented bound of the gradient, per slice
+
+CASES = [
+    # B, H, n, N, scale, empty groups, growth of the centroids from block to block
+    (1, 1, 130, 129, 0.125, (0, 0), 1.0),    # one group in the last block, two keys in the last tile
+    (1, 2, 500, 160, 0.5, (0, 40), 1.6),     # the first block and part of the second empty, shifts grow
+    (1, 1, 500, 224, 0.5, (180, 224), 0.6),  # the last block empty, shifts fall
+    (1, 1, 33000, 130, 0.125, (3, 9), 1.0),  # eight waves of one tile
+    (30, 10, 600, 130, -0.2, (0, 32), 1.2),  # one workgroup per slice, three tiles per wave
+]
+
+
+@pytest.mark.parametrize("case", CASES, ids=lambda c: "-".join(map(str, c[:4])))
+def test_backward_wide(oracle_mod, case):
+    B, H, n, N, scale, (e0, e1), grow = case
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    print(f"\n[case] backward {case}", flush=True)
+    dev = torch.device("cuda:0")
+    rng = np.random.default_rng(n + N)
+    Q, _, V = inputs.make_qkv(B, H, n, 64, "bf16", 5, 8, 0.1, 0.1)
+    dO = inputs.to_storage(rng.standard_normal((B, H, n, 64), dtype=np.float32), "bf16")
+    live = np.array([g for g in range(N) if not e0 <= g < e1], np.int32)
+    belong = live[rng.integers(0, len(live), size=(B, H, n))]
+    count = np.stack([[np.bincount(belong[b, h], minlength=N) for h in range(H)] for b in range(B)]).astype(np.int32)
+    centroid = 0.2 * rng.standard_normal((B, H, N, 64)) * grow ** (np.arange(N) // 32)[:, None]
+    centroid = centroid.astype(np.float32)
+    vsum = oracle_mod.aggregate(inputs.as_float64(V), belong, N)[0].astype(np.float32)
+    t = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to(dev)  # noqa: E731
+    got = [ga.backward(Q.to(dev), dO.to(dev), t(belong), t(centroid), t(count), t(vsum), N, scale) for _ in range(2)]
+    torch.cuda.synchronize()
+    assert all(torch.equal(x, y) for x, y in zip(*got)), "repeated calls differ"
+    ref = oracle_mod.backward(inputs.as_float64(Q), inputs.as_float64(dO), belong, centroid, count, vsum, N, scale,
+                              "bf16")
+    for X, R, what in zip(got[0], ref, ("dQ", "dK", "dV")):
+        err = np.abs(X.float().cpu().numpy() - R).max(axis=(2, 3))
+        assert (err <= TOL * np.abs(R).max(axis=(2, 3))).all(), (what, (err / np.abs(R).max(axis=(2, 3))).max())
