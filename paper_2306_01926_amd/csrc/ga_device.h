@@ -64,6 +64,109 @@ __device__ __forceinline__ float readlane_f(float x, int l) {
   return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), l));
 }
 
+// (value of lane q, value of lane q + 32) in every lane l, q = l % 32.
+__device__ __forceinline__ u32x2 halves(uint32_t x) {
+  const auto r = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+  return u32x2{r[0], r[1]};
+}
+
+// Lane exchanges by DPP (VALU, no LDS round trip): within 8 lanes as the xors
+// 1, 2 and (equal to 4 once the quads agree) the half-row mirror.
+template <int CTRL>
+__device__ __forceinline__ int dpp(int x) {
+  return __builtin_amdgcn_update_dpp(0, x, CTRL, 0xf, 0xf, true);
+}
+template <int CTRL>
+__device__ __forceinline__ double dpp(double x) {
+  const long long b = __double_as_longlong(x);
+  const uint32_t lo = (uint32_t)dpp<CTRL>((int)(uint32_t)b), hi = (uint32_t)dpp<CTRL>((int)(uint32_t)(b >> 32));
+  return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+constexpr int kXor1 = 0xB1, kXor2 = 0x4E, kHalfMirror = 0x141, kMirror = 0x140;
+
+// The largest of the 64 lanes' values, in every lane.
+__device__ __forceinline__ float wave_max(float x) {
+  x = max2(x, __int_as_float(dpp<kXor1>(__float_as_int(x))));
+  x = max2(x, __int_as_float(dpp<kXor2>(__float_as_int(x))));
+  x = max2(x, __int_as_float(dpp<kHalfMirror>(__float_as_int(x))));
+  x = max2(x, __int_as_float(dpp<kMirror>(__float_as_int(x))));
+  const auto p = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  x = max2(__uint_as_float(p[0]), __uint_as_float(p[1]));
+  const u32x2 q = halves(__float_as_uint(x));
+  return max2(__uint_as_float(q[0]), __uint_as_float(q[1]));
+}
+
+// The smallest of the 64 lanes' scores and its index (the lowest among equals),
+// in every lane.
+__device__ __forceinline__ void wave_argmin(double& best, int& bj) {
+  auto take = [&](double ob, int oj) __attribute__((always_inline)) {
+    if (ob < best || (ob == best && oj < bj)) {
+      best = ob;
+      bj = oj;
+    }
+  };
+  take(dpp<kXor1>(best), dpp<kXor1>(bj));
+  take(dpp<kXor2>(best), dpp<kXor2>(bj));
+  take(dpp<kHalfMirror>(best), dpp<kHalfMirror>(bj));
+  take(dpp<kMirror>(best), dpp<kMirror>(bj));
+  auto halves2 = [&](uint32_t lo, uint32_t hi) __attribute__((always_inline)) {
+    return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+  };
+  {
+    const long long b = __double_as_longlong(best);
+    const auto l = __builtin_amdgcn_permlane16_swap((uint32_t)b, (uint32_t)b, false, false);
+    const auto u = __builtin_amdgcn_permlane16_swap((uint32_t)(b >> 32), (uint32_t)(b >> 32), false, false);
+    const auto j = __builtin_amdgcn_permlane16_swap((uint32_t)bj, (uint32_t)bj, false, false);
+    best = halves2(l[0], u[0]);
+    bj = (int)j[0];
+    take(halves2(l[1], u[1]), (int)j[1]);
+  }
+  {
+    const long long b = __double_as_longlong(best);
+    const auto l = __builtin_amdgcn_permlane32_swap((uint32_t)b, (uint32_t)b, false, false);
+    const auto u = __builtin_amdgcn_permlane32_swap((uint32_t)(b >> 32), (uint32_t)(b >> 32), false, false);
+    const auto j = __builtin_amdgcn_permlane32_swap((uint32_t)bj, (uint32_t)bj, false, false);
+    best = halves2(l[0], u[0]);
+    bj = (int)j[0];
+    take(halves2(l[1], u[1]), (int)j[1]);
+  }
+}
+
+// |r|^2 of a bf16 row split over the eight lanes 8 k .. 8 k + 7 (rc: this lane's
+// eight features), in all of them.  The canonical value is the fp64 fma chain
+// over c = 0..63.  Each square of a bf16 number is exact in fp64 (16 significant
+// bits); if the nonzero squares of a row span at most 31 binades, every partial
+// sum in any order is a multiple of the smallest square's last bit and below
+// 2^53 of it, so every partial sum is exact and any summation order gives the
+// chain's bits.  False: not provably so, the caller runs the chain.
+__device__ __forceinline__ int sq_exp(double x) {  // biased exponent of a square (0 for 0)
+  return (int)((__double_as_longlong(x) >> 52) & 2047);
+}
+__device__ __forceinline__ bool norm8(const double (&rc)[8], double& nrm) {
+  double acc = 0.0;
+  int emax = 0, emin = 4096;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    const double q = rc[e] * rc[e];  // exact
+    acc += q;
+    if (q != 0.0) {
+      emax = max(emax, sq_exp(q));
+      emin = min(emin, sq_exp(q));
+    }
+  }
+  acc += dpp<kXor1>(acc);
+  acc += dpp<kXor2>(acc);
+  acc += dpp<kHalfMirror>(acc);
+  emax = max(emax, dpp<kXor1>(emax));
+  emin = min(emin, dpp<kXor1>(emin));
+  emax = max(emax, dpp<kXor2>(emax));
+  emin = min(emin, dpp<kXor2>(emin));
+  emax = max(emax, dpp<kHalfMirror>(emax));
+  emin = min(emin, dpp<kHalfMirror>(emin));
+  nrm = acc;
+  return emin == 4096 || emax - emin <= 31;
+}
+
 // |r|^2 as an fp64 fma chain over c = 0..63 (lane c holds r_c); same value in all lanes.
 __device__ double canon_nrm_wave(float r) {
   double acc = 0.0;
@@ -155,15 +258,7 @@ __device__ void exact_argmin_keys(const double* kd, const uint16_t* Rs, const do
   }
 #pragma unroll
   for (int b = 0; b < NK; ++b) {
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) {
-      const double ob = __shfl_xor(best[b], off);
-      const int oj = __shfl_xor(bj[b], off);
-      if (ob < best[b] || (ob == best[b] && oj < bj[b])) {
-        best[b] = ob;
-        bj[b] = oj;
-      }
-    }
+    wave_argmin(best[b], bj[b]);
     jb[b] = bj[b];
   }
 }
@@ -248,12 +343,6 @@ __device__ __forceinline__ int local_group(int b, int v) { return 32 * b + v + (
 struct Certify {
   float nmaxf, rmaxf, cm, cp;
 };
-
-// (value of lane q, value of lane q + 32) in every lane l, q = l % 32.
-__device__ __forceinline__ u32x2 halves(uint32_t x) {
-  const auto r = __builtin_amdgcn_permlane32_swap(x, x, false, false);
-  return u32x2{r[0], r[1]};
-}
 
 // Upper bound of |k| for the key whose 64 bf16 features are split over lanes
 // q and q + 32 (32 each, as MFMA fragments); the same value in both lanes.

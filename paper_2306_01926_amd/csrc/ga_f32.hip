@@ -81,16 +81,7 @@ __device__ __forceinline__ void exact_keys(const float* const (&k)[kExactK], con
     }
   }
 #pragma unroll
-  for (int b = 0; b < NK; ++b)
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) {
-      const double ob = __shfl_xor(best[b], off);
-      const int oj = __shfl_xor(jb[b], off);
-      if (ob < best[b] || (ob == best[b] && oj < jb[b])) {
-        best[b] = ob;
-        jb[b] = oj;
-      }
-    }
+  for (int b = 0; b < NK; ++b) wave_argmin(best[b], jb[b]);
 }
 
 // k_assign_f32: grid (ceil(tiles / (4 tpw)), BH), 256 threads; each wave

@@ -247,19 +247,29 @@ __device__ __forceinline__ double stage_reps(const uint16_t* __restrict__ Rbh, c
       *(u32x4*)(Rs + swz(row, ch)) = v;
     }
   } else {
-    for (int idx = tid; idx < Npad * 8; idx += 256) {
-      const int row = idx >> 3, ch = idx & 7;
-      u32x4 v = {0u, 0u, 0u, 0u};
-      if (row < N) {
-        const u32x4 w = *(const u32x4*)(Rbh + (int64_t)row * 64 + ch * 8);
+    constexpr int IT = 8;  // 16-byte loads in flight per thread: 256 rows a step
+    for (int i0 = tid; i0 < Npad * 8; i0 += 256 * IT) {
+      u32x4 w[IT];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const uint32_t lo = __float_as_uint(bf16_to_f32(w[e] & 0xffffu) * -2.0f) >> 16;
-          const uint32_t hi = __float_as_uint(bf16_to_f32(w[e] >> 16) * -2.0f) >> 16;
-          v[e] = lo | (hi << 16);
-        }
+      for (int it = 0; it < IT; ++it) {
+        const int idx = i0 + it * 256, row = min(idx >> 3, N - 1), ch = idx & 7;
+        w[it] = *(const u32x4*)(Rbh + (int64_t)row * 64 + ch * 8);
       }
-      *(u32x4*)(Rs + swz(row, ch)) = v;
+#pragma unroll
+      for (int it = 0; it < IT; ++it) {
+        const int idx = i0 + it * 256, row = idx >> 3, ch = idx & 7;
+        if (row >= Npad) break;
+        u32x4 v = {0u, 0u, 0u, 0u};
+        if (row < N) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const uint32_t lo = __float_as_uint(bf16_to_f32(w[it][e] & 0xffffu) * -2.0f) >> 16;
+            const uint32_t hi = __float_as_uint(bf16_to_f32(w[it][e] >> 16) * -2.0f) >> 16;
+            v[e] = lo | (hi << 16);
+          }
+        }
+        *(u32x4*)(Rs + swz(row, ch)) = v;
+      }
     }
   }
   if (j < Npad) *(u32x4*)(Ns + j * 8) = sp;
@@ -718,12 +728,6 @@ __global__ __launch_bounds__(256) void k_assign_bf16(
   const AssignLds L = assign_lds_layout(smem, Npad, tpw, false, &cnt);
   const uint16_t* Rs = L.Rs;
   const uint16_t* Ns = L.Ns;
-  const double nmax = stage_reps<0>(R + bh * (int64_t)N * 64, nsplit + bh * N * 8, nrm64 + bh * N, N, Npad, L.Rs,
-                                    L.Ns, red);
-  const float nmaxf = (float)nmax * (1.0f + 0x1p-20f);
-  const float rmaxf = sqrtf(nmaxf) * (1.0f + 0x1p-20f);
-  const Certify cf = {nmaxf, rmaxf, cm, cp};
-
   const int nblk = Npad >> 5;
   const int64_t key0 = (int64_t)blockIdx.x * 4 * tpw * 32;
   const int wv = __builtin_amdgcn_readfirstlane(wave);
@@ -752,10 +756,16 @@ __global__ __launch_bounds__(256) void k_assign_bf16(
       oldv = valid ? belong_bh[key] : 0;
     }
   };
+  // the first tiles load while the workgroup stages R
   if (tcount > 0) {
     fetch(0, kf[0], kn[0], old[0]);
     fetch(1, kf[1], kn[1], old[1]);
   }
+  const double nmax = stage_reps<0>(R + bh * (int64_t)N * 64, nsplit + bh * N * 8, nrm64 + bh * N, N, Npad, L.Rs,
+                                    L.Ns, red);
+  const float nmaxf = (float)nmax * (1.0f + 0x1p-20f);
+  const float rmaxf = sqrtf(nmaxf) * (1.0f + 0x1p-20f);
+  const Certify cf = {nmaxf, rmaxf, cm, cp};
 
   for (int tt = 0; tt < tcount; tt += 2) {
     u32x4 kf_n[2][4];
@@ -1061,6 +1071,27 @@ __device__ __forceinline__ void run_sums(const uint32_t* ent, const uint8_t* eg,
 constexpr int kGsumG = 32;
 constexpr int kGsumList = 8192;  // entry capacity of the sorted chunk list
 
+// The canonical |r|^2 and its split of up to 32 groups from their bf16
+// representatives rows[g][64] in LDS (row stride rs): eight lanes per group
+// (norm8), 256 threads; ok: this thread's group tid / 8 is wanted.
+__device__ __forceinline__ void store_norms(const float* rows, int rs, bool ok, double* __restrict__ nrm64,
+                                            uint16_t* __restrict__ nsplit) {
+  const int g = threadIdx.x >> 3, j = threadIdx.x & 7;
+  const float* r = rows + g * rs;
+  double rc[8], nrm;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) rc[e] = ok ? (double)r[8 * j + e] : 0.0;
+  const bool exact = norm8(rc, nrm);
+  if (!ok || j != 0) return;
+  if (!exact) {  // the chain itself
+    nrm = 0.0;
+#pragma unroll 8
+    for (int c = 0; c < 64; ++c) nrm = fma((double)r[c], (double)r[c], nrm);
+  }
+  nrm64[g] = nrm;
+  write_nsplit(nrm, nsplit + g * 8);
+}
+
 // Finishes groups g0 .. g0 + ng - 1 of slice bh from their fp64 sums
 // acc[kGsumG][64] and (MODE 0) counts dcnt; scratch: kGsumG * 65 words of LDS.
 template <int MODE>
@@ -1128,17 +1159,7 @@ __device__ __forceinline__ void gsum_finish(const double* acc, const int* dcnt, 
   }
   if (MODE == 2) return;
   __syncthreads();
-  if (tid < ng) {
-    const int64_t row = bh * N + g0 + tid;
-    double nrm = 0.0;
-#pragma unroll 8
-    for (int c = 0; c < 64; ++c) {
-      const double rc = (double)rsh[tid * 65 + c];
-      nrm = fma(rc, rc, nrm);
-    }
-    nrm64[row] = nrm;
-    write_nsplit(nrm, nsplit + row * 8);
-  }
+  store_norms(rsh, 65, (tid >> 3) < ng, nrm64 + bh * N + g0, nsplit + (bh * N + g0) * 8);
 }
 
 template <int MODE>
@@ -1276,6 +1297,7 @@ __global__ __launch_bounds__(256) void k_gsum_finish(const double* __restrict__ 
 //     sort, no padding);
 //   - run_sums adds the rows (joins +, leaves -).
 constexpr int kDeltaCh = 4096;  // records per pass (at most 2 entries each)
+constexpr int kDeltaPre = 1024;  // records requested before their count is known
 __global__ __launch_bounds__(256) void k_gdelta(const uint16_t* __restrict__ X,
                                                 const unsigned long long* __restrict__ mrec,
                                                 const int32_t* __restrict__ mcount_cur,
@@ -1310,21 +1332,26 @@ __global__ __launch_bounds__(256) void k_gdelta(const uint16_t* __restrict__ X,
     hit[tid] = 0;
   }
 
-  // (a slice records at most n moved keys; the clamp keeps the loads below in
-  // bounds even if the workspace was corrupted, e.g. shared by overlapping calls)
+  // The first kDeltaPre records are requested beside their count, before it is
+  // known (in bounds: the list has n places).  A slice records at most n moved
+  // keys; the clamp keeps the loads below in bounds even if the workspace was
+  // corrupted, e.g. shared by overlapping calls.
+  const unsigned long long* rec = mrec + bh * n;
+  unsigned long long pre[kDeltaPre / 256];
+#pragma unroll
+  for (int u = 0; u < kDeltaPre / 256; ++u) pre[u] = rec[min(tid + 256 * u, n - 1)];
   const int64_t total = min((int64_t)mcount_cur[bh], (int64_t)n);
-  constexpr int PER = kDeltaCh / 256;
   const uint16_t* Xb = X + bh * (int64_t)n * 64;
-  for (int64_t c0 = 0; c0 < total; c0 += kDeltaCh) {
+  auto pass = [&](int64_t c0, const auto& r) {
+    constexpr int PER = sizeof(r) / sizeof(unsigned long long);
     uint32_t kv[PER];
     int gj[PER], gl[PER];
 #pragma unroll
     for (int u = 0; u < PER; ++u) {
-      const int64_t e = c0 + tid + 256 * u, ec = min(e, total - 1);
-      const unsigned long long r = mrec[bh * n + ec];
-      kv[u] = (uint32_t)min((int)(r >> 32) & 0x7fffffff, n - 1);
-      gj[u] = e < total ? (int)(r & 0xffffu) - g0 : -1;
-      gl[u] = e < total ? (int)((r >> 16) & 0xffffu) - g0 : -1;
+      const bool in = c0 + tid + 256 * u < total;
+      kv[u] = (uint32_t)min((int)(r[u] >> 32) & 0x7fffffff, n - 1);
+      gj[u] = in ? (int)(r[u] & 0xffffu) - g0 : -1;
+      gl[u] = in ? (int)((r[u] >> 16) & 0xffffu) - g0 : -1;
     }
     __syncthreads();  // zeroed counters; the previous pass is done with the list
     // 1. count, offsets, scatter (the list keeps the groups in order)
@@ -1371,6 +1398,16 @@ __global__ __launch_bounds__(256) void k_gdelta(const uint16_t* __restrict__ X,
     run_sums(ent, eg, eoff[kGsumG], Xb, acc, wave, lane);
     __syncthreads();
     if (tid < kGsumG) ecnt[tid] = 0;
+  };
+  if (total <= kDeltaPre) {
+    if (total > 0) pass(0, pre);
+  } else {
+    for (int64_t c0 = 0; c0 < total; c0 += kDeltaCh) {
+      unsigned long long r[kDeltaCh / 256];
+#pragma unroll
+      for (int u = 0; u < kDeltaCh / 256; ++u) r[u] = rec[min(c0 + tid + 256 * u, total - 1)];
+      pass(c0, r);
+    }
   }
   __syncthreads();
 
@@ -1396,17 +1433,7 @@ __global__ __launch_bounds__(256) void k_gdelta(const uint16_t* __restrict__ X,
     rsh[g * 65 + c] = r;
   }
   __syncthreads();
-  if (tid < ng && hit[tid]) {
-    const int64_t row = bh * N + g0 + tid;
-    double nrm = 0.0;
-#pragma unroll 8
-    for (int c = 0; c < 64; ++c) {
-      const double rc = (double)rsh[tid * 65 + c];
-      nrm = fma(rc, rc, nrm);
-    }
-    nrm64[row] = nrm;
-    write_nsplit(nrm, nsplit + row * 8);
-  }
+  store_norms(rsh, 65, (tid >> 3) < ng && hit[tid >> 3], nrm64 + bh * N + g0, nsplit + (bh * N + g0) * 8);
   if (blockIdx.x == 0 && tid == 0) mcount_next[bh] = 0;
 }
 

@@ -188,33 +188,6 @@ __device__ __forceinline__ LloydLds lloyd_layout(unsigned char* base, int Npad, 
   return l;
 }
 
-// ------------------------------------------------------------ cross-lane
-// Lane exchanges by DPP (VALU, no LDS round trip): within 8 lanes as the xors
-// 1, 2 and (equal to 4 once the quads agree) the half-row mirror.
-template <int CTRL>
-__device__ __forceinline__ int dpp(int x) {
-  return __builtin_amdgcn_update_dpp(0, x, CTRL, 0xf, 0xf, true);
-}
-template <int CTRL>
-__device__ __forceinline__ double dpp(double x) {
-  const long long b = __double_as_longlong(x);
-  const uint32_t lo = (uint32_t)dpp<CTRL>((int)(uint32_t)b), hi = (uint32_t)dpp<CTRL>((int)(uint32_t)(b >> 32));
-  return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
-}
-constexpr int kXor1 = 0xB1, kXor2 = 0x4E, kHalfMirror = 0x141, kMirror = 0x140;
-
-// The largest of the 64 lanes' values, in every lane.
-__device__ __forceinline__ float wave_max(float x) {
-  x = max2(x, __int_as_float(dpp<kXor1>(__float_as_int(x))));
-  x = max2(x, __int_as_float(dpp<kXor2>(__float_as_int(x))));
-  x = max2(x, __int_as_float(dpp<kHalfMirror>(__float_as_int(x))));
-  x = max2(x, __int_as_float(dpp<kMirror>(__float_as_int(x))));
-  const auto p = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-  x = max2(__uint_as_float(p[0]), __uint_as_float(p[1]));
-  const u32x2 q = halves(__float_as_uint(x));
-  return max2(__uint_as_float(q[0]), __uint_as_float(q[1]));
-}
-
 // ------------------------------------------------------------ barrier
 // Arrive at barrier number k (0-based) of the slice and wait for all P ranks.
 // Returns false if the wait gave up (spin limit) or another workgroup did.
@@ -842,18 +815,7 @@ __device__ __forceinline__ int lloyd_gather(const LloydArgs& a, const LloydLds& 
 // share one counter (vmcnt): a load the compiler cannot track (e.g. a
 // conditional one) would make it wait for every earlier store, including the
 // slow device-scope ones, before each later use.
-//
-// |r|^2: the canonical value is the fp64 fma chain over c = 0..63.  Each
-// square of a bf16 component is exact in fp64 (16 significant bits); if the
-// nonzero squares of a row span at most 31 binades, every partial sum in any
-// order is a multiple of the smallest square's last bit and below 2^53 of it,
-// so every partial sum is exact and any summation order gives the chain's
-// bits (eight lanes per row sum eight squares each, then a shuffle tree).
-// Rows outside that range take the chain itself.
 constexpr int kLFinU = 128 * 32 / kLT;  // (group, feature pair) items per thread, Go <= 128
-__device__ __forceinline__ int sq_exp(double x) {  // biased exponent of a square (0 for 0)
-  return (int)((__double_as_longlong(x) >> 52) & 2047);
-}
 // The previous C of the rank's groups, (group, feature pair) items
 // tid + kLT u (clamped loads: every address is in bounds).
 __device__ __forceinline__ void lloyd_prev_c(const LloydArgs& a, int64_t s, int r, int Go, float2 (&prev)[kLFinU]) {
@@ -912,32 +874,12 @@ __device__ __forceinline__ void lloyd_finish(const LloydArgs& a, const LloydLds&
     const int t = base + tid, lg = t >> 3, j = t & 7, g = r + a.P * lg;
     const bool ok = lg < Go && g < a.N;
     const u32x4 w = ok ? *(const u32x4*)(rows + lg * kLRowS + 4 * j) : u32x4{0u, 0u, 0u, 0u};
-    double acc = 0.0;
-    int emax = 0, emin = 4096;
+    double rc[8], nrm;
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const uint32_t bits = (e & 1) ? (w[e >> 1] >> 16) : (w[e >> 1] & 0xffffu);
-      const double rc = (double)bf16_to_f32(bits);
-      const double q = rc * rc;  // exact
-      acc += q;
-      if (q != 0.0) {
-        emax = max(emax, sq_exp(q));
-        emin = min(emin, sq_exp(q));
-      }
-    }
-    // the group's eight lanes are consecutive lanes of one wave
-    acc += dpp<kXor1>(acc);
-    acc += dpp<kXor2>(acc);
-    acc += dpp<kHalfMirror>(acc);
-    emax = max(emax, dpp<kXor1>(emax));
-    emin = min(emin, dpp<kXor1>(emin));
-    emax = max(emax, dpp<kXor2>(emax));
-    emin = min(emin, dpp<kXor2>(emin));
-    emax = max(emax, dpp<kHalfMirror>(emax));
-    emin = min(emin, dpp<kHalfMirror>(emin));
+    for (int e = 0; e < 8; ++e) rc[e] = (double)bf16_to_f32((e & 1) ? (w[e >> 1] >> 16) : (w[e >> 1] & 0xffffu));
+    const bool exact = norm8(rc, nrm);
     if (!ok || j != 0) continue;
-    double nrm = acc;
-    if (emin != 4096 && emax - emin > 31) {  // not provably exact: the chain itself
+    if (!exact) {  // the chain itself
       nrm = 0.0;
 #pragma unroll
       for (int k = 0; k < 8; ++k) {
