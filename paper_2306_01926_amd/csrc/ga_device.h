@@ -28,12 +28,14 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
 // Storage-dtype traits: load as float, representative rounding, store.
 struct F32 {
   using T = float;
+  static constexpr int kBits = 32;
   __device__ static float load(const float* p, int64_t i) { return p[i]; }
   __device__ static float rep(float c) { return c; }
   __device__ static void store(float* p, int64_t i, float r) { p[i] = r; }
 };
 struct BF16 {
   using T = uint16_t;
+  static constexpr int kBits = 16;
   __device__ static float load(const uint16_t* p, int64_t i) { return bf16_to_f32(p[i]); }
   __device__ static float rep(float c) { return bf16_to_f32(f32_to_bf16(c)); }
   __device__ static void store(uint16_t* p, int64_t i, float r) { p[i] = (uint16_t)(__float_as_uint(r) >> 16); }

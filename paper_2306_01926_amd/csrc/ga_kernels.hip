@@ -47,10 +47,32 @@ constexpr int kOs = 72;          // LDS row stride (bf16) of the attention outpu
 constexpr int kExactB = 4;       // queued keys decided together by one wave in k_assign_reg
 constexpr int kAttMaxN = 256; // groups held in LDS by the bf16 attention kernel
 
+// The canonical |r|^2 and its split of up to 32 groups from their bf16
+// representatives rows[g][64] in LDS (row stride rs): eight lanes per group
+// (norm8); ok: this thread's group tid / 8 is one of them.
+__device__ __forceinline__ void store_norms(const float* rows, int rs, bool ok, double* __restrict__ nrm64,
+                                            uint16_t* __restrict__ nsplit) {
+  const int g = threadIdx.x >> 3, j = threadIdx.x & 7;
+  const float* r = rows + g * rs;
+  double rc[8], nrm;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) rc[e] = ok ? (double)r[8 * j + e] : 0.0;
+  const bool exact = norm8(rc, nrm);
+  if (!ok || j != 0) return;
+  if (!exact) {  // the chain itself
+    nrm = 0.0;
+#pragma unroll 8
+    for (int c = 0; c < 64; ++c) nrm = fma((double)r[c], (double)r[c], nrm);
+  }
+  nrm64[g] = nrm;
+  write_nsplit(nrm, nsplit + g * 8);
+}
+
 // ------------------------------------------------------------------ init
 // grid (ceil(N/64), BH), 256 threads; groups g0 = 64 x .. g0 + 63.  Each wave
 // reads 16 groups' initial rows at once (lane = feature) and writes C and R;
-// then one lane per group forms the canonical |r|^2 from the LDS copy of R.
+// then the canonical |r|^2 is formed from the LDS copy of R (bf16: eight lanes per
+// group; fp32: one lane's chain).
 template <class S>
 __global__ __launch_bounds__(256) void k_init(const typename S::T* __restrict__ K,
                                               const float* __restrict__ init, int n, int N,
@@ -83,6 +105,11 @@ __global__ __launch_bounds__(256) void k_init(const typename S::T* __restrict__ 
     mcount[gridDim.y + bh] = 0;
   }
   __syncthreads();
+  if constexpr (S::kBits == 16) {
+    for (int g = 0; g < ng; g += 32)
+      store_norms(&rsh[g][0], 65, g + (tid >> 3) < ng, nrm64 + bh * N + g0 + g, nsplit + (bh * N + g0 + g) * 8);
+    return;
+  }
   if (tid < ng) {
     const int64_t row = bh * N + g0 + tid;
     double nrm = 0.0;
@@ -985,7 +1012,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
 // ------------------------------------------------------------------ group sums (bf16)
 // run_sums: the rows of a group-sorted entry list (ent: key | leave << 31;
 // eg: the entry's group within the workgroup's block) added into the LDS sums
-// acc[g][64] by one workgroup of 4 waves.  The list is cut into 32 contiguous
+// acc[g][64] by one workgroup of T threads.  The list is cut into T / 8 contiguous
 // ranges, one per 8-lane slot (lane j of a slot holds features 8 j .. 8 j + 7
 // of the slot's row, one 16-byte load); a slot adds its rows in fp64
 // registers while the group stays the same and adds the partial sum into acc
@@ -993,12 +1020,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
 // the rows.  The member sums are exact in fp64 (see the bf16 member sums
 // above), so neither the cut nor the order of the atomics can change a bit.
 constexpr int kRunU = 8;  // rows per slot and batch (two batches in flight)
+template <int T>
 __device__ __forceinline__ void run_sums(const uint32_t* ent, const uint8_t* eg, int ne,
                                          const uint16_t* __restrict__ Xb, double* acc, int wave, int lane) {
   if (ne <= 0) return;
   const int j = lane & 7, gsl = 8 * wave + (lane >> 3);
-  const int b0 = (int)((int64_t)gsl * ne / 32), b1 = (int)((int64_t)(gsl + 1) * ne / 32);
-  const int steps = (ne + 31) / 32;  // >= every slot's range (they differ by at most one)
+  constexpr int kSlots = T / 8;
+  const int b0 = (int)((int64_t)gsl * ne / kSlots), b1 = (int)((int64_t)(gsl + 1) * ne / kSlots);
+  const int steps = (ne + kSlots - 1) / kSlots;  // >= every slot's range (they differ by at most one)
   double a[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
   int cur = -1;
   auto load = [&](int k0, uint32_t (&ei)[kRunU], int (&gi)[kRunU], u32x4 (&w)[kRunU]) {
@@ -1049,7 +1078,7 @@ __device__ __forceinline__ void run_sums(const uint32_t* ent, const uint8_t* eg,
 // The member sums of the bf16 path are exact in fp64 (see above), so they can
 // be accumulated in any order and split any way: no global bucketing.
 //
-// k_gsum: grid (ceil(N / 32), BH, Z), 256 threads.  Workgroup (x, bh, z) sums
+// k_gsum: grid (ceil(N / 32), BH, Z), T threads (gsum_threads).  Workgroup (x, bh, z) sums
 // the rows of the keys [z ck, (z + 1) ck) of slice bh that belong to groups
 // g0 = 32 x .. g0 + 31 and, with Z = 1, finishes the groups itself:
 //   MODE 0 (first round): S = sum of the member key rows, count = members
@@ -1071,30 +1100,9 @@ __device__ __forceinline__ void run_sums(const uint32_t* ent, const uint8_t* eg,
 constexpr int kGsumG = 32;
 constexpr int kGsumList = 8192;  // entry capacity of the sorted chunk list
 
-// The canonical |r|^2 and its split of up to 32 groups from their bf16
-// representatives rows[g][64] in LDS (row stride rs): eight lanes per group
-// (norm8), 256 threads; ok: this thread's group tid / 8 is wanted.
-__device__ __forceinline__ void store_norms(const float* rows, int rs, bool ok, double* __restrict__ nrm64,
-                                            uint16_t* __restrict__ nsplit) {
-  const int g = threadIdx.x >> 3, j = threadIdx.x & 7;
-  const float* r = rows + g * rs;
-  double rc[8], nrm;
-#pragma unroll
-  for (int e = 0; e < 8; ++e) rc[e] = ok ? (double)r[8 * j + e] : 0.0;
-  const bool exact = norm8(rc, nrm);
-  if (!ok || j != 0) return;
-  if (!exact) {  // the chain itself
-    nrm = 0.0;
-#pragma unroll 8
-    for (int c = 0; c < 64; ++c) nrm = fma((double)r[c], (double)r[c], nrm);
-  }
-  nrm64[g] = nrm;
-  write_nsplit(nrm, nsplit + g * 8);
-}
-
 // Finishes groups g0 .. g0 + ng - 1 of slice bh from their fp64 sums
 // acc[kGsumG][64] and (MODE 0) counts dcnt; scratch: kGsumG * 65 words of LDS.
-template <int MODE>
+template <int MODE, int T>
 __device__ __forceinline__ void gsum_finish(const double* acc, const int* dcnt, uint32_t* scratch, int64_t bh, int g0,
                                             int ng, int N, double* __restrict__ S64, int32_t* __restrict__ count,
                                             float* __restrict__ out, uint16_t* __restrict__ R,
@@ -1102,12 +1110,12 @@ __device__ __forceinline__ void gsum_finish(const double* acc, const int* dcnt, 
                                             float inv_sl2e, int vts) {
   const int tid = threadIdx.x;
   float* rsh = (float*)scratch;  // [32][65] bf16 representatives
-  // element (g, c) = (idx / 64, idx % 64), 8 per thread
-  constexpr int EPT = kGsumG * 64 / 256;
+  // element (g, c) = (idx / 64, idx % 64), EPT per thread
+  constexpr int EPT = kGsumG * 64 / T;
   int pc[EPT];
 #pragma unroll
   for (int u = 0; u < EPT; ++u) {
-    const int idx = tid + 256 * u, g = idx >> 6;
+    const int idx = tid + T * u, g = idx >> 6;
     const int64_t row = bh * N + g0 + min(g, ng - 1);
     pc[u] = MODE == 3 ? count[row] : 0;
   }
@@ -1119,7 +1127,7 @@ __device__ __forceinline__ void gsum_finish(const double* acc, const int* dcnt, 
     uint16_t* mt = (uint16_t*)scratch;  // [64][36]
 #pragma unroll
     for (int u = 0; u < EPT; ++u) {
-      const int idx = tid + 256 * u, g = idx >> 6, c = idx & 63;
+      const int idx = tid + T * u, g = idx >> 6, c = idx & 63;
       const float vs = g < ng ? (float)acc[g * 64 + c] : 0.f;
       const int cnt = g < ng ? pc[u] : 0;
       mt[c * 36 + g] = (uint16_t)f32_to_bf16(cnt > 0 ? vs / (float)cnt : 0.f);
@@ -1127,15 +1135,15 @@ __device__ __forceinline__ void gsum_finish(const double* acc, const int* dcnt, 
     }
     __syncthreads();
 #pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      const int x = tid + 256 * u, f = x >> 3, q4 = x & 7;  // 64 features x 8 segments of 4 groups
+    for (int u = 0; u < 512 / T; ++u) {
+      const int x = tid + T * u, f = x >> 3, q4 = x & 7;  // 64 features x 8 segments of 4 groups
       *(uint2*)(R + (bh * 64 + f) * (int64_t)vts + g0 + 4 * q4) = *(const uint2*)(mt + f * 36 + 4 * q4);
     }
     return;
   }
 #pragma unroll
   for (int u = 0; u < EPT; ++u) {
-    const int idx = tid + 256 * u, g = idx >> 6, c = idx & 63;
+    const int idx = tid + T * u, g = idx >> 6, c = idx & 63;
     if (g >= ng) continue;
     const int64_t row = bh * N + g0 + g;
     const double s = acc[g * 64 + c];
@@ -1162,8 +1170,8 @@ __device__ __forceinline__ void gsum_finish(const double* acc, const int* dcnt, 
   store_norms(rsh, 65, (tid >> 3) < ng, nrm64 + bh * N + g0, nsplit + (bh * N + g0) * 8);
 }
 
-template <int MODE>
-__global__ __launch_bounds__(256) void k_gsum(const uint16_t* __restrict__ X, const int32_t* __restrict__ belong,
+template <int MODE, int T>
+__global__ __launch_bounds__(T) void k_gsum(const uint16_t* __restrict__ X, const int32_t* __restrict__ belong,
                                               int n, int N, int ck, double* __restrict__ part,
                                               int32_t* __restrict__ pcnt, double* __restrict__ S64,
                                               int32_t* __restrict__ count, float* __restrict__ out, uint16_t* __restrict__ R,
@@ -1176,24 +1184,24 @@ __global__ __launch_bounds__(256) void k_gsum(const uint16_t* __restrict__ X, co
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int64_t bh = blockIdx.y;
   const int g0 = blockIdx.x * kGsumG, ng = min(kGsumG, N - g0);
-  for (int i = tid; i < kGsumG * 64; i += 256) acc[i] = 0.0;
+  for (int i = tid; i < kGsumG * 64; i += T) acc[i] = 0.0;
   if (tid < kGsumG) dcnt[tid] = 0;
 
   const int64_t begin = (int64_t)blockIdx.z * ck, total = min((int64_t)n, begin + ck);
   constexpr int CH = kGsumList;  // keys per chunk
-  constexpr int PER = CH / 256;
+  constexpr int PER = CH / T;
   const uint16_t* Xb = X + bh * (int64_t)n * 64;
   for (int64_t c0 = begin; c0 < total; c0 += CH) {
     int gj[PER];
     // every lane loads (index clamped into the chunk) so that the loads overlap
 #pragma unroll
     for (int u = 0; u < PER; ++u) {
-      const int64_t e = c0 + tid + 256 * u;
+      const int64_t e = c0 + tid + T * u;
       gj[u] = belong[bh * n + min(e, total - 1)] - g0;
     }
 #pragma unroll
     for (int u = 0; u < PER; ++u)
-      if (c0 + tid + 256 * u >= total) gj[u] = -1;
+      if (c0 + tid + T * u >= total) gj[u] = -1;
     if (tid < kGsumG) ecnt[tid] = 0;
     __syncthreads();
     // 1. count, lay out, scatter
@@ -1226,30 +1234,30 @@ __global__ __launch_bounds__(256) void k_gsum(const uint16_t* __restrict__ X, co
       const int g = gj[u];
       if ((unsigned)g < (unsigned)ng) {
         const int pos = atomicAdd(&ecur[g], 1);
-        ent[pos] = (uint32_t)(c0 + tid + 256 * u);
+        ent[pos] = (uint32_t)(c0 + tid + T * u);
         eg[pos] = (uint8_t)g;
       }
     }
     __syncthreads();
     // 2. the rows, summed per group
-    run_sums(ent, eg, eoff[kGsumG], Xb, acc, wave, lane);
+    run_sums<T>(ent, eg, eoff[kGsumG], Xb, acc, wave, lane);
     __syncthreads();
   }
 
   // 3. finish the owned groups, or hand the sums on
   if (gridDim.z == 1) {
-    gsum_finish<MODE>(acc, dcnt, ent, bh, g0, ng, N, S64, count, out, R, nrm64, nsplit, inv_sl2e, vts);
+    gsum_finish<MODE, T>(acc, dcnt, ent, bh, g0, ng, N, S64, count, out, R, nrm64, nsplit, inv_sl2e, vts);
     return;
   }
   const int64_t row0 = (bh * gridDim.z + blockIdx.z) * (int64_t)((N + 31) & ~31) + g0;
-  for (int i = 2 * tid; i < kGsumG * 64; i += 512) *(double2*)(part + row0 * 64 + i) = *(const double2*)(acc + i);
+  for (int i = 2 * tid; i < kGsumG * 64; i += 2 * T) *(double2*)(part + row0 * 64 + i) = *(const double2*)(acc + i);
   if (MODE == 0 && tid < kGsumG) pcnt[row0 + tid] = dcnt[tid];
 }
 
-// k_gsum_finish: grid (ceil(N / 32), BH), 256 threads: adds the Z partial
+// k_gsum_finish: grid (ceil(N / 32), BH), 512 threads: adds the Z partial
 // sums (and MODE 0's counts) of k_gsum in order and finishes the groups.
 template <int MODE>
-__global__ __launch_bounds__(256) void k_gsum_finish(const double* __restrict__ part, const int32_t* __restrict__ pcnt,
+__global__ __launch_bounds__(512) void k_gsum_finish(const double* __restrict__ part, const int32_t* __restrict__ pcnt,
                                                      int Z, int N, double* __restrict__ S64,
                                                      int32_t* __restrict__ count, float* __restrict__ out,
                                                      uint16_t* __restrict__ R, double* __restrict__ nrm64,
@@ -1261,31 +1269,32 @@ __global__ __launch_bounds__(256) void k_gsum_finish(const double* __restrict__ 
   const int64_t bh = blockIdx.y, Npad = (N + 31) & ~31;
   const int g0 = blockIdx.x * kGsumG, ng = min(kGsumG, N - g0);
   const double* p = part + (bh * Z * Npad + g0) * 64 + 2 * tid;
-  double2 sum[4];
+  constexpr int kU = kGsumG * 32 / 512;
+  double2 sum[kU];
 #pragma unroll
-  for (int u = 0; u < 4; ++u) sum[u] = double2{0.0, 0.0};
+  for (int u = 0; u < kU; ++u) sum[u] = double2{0.0, 0.0};
 #pragma unroll 8
   for (int z = 0; z < Z; ++z) {
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const double2 v = *(const double2*)(p + z * Npad * 64 + 512 * u);
+    for (int u = 0; u < kU; ++u) {
+      const double2 v = *(const double2*)(p + z * Npad * 64 + 2 * 512 * u);
       sum[u].x += v.x;
       sum[u].y += v.y;
     }
   }
 #pragma unroll
-  for (int u = 0; u < 4; ++u) *(double2*)(acc + 2 * tid + 512 * u) = sum[u];
+  for (int u = 0; u < kU; ++u) *(double2*)(acc + 2 * tid + 2 * 512 * u) = sum[u];
   if (MODE == 0 && tid < kGsumG) {
     int c = 0;
     for (int z = 0; z < Z; ++z) c += pcnt[(bh * Z + z) * Npad + g0 + tid];
     dcnt[tid] = c;
   }
   __syncthreads();
-  gsum_finish<MODE>(acc, dcnt, scratch, bh, g0, ng, N, S64, count, out, R, nrm64, nsplit, inv_sl2e, vts);
+  gsum_finish<MODE, 512>(acc, dcnt, scratch, bh, g0, ng, N, S64, count, out, R, nrm64, nsplit, inv_sl2e, vts);
 }
 
 // ------------------------------------------------------------------ later-round update (bf16)
-// k_gdelta: grid (ceil(N / 32), BH), 256 threads: the later rounds' update
+// k_gdelta: grid (ceil(N / 32), BH), T threads (gsum_threads): the later rounds' update
 // of workgroup x's groups g0 = 32 x .. g0 + 31 of slice bh from the round's
 // moved-key records (key, group joined, group left): S += joins - leaves,
 // count += joins - leaves, then C, R, |r|^2 and its split as k_gsum forms them
@@ -1298,7 +1307,8 @@ __global__ __launch_bounds__(256) void k_gsum_finish(const double* __restrict__ 
 //   - run_sums adds the rows (joins +, leaves -).
 constexpr int kDeltaCh = 4096;  // records per pass (at most 2 entries each)
 constexpr int kDeltaPre = 1024;  // records requested before their count is known
-__global__ __launch_bounds__(256) void k_gdelta(const uint16_t* __restrict__ X,
+template <int T>
+__global__ __launch_bounds__(T) void k_gdelta(const uint16_t* __restrict__ X,
                                                 const unsigned long long* __restrict__ mrec,
                                                 const int32_t* __restrict__ mcount_cur,
                                                 int32_t* __restrict__ mcount_next, int n, int N,
@@ -1314,18 +1324,18 @@ __global__ __launch_bounds__(256) void k_gdelta(const uint16_t* __restrict__ X,
   const int64_t bh = blockIdx.y;
   const int g0 = blockIdx.x * kGsumG, ng = min(kGsumG, N - g0);
 
-  // previous sums and counts: element (g, c) = (idx / 64, idx % 64), 8 per thread
-  constexpr int EPT = kGsumG * 64 / 256;
+  // previous sums and counts: element (g, c) = (idx / 64, idx % 64), EPT per thread
+  constexpr int EPT = kGsumG * 64 / T;
   double prev[EPT];
   int pc[EPT];
 #pragma unroll
   for (int u = 0; u < EPT; ++u) {
-    const int idx = tid + 256 * u, g = idx >> 6, c = idx & 63;
+    const int idx = tid + T * u, g = idx >> 6, c = idx & 63;
     const int64_t row = bh * N + g0 + min(g, ng - 1);
     prev[u] = S64[row * 64 + c];
     pc[u] = count[row];
   }
-  for (int i = tid; i < kGsumG * 64; i += 256) acc[i] = 0.0;
+  for (int i = tid; i < kGsumG * 64; i += T) acc[i] = 0.0;
   if (tid < kGsumG) {
     ecnt[tid] = 0;
     dcnt[tid] = 0;
@@ -1337,9 +1347,9 @@ __global__ __launch_bounds__(256) void k_gdelta(const uint16_t* __restrict__ X,
   // keys; the clamp keeps the loads below in bounds even if the workspace was
   // corrupted, e.g. shared by overlapping calls.
   const unsigned long long* rec = mrec + bh * n;
-  unsigned long long pre[kDeltaPre / 256];
+  unsigned long long pre[kDeltaPre / T];
 #pragma unroll
-  for (int u = 0; u < kDeltaPre / 256; ++u) pre[u] = rec[min(tid + 256 * u, n - 1)];
+  for (int u = 0; u < kDeltaPre / T; ++u) pre[u] = rec[min(tid + T * u, n - 1)];
   const int64_t total = min((int64_t)mcount_cur[bh], (int64_t)n);
   const uint16_t* Xb = X + bh * (int64_t)n * 64;
   auto pass = [&](int64_t c0, const auto& r) {
@@ -1348,7 +1358,7 @@ __global__ __launch_bounds__(256) void k_gdelta(const uint16_t* __restrict__ X,
     int gj[PER], gl[PER];
 #pragma unroll
     for (int u = 0; u < PER; ++u) {
-      const bool in = c0 + tid + 256 * u < total;
+      const bool in = c0 + tid + T * u < total;
       kv[u] = (uint32_t)min((int)(r[u] >> 32) & 0x7fffffff, n - 1);
       gj[u] = in ? (int)(r[u] & 0xffffu) - g0 : -1;
       gl[u] = in ? (int)((r[u] >> 16) & 0xffffu) - g0 : -1;
@@ -1395,7 +1405,7 @@ __global__ __launch_bounds__(256) void k_gdelta(const uint16_t* __restrict__ X,
       }
     __syncthreads();
     // 2. the rows, summed per group
-    run_sums(ent, eg, eoff[kGsumG], Xb, acc, wave, lane);
+    run_sums<T>(ent, eg, eoff[kGsumG], Xb, acc, wave, lane);
     __syncthreads();
     if (tid < kGsumG) ecnt[tid] = 0;
   };
@@ -1403,9 +1413,9 @@ __global__ __launch_bounds__(256) void k_gdelta(const uint16_t* __restrict__ X,
     if (total > 0) pass(0, pre);
   } else {
     for (int64_t c0 = 0; c0 < total; c0 += kDeltaCh) {
-      unsigned long long r[kDeltaCh / 256];
+      unsigned long long r[kDeltaCh / T];
 #pragma unroll
-      for (int u = 0; u < kDeltaCh / 256; ++u) r[u] = rec[min(c0 + tid + 256 * u, total - 1)];
+      for (int u = 0; u < kDeltaCh / T; ++u) r[u] = rec[min(c0 + tid + T * u, total - 1)];
       pass(c0, r);
     }
   }
@@ -1414,7 +1424,7 @@ __global__ __launch_bounds__(256) void k_gdelta(const uint16_t* __restrict__ X,
   // the touched groups: S, count, C (an empty group keeps C), R, |r|^2
 #pragma unroll
   for (int u = 0; u < EPT; ++u) {
-    const int idx = tid + 256 * u, g = idx >> 6, c = idx & 63;
+    const int idx = tid + T * u, g = idx >> 6, c = idx & 63;
     if (g >= ng || !hit[g]) continue;
     const int64_t row = bh * N + g0 + g;
     const double S = prev[u] + acc[g * 64 + c];
@@ -1433,7 +1443,7 @@ __global__ __launch_bounds__(256) void k_gdelta(const uint16_t* __restrict__ X,
     rsh[g * 65 + c] = r;
   }
   __syncthreads();
-  store_norms(rsh, 65, (tid >> 3) < ng && hit[tid >> 3], nrm64 + bh * N + g0, nsplit + (bh * N + g0) * 8);
+  store_norms(rsh, 65, (tid >> 3) < ng && hit[(tid >> 3) & 31], nrm64 + bh * N + g0, nsplit + (bh * N + g0) * 8);
   if (blockIdx.x == 0 && tid == 0) mcount_next[bh] = 0;
 }
 
@@ -1995,21 +2005,30 @@ static int gsum_parts(const Dims& d) {
   return (int)max((int64_t)1, z);
 }
 
+// Threads of a workgroup of k_gsum and k_gdelta: 512 where the launch leaves about
+// one per compute unit (256 workgroups of 256 threads have four waves per unit:
+// the first round's sums of 32 slices, 256 groups 46 -> 37 us with 512), 256 where
+// more than one would share a unit, which 512 threads' registers do not allow
+// (512 workgroups at 128 slices of 8000 values, 128 groups: 43 us, 49 with 512).
+static int gsum_threads(int64_t wgs) { return wgs <= 320 ? 512 : 256; }
+
 template <int MODE>
 static hipError_t run_gsum(const Dims& d, const uint16_t* X, const int32_t* belong, double* part, int32_t* pcnt,
                            double* S64, int32_t* count, float* out, uint16_t* R, double* nrm64, uint16_t* nsplit,
                            float inv_sl2e, int vts, hipStream_t st) {
   const int Z = gsum_parts(d), ck = (int)cdiv(d.n, Z);
-  const dim3 grid(cdiv(d.N, kGsumG), (unsigned)d.BH, (unsigned)Z), block(256);
+  const dim3 grid(cdiv(d.N, kGsumG), (unsigned)d.BH, (unsigned)Z);
+  const int T = gsum_threads((int64_t)grid.x * grid.y * grid.z);
   {
     TimedLaunch timed(MODE == 0 ? "sums_full" : "valuesum", st);
-    hipLaunchKernelGGL(k_gsum<MODE>, grid, block, 0, st, X, belong, d.n, d.N, ck, part, pcnt, S64, count, out, R,
-                       nrm64, nsplit, inv_sl2e, vts);
+    const auto kern = T == 512 ? k_gsum<MODE, 512> : k_gsum<MODE, 256>;
+    hipLaunchKernelGGL(kern, grid, dim3(T), 0, st, X, belong, d.n, d.N, ck, part, pcnt, S64, count, out, R, nrm64,
+                       nsplit, inv_sl2e, vts);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess || Z == 1) return e;
   }
   TimedLaunch timed("sums_finish", st);
-  hipLaunchKernelGGL(k_gsum_finish<MODE>, dim3(grid.x, grid.y), block, 0, st, part, pcnt, Z, d.N, S64, count, out, R,
+  hipLaunchKernelGGL(k_gsum_finish<MODE>, dim3(grid.x, grid.y), dim3(512), 0, st, part, pcnt, Z, d.N, S64, count, out, R,
                      nrm64, nsplit, inv_sl2e, vts);
   return hipGetLastError();
 }
@@ -2023,7 +2042,9 @@ hipError_t launch_sums_full(const Dims& d, const void* K, const int32_t* belong,
 hipError_t launch_sums_delta(const Dims& d, const void* K, const int32_t* mcount_cur, int32_t* mcount_next,
                              const Workspace& w, int32_t* count, float* C, hipStream_t st) {
   TimedLaunch timed("sums_delta", st);
-  hipLaunchKernelGGL(k_gdelta, dim3(cdiv(d.N, kGsumG), (unsigned)d.BH), dim3(256), 0, st, (const uint16_t*)K, w.mrec,
+  const dim3 grid(cdiv(d.N, kGsumG), (unsigned)d.BH);
+  const int T = gsum_threads((int64_t)grid.x * grid.y);
+  hipLaunchKernelGGL(T == 512 ? k_gdelta<512> : k_gdelta<256>, grid, dim3(T), 0, st, (const uint16_t*)K, w.mrec,
                      mcount_cur, mcount_next, d.n, d.N, w.S64, count, C, (uint16_t*)w.R, w.nrm64, w.nsplit);
   return hipGetLastError();
 }
