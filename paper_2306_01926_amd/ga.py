@@ -149,8 +149,20 @@ def _check(rc: int):
         raise GAError(rc, lib().ga_last_error().decode())
 
 
+# torch's handle of the current stream without a Stream object (3 us less per
+# lookup, and every call needs one or two: the smallest calls are bound by the
+# host); a torch without it takes the public way.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
+def _stream_handle(device) -> int:
+    if _raw_stream is None or device.index is None:
+        return torch.cuda.current_stream(device).cuda_stream
+    return _raw_stream(device.index)
+
+
 def _stream(device) -> ctypes.c_void_p:
-    return ctypes.c_void_p(torch.cuda.current_stream(device).cuda_stream)
+    return ctypes.c_void_p(_stream_handle(device))
 
 
 _ws_cache: dict = {}
@@ -168,14 +180,13 @@ def workspace(shape: Shape, N: int, device, stream=None) -> tuple:
     calls without ws on different streams never share a buffer.  The buffer
     is allocated on (and its memory ordered by) that stream.
     """
-    device = torch.device(device)
-    if stream is None:
-        stream = torch.cuda.current_stream(device)
+    if not isinstance(device, torch.device):
+        device = torch.device(device)
     nbytes = max(workspace_bytes(shape, N), 256)
-    key = (device, stream.cuda_stream)
+    key = (device, _stream_handle(device) if stream is None else stream.cuda_stream)
     ws = _ws_cache.get(key)
     if ws is None or ws.numel() < nbytes:
-        with torch.cuda.stream(stream):
+        with torch.cuda.stream(torch.cuda.current_stream(device) if stream is None else stream):
             ws = torch.empty(nbytes, dtype=torch.uint8, device=device)
         _ws_cache[key] = ws
     return ws, ws.numel()
