@@ -114,8 +114,7 @@ int run_cluster(const ga::Dims& d, const void* K, int32_t iters, const float* in
               "grouping launch");
     return GA_OK;
   }
-  // with the fused first round the assign launch forms the initial centroids itself
-  if (ga::fused_first_parts(d) == 0)
+  if (!ga::first_round_inits(d, init != nullptr))
     GA_LAUNCH(ga::launch_init(d, K, init, C, w.R, w.nrm64, w.nsplit, w.mcount, st), "init launch");
   const ga::FusedUpdate fu{w.Sp, w.cntp, w.pbits, init, C};
   for (int t = 0; t < iters; ++t) {

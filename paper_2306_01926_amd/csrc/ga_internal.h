@@ -90,13 +90,13 @@ hipError_t static_scratch(void** out);
 
 hipError_t launch_init(const Dims& d, const void* K, const float* init, float* C, void* R,
                        double* nrm64, uint16_t* nsplit, int32_t* mcount, hipStream_t st);
-// Partitions per slice of the first round's fused assign launch (which then
-// also does the init), 0 if that launch is not used for d.
-int fused_first_parts(const Dims& d);
+// Whether the first round's assign launch forms the initial centroids and
+// representatives itself (init: from given ones), without launch_init.
+bool first_round_inits(const Dims& d, bool init);
 // First round, bf16, N <= kFusedG and at most kFusedP workgroups per slice:
 // the assign launch also writes the partition sums of the round's update (fu)
 // and *parts is their number per slice, to be finished by launch_part_finish;
-// else *parts = 0 and the caller runs the update (fu unused).
+// else *parts = 0 and the caller runs the update.
 hipError_t launch_assign(const Dims& d, const void* K, const void* R, const uint16_t* nsplit,
                          const double* nrm64, float* knorm, int32_t* belong, int32_t* mcount,
                          unsigned long long* mrec, bool first, const FusedUpdate& fu, int* parts,

@@ -389,6 +389,101 @@ __device__ __forceinline__ double stage_init(const uint16_t* __restrict__ Kbh, c
   return fmax(fmax(red[0], red[1]), fmax(red[2], red[3]));
 }
 
+// The first round of k_assign_bf16<true, true>: stage_init for any N, 256 threads; the
+// |r|^2 of 32 groups at a time by eight lanes each (norm8), to nrm_l as well.
+__device__ __forceinline__ double stage_init_wide(const uint16_t* __restrict__ Kbh, const float* __restrict__ init_bh,
+                                                  int n, int N, int Npad, float* __restrict__ C_bh, uint16_t* Rs,
+                                                  uint16_t* Ns, double* nrm_l, double* red) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  constexpr int IT = 8;  // 256 rows a step, their loads in flight together
+  for (int i0 = tid; i0 < Npad * 8; i0 += 256 * IT) {
+    float4 a[IT], b[IT];
+    u32x4 w[IT];
+    if (init_bh) {
+#pragma unroll
+      for (int it = 0; it < IT; ++it) {
+        const int idx = i0 + it * 256, row = min(idx >> 3, N - 1), ch = idx & 7;
+        a[it] = *(const float4*)(init_bh + row * 64 + ch * 8);
+        b[it] = *(const float4*)(init_bh + row * 64 + ch * 8 + 4);
+      }
+#pragma unroll
+      for (int it = 0; it < IT; ++it)
+        w[it] = u32x4{f32_to_bf16(a[it].x) | (f32_to_bf16(a[it].y) << 16),
+                      f32_to_bf16(a[it].z) | (f32_to_bf16(a[it].w) << 16),
+                      f32_to_bf16(b[it].x) | (f32_to_bf16(b[it].y) << 16),
+                      f32_to_bf16(b[it].z) | (f32_to_bf16(b[it].w) << 16)};
+    } else {
+#pragma unroll
+      for (int it = 0; it < IT; ++it) {
+        const int idx = i0 + it * 256, row = min(idx >> 3, N - 1), ch = idx & 7;
+        w[it] = *(const u32x4*)(Kbh + ((int64_t)row * n / N) * 64 + ch * 8);
+      }
+#pragma unroll
+      for (int it = 0; it < IT; ++it) {
+        a[it] = float4{bf16_to_f32(w[it][0] & 0xffffu), bf16_to_f32(w[it][0] >> 16), bf16_to_f32(w[it][1] & 0xffffu),
+                       bf16_to_f32(w[it][1] >> 16)};
+        b[it] = float4{bf16_to_f32(w[it][2] & 0xffffu), bf16_to_f32(w[it][2] >> 16), bf16_to_f32(w[it][3] & 0xffffu),
+                       bf16_to_f32(w[it][3] >> 16)};
+      }
+    }
+#pragma unroll
+    for (int it = 0; it < IT; ++it) {
+      const int idx = i0 + it * 256, row = idx >> 3, ch = idx & 7;
+      if (row >= Npad) break;
+      u32x4 v = {0u, 0u, 0u, 0u};
+      if (row < N) {
+        if (C_bh) {
+          *(float4*)(C_bh + row * 64 + ch * 8) = a[it];
+          *(float4*)(C_bh + row * 64 + ch * 8 + 4) = b[it];
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const uint32_t lo = __float_as_uint(bf16_to_f32(w[it][e] & 0xffffu) * -2.0f) >> 16;
+          const uint32_t hi = __float_as_uint(bf16_to_f32(w[it][e] >> 16) * -2.0f) >> 16;
+          v[e] = lo | (hi << 16);
+        }
+      }
+      *(u32x4*)(Rs + swz(row, ch)) = v;
+    }
+  }
+  __syncthreads();
+  double mx = 0.0;
+  for (int g0 = 0; g0 < Npad; g0 += 32) {
+    const int g = g0 + (tid >> 3), j = tid & 7;
+    const u32x4 v = *(const u32x4*)(Rs + swz(g, j));
+    double rc[8], nrm;
+#pragma unroll
+    for (int e = 0; e < 8; ++e)
+      rc[e] = (double)(-0.5f * bf16_to_f32((e & 1) ? (v[e >> 1] >> 16) : (v[e >> 1] & 0xffffu)));
+    const bool exact = norm8(rc, nrm);
+    if (j != 0) continue;
+    if (!exact) {  // the chain itself
+      nrm = 0.0;
+#pragma unroll
+      for (int c = 0; c < 8; ++c) {
+        const u32x4 x = *(const u32x4*)(Rs + swz(g, c));
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          const double r = (double)(-0.5f * bf16_to_f32((e & 1) ? (x[e >> 1] >> 16) : (x[e >> 1] & 0xffffu)));
+          nrm = fma(r, r, nrm);
+        }
+      }
+    }
+    if (g < N) {
+      write_nsplit(nrm, Ns + g * 8);
+      mx = fmax(mx, nrm);
+    } else {
+      *(u32x4*)(Ns + g * 8) = u32x4{0x7f7fu, 0u, 0u, 0u};
+    }
+    nrm_l[g] = nrm;
+  }
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1) mx = fmax(mx, __shfl_xor(mx, off));
+  if (lane == 0) red[wave] = mx;
+  __syncthreads();
+  return fmax(fmax(red[0], red[1]), fmax(red[2], red[3]));
+}
+
 // Dynamic LDS of the assign kernels: region A = -2R as [Npad][64] bf16
 // (swizzled), the |r|^2 split as [Npad][8] bf16 and the uncertain queue
 // (4 tpw 32 words), then three arrays of 4 tpw 32 words: moved records, staged
@@ -401,6 +496,11 @@ __host__ __device__ constexpr int fused_words(int Npad, int cap4) { return (cap4
 __host__ __device__ constexpr int fused_bytes(int Npad, int cap4) { return fused_words(Npad, cap4) * 4 + 4 * 4096; }
 __host__ __device__ constexpr int assign_region_a(int Npad, int cap4, bool fused) {
   return fused && fused_bytes(Npad, cap4) > Npad * 144 + cap4 * 4 ? fused_bytes(Npad, cap4) : Npad * 144 + cap4 * 4;
+}
+
+// k_assign_bf16's first round keeps |r|^2 [Npad] in fp64 after those.
+__host__ __device__ constexpr int assign_nrm_at(int Npad, int tpw) {
+  return (assign_region_a(Npad, 4 * tpw * 32, false) + 3 * 4 * tpw * 32 * 4 + 15) & ~15;
 }
 
 struct AssignLds {
@@ -738,12 +838,12 @@ __global__ __launch_bounds__(256) void k_part_finish(const double* __restrict__ 
 // against 512 groups 38.5 -> 36 us.  (k_assign_reg and the one-launch grouping
 // keep the chain: there the class minima spill at 128 groups, and the key
 // stream, not the VALU, bounds the loop.)
-template <bool FIRST>
+template <bool FIRST, bool INIT>
 __global__ __launch_bounds__(256) void k_assign_bf16(
     const uint16_t* __restrict__ K, const uint16_t* __restrict__ R, const uint16_t* __restrict__ nsplit,
     const double* __restrict__ nrm64, float* __restrict__ knorm, int32_t* __restrict__ belong,
     int32_t* __restrict__ mcount, unsigned long long* __restrict__ mrec, int n, int N, int tpw, float cm,
-    float cp, FusedUpdate) {
+    float cp, FusedUpdate fu) {
   extern __shared__ __align__(16) unsigned char smem[];
   __shared__ double red[4];
   __shared__ AssignCounts cnt;
@@ -788,8 +888,22 @@ __global__ __launch_bounds__(256) void k_assign_bf16(
     fetch(0, kf[0], kn[0], old[0]);
     fetch(1, kf[1], kn[1], old[1]);
   }
-  const double nmax = stage_reps<0>(R + bh * (int64_t)N * 64, nsplit + bh * N * 8, nrm64 + bh * N, N, Npad, L.Rs,
-                                    L.Ns, red);
+  // INIT (first round): the initial representatives from the keys or the given init, without
+  // a launch of their own; workgroup 0 of the slice writes C and clears the
+  // moved-key counters of the next rounds
+  double* nrm_l = (double*)(smem + assign_nrm_at(Npad, tpw));
+  double nmax;
+  if (INIT) {
+    if (blockIdx.x == 0 && tid == 0) {
+      mcount[bh] = 0;
+      mcount[gridDim.y + bh] = 0;
+    }
+    nmax = stage_init_wide(Kbh, fu.init ? fu.init + bh * (int64_t)N * 64 : nullptr, n, N, Npad,
+                           blockIdx.x == 0 ? fu.C + bh * (int64_t)N * 64 : nullptr, L.Rs, L.Ns, nrm_l, red);
+  } else {
+    nmax = stage_reps<0>(R + bh * (int64_t)N * 64, nsplit + bh * N * 8, nrm64 + bh * N, N, Npad, L.Rs, L.Ns, red);
+  }
+  const double* nrm_x = INIT ? (const double*)nrm_l : nrm64 + bh * N;  // |r|^2 for the exact decisions
   const float nmaxf = (float)nmax * (1.0f + 0x1p-20f);
   const float rmaxf = sqrtf(nmaxf) * (1.0f + 0x1p-20f);
   const Certify cf = {nmaxf, rmaxf, cm, cp};
@@ -872,7 +986,7 @@ __global__ __launch_bounds__(256) void k_assign_bf16(
     cnt.wcnt[wv] = wn;
     cnt.ucnt[wv] = un;
   }
-  assign_epilogue<FIRST, false, 1>(Kbh, key0, tpw, Rs, nrm64 + bh * N, n, N, belong_bh, knorm + bh * n, mcount + bh,
+  assign_epilogue<FIRST, false, 1>(Kbh, key0, tpw, Rs, nrm_x, n, N, belong_bh, knorm + bh * n, mcount + bh,
                                    mrec + bh * n, kd[wave], L.lists);
 }
 
@@ -1764,8 +1878,9 @@ __global__ __launch_bounds__(256) void k_attend_bf16(const uint16_t* __restrict_
 
 constexpr size_t kAssignLdsMax = 160 * 1024 - 3 * 1024;  // dynamic LDS budget (static arrays use the rest)
 
-size_t assign_lds(int N, int tpw = 12, bool fused = false) {  // see assign_lds_layout
+size_t assign_lds(int N, int tpw = 12, bool fused = false, bool wide_first = false) {  // see assign_lds_layout
   const int Npad = (N + 31) & ~31, cap4 = 4 * tpw * 32;
+  if (wide_first) return (size_t)assign_nrm_at(Npad, tpw) + (size_t)Npad * 8;
   return (size_t)assign_region_a(Npad, cap4, fused) + (size_t)3 * cap4 * 4;
 }
 size_t attend_lds(int N) {
@@ -1779,10 +1894,9 @@ size_t attend_lds(int N) {
 void set_lds_limits() {
   static std::once_flag once;
   std::call_once(once, [] {
-    (void)hipFuncSetAttribute((const void*)k_assign_bf16<true>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                              (int)kAssignLdsMax);
-    (void)hipFuncSetAttribute((const void*)k_assign_bf16<false>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                              (int)kAssignLdsMax);
+    for (const void* f : {(const void*)k_assign_bf16<true, true>, (const void*)k_assign_bf16<true, false>,
+                          (const void*)k_assign_bf16<false, false>})
+      (void)hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kAssignLdsMax);
     for (const void* f : {(const void*)k_attend_bf16<1>, (const void*)k_attend_bf16<2>, (const void*)k_attend_bf16<3>,
                           (const void*)k_attend_bf16<4>, (const void*)k_attend_bf16<5>, (const void*)k_attend_bf16<6>,
                           (const void*)k_attend_bf16<7>, (const void*)k_attend_bf16<8>})
@@ -1913,13 +2027,14 @@ using AssignFn = void (*)(const uint16_t*, const uint16_t*, const uint16_t*, con
 struct AssignPlan {
   AssignFn kern;
   int64_t tpw, parts;
-  bool fused;
+  bool fused;  // first round with partition sums (N <= kFusedG)
+  bool wide;   // first round for N > kFusedG with the initial representatives
 };
 
 // bf16 kernel choice and grid: one round of resident workgroups, the same
 // number per slice, at most 16 tiles per wave (the LDS lists grow with tpw;
 // the occupancy is taken at 16).
-static AssignPlan plan_assign(const Dims& d, bool first) {
+static AssignPlan plan_assign(const Dims& d, bool first, bool init) {
   const int64_t tiles = (d.n + 31) / 32;
   const int Npad = (d.N + 31) & ~31;
   // Npad <= 128: the register-resident kernel, one instantiation per block
@@ -1933,20 +2048,29 @@ static AssignPlan plan_assign(const Dims& d, bool first) {
        k_assign_reg<true, 4, true>}};
   const bool small = Npad <= kFusedG;
   AssignPlan p;
-  p.kern = small ? reg[first][(Npad >> 5) - 1] : (first ? k_assign_bf16<true> : k_assign_bf16<false>);
+  // For N > kFusedG the first round also forms the initial representatives where
+  // staging them from the keys (or the given fp32 init, twice the bytes) in every
+  // workgroup costs less than a launch of its own: cluster calls of 16 slices of
+  // 10000 keys, 384 groups 198 -> 194 us, 512 222 -> 219, but 1024 groups (16
+  // slices of 3000) 194 -> 212 and 512 with an init 214 -> 217.
+  p.wide = first && !small && Npad * (init ? 2 : 1) <= 512;
+  p.kern = small    ? reg[first][(Npad >> 5) - 1]
+           : p.wide ? k_assign_bf16<true, true>
+           : first  ? k_assign_bf16<true, false>
+                    : k_assign_bf16<false, false>;
   int64_t tpw = 16;
-  while (tpw > 1 && assign_lds(d.N, (int)tpw) > kAssignLdsMax) --tpw;
-  p.tpw = tiles_per_wave(tiles, d.BH, resident_wgs((const void*)p.kern, assign_lds(d.N, (int)tpw)), tpw);
+  while (tpw > 1 && assign_lds(d.N, (int)tpw, false, p.wide) > kAssignLdsMax) --tpw;
+  p.tpw = tiles_per_wave(tiles, d.BH, resident_wgs((const void*)p.kern, assign_lds(d.N, (int)tpw, false, p.wide)), tpw);
   p.parts = cdiv(tiles, 4 * p.tpw);
   p.fused = first && small && p.parts <= kFusedP;
   if (p.fused) p.kern = reg[2][(Npad >> 5) - 1];
   return p;
 }
 
-int fused_first_parts(const Dims& d) {
-  if (d.dtype != 1) return 0;
-  const AssignPlan p = plan_assign(d, true);
-  return p.fused ? (int)p.parts : 0;
+bool first_round_inits(const Dims& d, bool init) {
+  if (d.dtype != 1) return false;
+  const AssignPlan p = plan_assign(d, true, init);
+  return p.fused || p.wide;
 }
 
 hipError_t launch_assign(const Dims& d, const void* K, const void* R, const uint16_t* nsplit,
@@ -1964,10 +2088,10 @@ hipError_t launch_assign(const Dims& d, const void* K, const void* R, const uint
   // < 2^(4 - 23) of its magnitude.
   const float cm = (float)(kD + 4) * 0x1p-23f * (1.0f + 0x1p-10f) * cert_widen();
   const float cp = 0x1p-19f * (1.0f + 0x1p-10f) * cert_widen();
-  const AssignPlan p = plan_assign(d, first);
+  const AssignPlan p = plan_assign(d, first, fu.init != nullptr);
   if (p.fused) *parts_out = (int)p.parts;
   const dim3 grid((unsigned)p.parts, (unsigned)d.BH), block(256);
-  const size_t lds = assign_lds(d.N, (int)p.tpw, p.fused);
+  const size_t lds = assign_lds(d.N, (int)p.tpw, p.fused, p.wide);
   hipLaunchKernelGGL(p.kern, grid, block, lds, st, (const uint16_t*)K, (const uint16_t*)R, nsplit, nrm64, knorm,
                      belong, mcount, mrec, d.n, d.N, (int)p.tpw, cm, cp, fu);
   return hipGetLastError();

@@ -69,3 +69,23 @@ def test_forward_split(oracle_mod, dev, case):
     # 2e-2 per row: the documented bound of the bf16 attention
     err = np.linalg.norm(O.float().cpu().numpy() - ref["O"], axis=-1)
     assert (err <= 2e-2 * np.linalg.norm(ref["O"], axis=-1)).all()
+
+
+@pytest.mark.parametrize("N,init,launch", [(129, False, False), (512, False, False), (513, False, True),
+                                           (256, True, False), (257, True, True), (1024, True, True)])
+def test_cluster_initial_representatives(oracle_mod, dev, N, init, launch):
+    """More than 128 groups: the first round forms the initial representatives
+    itself up to 512 groups (256 with a caller's init), else a launch of its own
+    does; a group that no key joins keeps its initial centroid."""
+    print(f"\n[case] initial representatives {N} {init}", flush=True)
+    _, K, _ = inputs.make_qkv(1, 2, 1100, 64, "bf16", N, 200, 0.05, 0.3)
+    K[:, :, 1::2] = K[:, :, ::2]  # pairs of equal keys: the second one's group stays empty
+    ini = None
+    if init:
+        ini = torch.from_numpy(np.random.default_rng(N).standard_normal((1, 2, N, 64)).astype(np.float32) * 0.2)
+    (bel, cnt, cen), names = launches(lambda: ga.cluster(K.to(dev), N, 2, init=None if ini is None else ini.to(dev)))
+    ref = oracle_mod.cluster(inputs.as_float64(K), N, 2, "bf16", init=None if ini is None else ini.numpy())
+    assert np.array_equal(bel.cpu().numpy(), ref["belong"])
+    assert np.array_equal(cnt.cpu().numpy(), ref["count"])
+    assert np.array_equal(cen.cpu().numpy().view(np.uint32), ref["centroid"].view(np.uint32))
+    assert ("init" in names) == launch, sorted(names)
