@@ -1200,8 +1200,7 @@ __device__ __forceinline__ void run_sums(const uint32_t* ent, const uint8_t* eg,
 //   MODE 3 (value sums for the attention): the bf16 value means, transposed,
 //           and the log2(count) score bias, as k_attend_prep forms them
 // MODE 0 then sets C = (float)(S / count) (an empty group keeps C), R =
-// bf16(C), the canonical fp64 |r|^2 (fma chain over c = 0..63, one lane per
-// group) and its split.  (The later rounds' update is k_gdelta.)  With Z > 1
+// bf16(C), the canonical fp64 |r|^2 and its split (store_norms).  (The later rounds' update is k_gdelta.)  With Z > 1
 // every workgroup writes its partial fp64 sums (and MODE 0's counts) and
 // k_gsum_finish adds the Z parts: the sums are exact, so the split cannot
 // change a bit.
