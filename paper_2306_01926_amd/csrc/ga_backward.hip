@@ -28,8 +28,8 @@
 //   k_bwd_prep    per slice: R = bf16(centroid) rows and transposed, bf16
 //                 value means, log2(count) (-inf for an empty group)
 //   k_bwd_query   per 32-query tile (lane = query): the query side as above
-//                 in two passes over the 32-group blocks (shift, sum and D;
-//                 dp and dQ), recomputing the block's MFMAs; stores each
+//                 in three passes over the 32-group blocks (shift; sum and
+//                 D; dp and dQ), recomputing the block's MFMAs; stores each
 //                 query's softmax shift plus log2 of its sum (so that a
 //                 weight is one exp2) and D
 //   k_bwd_group   per (32-group block, query chunk): the same scores and dw
@@ -176,10 +176,12 @@ __device__ __forceinline__ void load_row_frags(const uint16_t* __restrict__ X, i
 
 // grid (ceil(tiles / (nw tpw)), BH), kBqW waves, of which the first nw have
 // wave tiles of 32 queries (all of them stage).
-// The staged group rows (111 KB at 224 groups) leave room for one workgroup per
-// compute unit, so it has eight waves, two per SIMD, and the launch is one round
-// of workgroups: with four waves and two rounds 46 us at 24 slices of 3333
-// queries and 200 groups.
+// The staged group rows (92 KB at 224 groups, 128 KB with the waves' output
+// tiles) leave room for one workgroup per compute unit, so it has eight waves, two
+// per SIMD, and the launch is one round of workgroups: whole backward of 24 slices
+// of 3333 queries and 200 groups 89 us with four waves and two rounds, 76 with
+// eight.  The shift and the sums in one pass, the sums rescaled where the shift
+// grows, takes 73 us there but rounds the sums differently.
 constexpr int kBqW = 8;
 template <int NB>
 __global__ __launch_bounds__(64 * kBqW) void k_bwd_query(const uint16_t* __restrict__ Q, const uint16_t* __restrict__ G,
@@ -254,38 +256,32 @@ __global__ __launch_bounds__(64 * kBqW) void k_bwd_query(const uint16_t* __restr
     };
     float Ms_, inv, Dq, Lq;  // Lq: the shift plus log2 of the sum (+inf if every group is empty)
     {
-      // more groups than fit in registers: two passes over the blocks (shift,
-      // sum and D, the sums rescaled when a lane's shift grows; dp and dQ), the
-      // MFMAs recomputed in the second
-      float M = -INFINITY, S = 0.f, SD = 0.f;  // over this lane's half of the groups
+      // more groups than fit in registers: three passes over the blocks
+      // (shift; sum and D; dp and dQ), the MFMAs recomputed in each
+      float M = -INFINITY;
 #pragma unroll 1
       for (int b = 0; b < NB; ++b) {
         f32x16 a, d;
         block_mfma(b, a, d);
-        float x[16], Mn = M;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) M = fmaxf(M, fmaf(a[v], sl2e, lc[32 * b + 8 * (v >> 2) + 4 * h + (v & 3)]));
+      }
+      M = fmaxf(M, __shfl_xor(M, 32));
+      const bool any = M != -INFINITY;
+      Ms_ = any ? M : 0.f;
+      float S = 0.f, SD = 0.f;
+#pragma unroll 1
+      for (int b = 0; b < NB; ++b) {
+        f32x16 a, d;
+        block_mfma(b, a, d);
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
-          x[v] = fmaf(a[v], sl2e, lc[32 * b + 8 * (v >> 2) + 4 * h + (v & 3)]);
-          Mn = fmaxf(Mn, x[v]);
-        }
-        const float ref = Mn == -INFINITY ? 0.f : Mn;  // no group so far: every term below is 0
-        const float alpha = __builtin_amdgcn_exp2f(M - ref);
-        S *= alpha;
-        SD *= alpha;
-        M = Mn;
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          const float e = __builtin_amdgcn_exp2f(x[v] - ref);
+          const float e =
+              __builtin_amdgcn_exp2f(fmaf(a[v], sl2e, lc[32 * b + 8 * (v >> 2) + 4 * h + (v & 3)]) - Ms_);
           S += e;
           SD = fmaf(e, d[v], SD);
         }
       }
-      const float Mo = fmaxf(M, __shfl_xor(M, 32));
-      const bool any = Mo != -INFINITY;
-      Ms_ = any ? Mo : 0.f;
-      const float beta = __builtin_amdgcn_exp2f(M - Ms_);
-      S *= beta;
-      SD *= beta;
       S += __shfl_xor(S, 32);
       SD += __shfl_xor(SD, 32);
       inv = any ? 1.0f / S : 0.f;
