@@ -29,7 +29,7 @@
 //                 value means, log2(count) (-inf for an empty group)
 //   k_bwd_query   per 32-query tile (lane = query): the query side as above
 //                 in three passes over the 32-group blocks (shift; sum and
-//                 D; dp and dQ), recomputing the block's MFMAs; stores each
+//                 D; dp and dQ), the products kept or formed again; stores each
 //                 query's softmax shift plus log2 of its sum (so that a
 //                 weight is one exp2) and D
 //   k_bwd_group   per (32-group block, query chunk): the same scores and dw
@@ -174,48 +174,59 @@ __device__ __forceinline__ void load_row_frags(const uint16_t* __restrict__ X, i
   for (int s = 0; s < 4; ++s) f[s] = *(const u32x4*)(X + row * 64 + 32 * h + 8 * s);
 }
 
-// grid (ceil(tiles / (nw tpw)), BH), kBqW waves, of which the first nw have
-// wave tiles of 32 queries (all of them stage).
-// The staged group rows (92 KB at 224 groups, 128 KB with the waves' output
-// tiles) leave room for one workgroup per compute unit, so it has eight waves, two
-// per SIMD, and the launch is one round of workgroups: whole backward of 24 slices
-// of 3333 queries and 200 groups 89 us with four waves and two rounds, 76 with
-// eight.  The shift and the sums in one pass, the sums rescaled where the shift
-// grows, takes 73 us there but rounds the sums differently.
-constexpr int kBqW = 8;
+// grid (ceil(tiles / per), BH), bq_waves(NB) waves: a workgroup's tiles (32
+// queries each) are per consecutive ones of the slice, dealt to its waves in turn.
+//
+// The staged group rows (128 KB with the waves' output tiles at 224 groups and
+// eight waves) leave room for one workgroup per compute unit.  Up to 192 groups
+// one wave per SIMD: its 512 registers hold the products of every block through
+// all three unrolled passes.  Beyond that they do not, and two waves per SIMD
+// that form the products again in each pass hide each other's waits.  Whole
+// backward, us, one wave : two: 320 slices of 2000 queries and 180 groups 319 : 343,
+// 24 of 3333 and 180 67 : 68, 24 of 3333 and 256 84 : 80, 86 of 5000 and 256
+// 289 : 275.  The shift and the sums in one pass, the sums rescaled where the
+// shift grows, takes up to 5% less beyond 192 groups but rounds the sums
+// differently.
+constexpr bool bq_keeps(int NB) { return NB <= 6; }
+constexpr int bq_waves(int NB) { return bq_keeps(NB) ? 4 : 8; }
 template <int NB>
-__global__ __launch_bounds__(64 * kBqW) void k_bwd_query(const uint16_t* __restrict__ Q, const uint16_t* __restrict__ G,
-                                                   const uint16_t* __restrict__ R, const uint16_t* __restrict__ RT,
-                                                   const uint16_t* __restrict__ MU, const float* __restrict__ LC,
-                                                   int n, int rts, float scale, float sl2e, int nw, int tpw,
-                                                   uint16_t* __restrict__ dQ, float2* __restrict__ stats) {
+__global__ __launch_bounds__(64 * bq_waves(NB)) void k_bwd_query(const uint16_t* __restrict__ Q,
+                                                                 const uint16_t* __restrict__ G,
+                                                                 const uint16_t* __restrict__ R,
+                                                                 const uint16_t* __restrict__ RT,
+                                                                 const uint16_t* __restrict__ MU,
+                                                                 const float* __restrict__ LC, int n, int rts,
+                                                                 float scale, float sl2e, int per,
+                                                                 uint16_t* __restrict__ dQ,
+                                                                 float2* __restrict__ stats) {
+  constexpr int W = bq_waves(NB), kUnroll = bq_keeps(NB) ? NB : 1;
   constexpr int Npad = NB * 32;
   __shared__ __attribute__((aligned(16))) uint16_t Rs[Npad * kBs];
   __shared__ __attribute__((aligned(16))) uint16_t Ms[Npad * kBs];
   __shared__ __attribute__((aligned(16))) uint16_t RTs[64 * (Npad + 4)];
   __shared__ float lc[Npad];
-  __shared__ __attribute__((aligned(16))) uint16_t Ot[kBqW][32 * kBs];
+  __shared__ __attribute__((aligned(16))) uint16_t Ot[W][32 * kBs];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, h = lane >> 5, q = lane & 31;
   const int64_t bh = blockIdx.y;
-  stage_groups<NB, 64 * kBqW>(R, MU, LC, bh, Rs, Ms, lc);
-  for (int x = tid; x < 64 * (Npad / 4); x += 64 * kBqW) {
+  stage_groups<NB, 64 * W>(R, MU, LC, bh, Rs, Ms, lc);
+  for (int x = tid; x < 64 * (Npad / 4); x += 64 * W) {
     const int row = x / (Npad / 4), ch = x % (Npad / 4);
     *(u32x2*)(RTs + row * (Npad + 4) + 4 * ch) = *(const u32x2*)(RT + (bh * 64 + row) * rts + 4 * ch);
   }
   __syncthreads();
   const int64_t ntiles = ((int64_t)n + 31) / 32;
-  if (wave >= nw) return;  // (no barrier below)
-  const int64_t t0 = ((int64_t)blockIdx.x * nw + wave) * tpw;
+  const int64_t first = (int64_t)blockIdx.x * per, t0 = first + wave;
   const uint16_t* Qb = Q + bh * (int64_t)n * 64;
   const uint16_t* Gb = G + bh * (int64_t)n * 64;
   uint16_t* Ow = Ot[wave];
-  const int64_t tend = min(t0 + tpw, ntiles);
+  const int64_t tend = min(first + per, ntiles);
+  if (t0 >= tend) return;  // (no barrier below)
   // the next tile's rows load while the current tile is processed
   // (unconditional, rows clamped, so the loads stay ahead of the tile's work)
   u32x4 qn[4], gn[4];
   load_row_frags(Qb, min(t0 * 32 + q, (int64_t)n - 1), qn);
   load_row_frags(Gb, min(t0 * 32 + q, (int64_t)n - 1), gn);
-  for (int64_t t = t0; t < tend; ++t) {
+  for (int64_t t = t0; t < tend; t += W) {
     const int64_t qi = t * 32 + q;
     u32x4 qf[4], gf[4];
 #pragma unroll
@@ -223,8 +234,8 @@ __global__ __launch_bounds__(64 * kBqW) void k_bwd_query(const uint16_t* __restr
       qf[s] = qn[s];
       gf[s] = gn[s];
     }
-    load_row_frags(Qb, min(qi + 32, (int64_t)n - 1), qn);
-    load_row_frags(Gb, min(qi + 32, (int64_t)n - 1), gn);
+    load_row_frags(Qb, min(qi + 32 * W, (int64_t)n - 1), qn);
+    load_row_frags(Gb, min(qi + 32 * W, (int64_t)n - 1), gn);
     __builtin_amdgcn_sched_barrier(0);
     // block b's scores r_g . q and dw_gq = mu_g . G_q (rows g, column q)
     auto block_mfma = [&](int b, f32x16& a, f32x16& d) __attribute__((always_inline)) {
@@ -256,10 +267,9 @@ __global__ __launch_bounds__(64 * kBqW) void k_bwd_query(const uint16_t* __restr
     };
     float Ms_, inv, Dq, Lq;  // Lq: the shift plus log2 of the sum (+inf if every group is empty)
     {
-      // more groups than fit in registers: three passes over the blocks
-      // (shift; sum and D; dp and dQ), the MFMAs recomputed in each
+      // three passes over the blocks: shift; sum and D; dp and dQ
       float M = -INFINITY;
-#pragma unroll 1
+#pragma unroll kUnroll
       for (int b = 0; b < NB; ++b) {
         f32x16 a, d;
         block_mfma(b, a, d);
@@ -270,7 +280,7 @@ __global__ __launch_bounds__(64 * kBqW) void k_bwd_query(const uint16_t* __restr
       const bool any = M != -INFINITY;
       Ms_ = any ? M : 0.f;
       float S = 0.f, SD = 0.f;
-#pragma unroll 1
+#pragma unroll kUnroll
       for (int b = 0; b < NB; ++b) {
         f32x16 a, d;
         block_mfma(b, a, d);
@@ -287,7 +297,7 @@ __global__ __launch_bounds__(64 * kBqW) void k_bwd_query(const uint16_t* __restr
       inv = any ? 1.0f / S : 0.f;
       Lq = any ? Ms_ + log2f(S) : INFINITY;
       Dq = SD * inv;
-#pragma unroll 1
+#pragma unroll kUnroll
       for (int b = 0; b < NB; ++b) {
         f32x16 a, d;
         block_mfma(b, a, d);
@@ -898,6 +908,29 @@ size_t backward_workspace_layout(const Dims& d, BackwardWorkspace* w, void* base
   return off;
 }
 
+// Query tiles per workgroup of k_bwd_query (one workgroup per compute unit at a
+// time): the fewest workgroups per slice that fill one round of 256 or, if
+// cheaper by this count, up to seven more in several rounds: a round costs its
+// workgroup's tiles per SIMD and the staging, which takes about as long as kStage
+// tiles (1 and 2 within a percent of each other, 5 up to 4% slower).  Whole
+// backward of 320 slices of 4000 queries and 140 groups 657 us with one workgroup
+// per slice, its second round a quarter full, 593 with four (both with two waves
+// per SIMD); 160 slices of 4000 and 200 groups 421 -> 391.
+static int64_t bwd_query_tiles(int64_t ntiles, int64_t BH) {
+  constexpr int64_t kStage = 2;
+  const int64_t p0 = 256 / BH > 1 ? 256 / BH : 1;
+  int64_t best = 0, least = 0;
+  for (int64_t p = p0; p < p0 + 8; ++p) {
+    const int64_t even = (ntiles + p - 1) / p, per = even > 4 ? even : 4;
+    const int64_t rounds = ((ntiles + per - 1) / per * BH + 255) / 256, cost = rounds * ((per + 3) / 4 + kStage);
+    if (best == 0 || cost < least) {
+      best = per;
+      least = cost;
+    }
+  }
+  return best;
+}
+
 hipError_t launch_backward(const Dims& d, const void* Q, const void* dO, const int32_t* belong,
                            const float* centroid, const int32_t* count, const float* vsum, float scale, void* dQ,
                            void* dK, void* dV, const BackwardWorkspace& w, hipStream_t st) {
@@ -935,17 +968,13 @@ hipError_t launch_backward(const Dims& d, const void* Q, const void* dO, const i
                        Npad, rts, w.R, w.RT, w.MU, w.LC);
   }
   const int64_t ntiles = ((int64_t)d.n + 31) / 32;
-  // at most one round of 256 workgroups (one per compute unit), the same number
-  // per slice; where four waves of one tile each are enough for that, four
-  const int64_t per_slice = 256 / d.BH > 1 ? 256 / d.BH : 1;
-  const int nw = ntiles <= 4 * per_slice ? 4 : kBqW;
-  const int tpw = (int)((ntiles + nw * per_slice - 1) / (nw * per_slice));
-  const unsigned gq = (unsigned)((ntiles + nw * tpw - 1) / (nw * tpw));
+  const int64_t per = bwd_query_tiles(ntiles, d.BH);
+  const unsigned gq = (unsigned)((ntiles + per - 1) / per);
   {
     TimedLaunch tl("bwd_query", st);
 #define GA_BWD_Q(NBV)                                                                                              \
-  hipLaunchKernelGGL(k_bwd_query<NBV>, dim3(gq, (unsigned)d.BH), dim3(64 * kBqW), 0, st, (const uint16_t*)Q,            \
-                     (const uint16_t*)dO, w.R, w.RT, w.MU, w.LC, d.n, rts, scale, sl2e, nw, tpw, (uint16_t*)dQ,       \
+  hipLaunchKernelGGL(k_bwd_query<NBV>, dim3(gq, (unsigned)d.BH), dim3(64 * bq_waves(NBV)), 0, st, (const uint16_t*)Q,   \
+                     (const uint16_t*)dO, w.R, w.RT, w.MU, w.LC, d.n, rts, scale, sl2e, (int)per, (uint16_t*)dQ,  \
                      (float2*)w.stats)
     switch (NB) {
       case 5: GA_BWD_Q(5); break;

@@ -17,8 +17,10 @@ CASES = [
     (1, 1, 130, 129, 0.125, (0, 0), 1.0),    # one group in the last block, two keys in the last tile
     (1, 2, 500, 160, 0.5, (0, 40), 1.6),     # the first block and part of the second empty, shifts grow
     (1, 1, 500, 224, 0.5, (180, 224), 0.6),  # the last block empty, shifts fall
-    (1, 1, 33000, 130, 0.125, (3, 9), 1.0),  # eight waves of one tile
-    (30, 10, 600, 130, -0.2, (0, 32), 1.2),  # one workgroup per slice, three tiles per wave
+    (1, 1, 33000, 130, 0.125, (3, 9), 1.0),  # five tiles for four waves
+    (30, 10, 600, 130, -0.2, (0, 32), 1.2),  # more slices than compute units
+    (30, 10, 1250, 130, 0.2, (0, 32), 1.0),  # and two workgroups of 20 tiles for each
+    (20, 7, 650, 222, 0.125, (3, 9), 1.0),   # 21 tiles for eight waves
 ]
 
 
