@@ -235,6 +235,12 @@ __device__ __forceinline__ void exact_decide_queue(const uint16_t* __restrict__ 
   }
 }
 
+// The larger of two |r|^2, NaN if either is: with a NaN or an infinity the error
+// bound of the certified decisions is no finite number, so that every key of the
+// slice goes to the exact decision, where such a group never wins.  (The class
+// minima of k_assign_bf16 pass a NaN score on and cannot be ranked.)
+__device__ __forceinline__ double norm_max(double a, double b) { return a > b || a != a ? a : b; }
+
 // Stage -2R (swizzled, see swz) and the |r|^2 split of one slice into LDS and
 // return the slice's largest canonical |r|^2.  Padded groups (j >= N) get
 // zero rows and the largest bf16 as |r|^2, so they never win.  Every thread
@@ -303,13 +309,13 @@ __device__ __forceinline__ double stage_reps(const uint16_t* __restrict__ Rbh, c
   for (int jj = tid + 256; jj < Npad; jj += 256) {
     const u32x4 sp2 = jj < N ? *(const u32x4*)(nsplit_bh + jj * 8) : u32x4{0x7f7fu, 0u, 0u, 0u};
     *(u32x4*)(Ns + jj * 8) = sp2;
-    if (jj < N) mx = fmax(mx, nrm_bh[jj]);
+    if (jj < N) mx = norm_max(mx, nrm_bh[jj]);
   }
 #pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) mx = fmax(mx, __shfl_xor(mx, off));
+  for (int off = 32; off >= 1; off >>= 1) mx = norm_max(mx, __shfl_xor(mx, off));
   if (lane == 0) red[wave] = mx;
   __syncthreads();
-  return fmax(fmax(red[0], red[1]), fmax(red[2], red[3]));
+  return norm_max(norm_max(red[0], red[1]), norm_max(red[2], red[3]));
 }
 
 // First round with partition sums: the initial representatives straight from
@@ -383,10 +389,10 @@ __device__ __forceinline__ double stage_init(const uint16_t* __restrict__ Kbh, c
     nrm_l[j] = nrm;
   }
 #pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) mx = fmax(mx, __shfl_xor(mx, off));
+  for (int off = 32; off >= 1; off >>= 1) mx = norm_max(mx, __shfl_xor(mx, off));
   if (lane == 0) red[wave] = mx;
   __syncthreads();
-  return fmax(fmax(red[0], red[1]), fmax(red[2], red[3]));
+  return norm_max(norm_max(red[0], red[1]), norm_max(red[2], red[3]));
 }
 
 // The first round of k_assign_bf16<true, true>: stage_init for any N, 256 threads; the
@@ -471,17 +477,17 @@ __device__ __forceinline__ double stage_init_wide(const uint16_t* __restrict__ K
     }
     if (g < N) {
       write_nsplit(nrm, Ns + g * 8);
-      mx = fmax(mx, nrm);
+      mx = norm_max(mx, nrm);
     } else {
       *(u32x4*)(Ns + g * 8) = u32x4{0x7f7fu, 0u, 0u, 0u};
     }
     nrm_l[g] = nrm;
   }
 #pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) mx = fmax(mx, __shfl_xor(mx, off));
+  for (int off = 32; off >= 1; off >>= 1) mx = norm_max(mx, __shfl_xor(mx, off));
   if (lane == 0) red[wave] = mx;
   __syncthreads();
-  return fmax(fmax(red[0], red[1]), fmax(red[2], red[3]));
+  return norm_max(norm_max(red[0], red[1]), norm_max(red[2], red[3]));
 }
 
 // Dynamic LDS of the assign kernels: region A = -2R as [Npad][64] bf16

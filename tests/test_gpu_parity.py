@@ -447,3 +447,29 @@ def test_full_size_n20000_varying_groups(oracle_mod, dev):
         N = inputs.draw_group_count(w, 0, call)
         say(f"full size {w.name}, call {call}, N={N}")
         _sampled_full_size(oracle_mod, dev, w, call, N, [(0, 0), (3, 7)], queries=256)
+
+
+@pytest.mark.parametrize("bad", [float("nan"), float("inf")], ids=["nan", "inf"])
+@pytest.mark.parametrize("dtype,N,rounds", [("bf16", 100, False), ("bf16", 100, True), ("bf16", 129, False),
+                                            ("bf16", 200, False), ("bf16", 400, False), ("bf16", 1000, False),
+                                            ("f32", 100, False), ("f32", 300, False)])
+def test_non_finite_representatives(oracle_mod, dtype, N, rounds, bad, monkeypatch):
+    """Initial centroids with a non-finite component: no score of such a group
+    is smaller than another, so no key joins it, every key goes to the best
+    of the others, and the group keeps its centroid."""
+    if rounds:
+        monkeypatch.setenv("GA_GROUPING", "rounds")
+    print(f"\n[case] non-finite representatives {dtype} {N} {rounds} {bad}", flush=True)
+    B, H, n = 1, 4, 1100
+    _, K, _ = inputs.make_qkv(B, H, n, 64, dtype, N, 60, 0.05, 0.3)
+    init = (0.3 * np.random.default_rng(N).standard_normal((B, H, N, 64))).astype(np.float32)
+    init[0, 0, 2, 7] = bad  # one in a slice: several can hide each other
+    init[0, 1, 68, 0] = bad
+    init[0, 2, N - 1] = bad
+    init[0, 3, [1, 68, N // 2], 0] = bad
+    bel, cnt, cen = ga.cluster(K.cuda(), N, 3, init=torch.from_numpy(init).cuda())
+    torch.cuda.synchronize()
+    ref = oracle_mod.cluster(inputs.as_float64(K), N, 3, dtype, init=init)
+    assert np.array_equal(bel.cpu().numpy(), ref["belong"])
+    assert np.array_equal(cnt.cpu().numpy(), ref["count"])
+    assert np.array_equal(cen.cpu().numpy(), ref["centroid"], equal_nan=True)
