@@ -2134,12 +2134,14 @@ static int gsum_parts(const Dims& d) {
   return (int)max((int64_t)1, z);
 }
 
-// Threads of a workgroup of k_gsum and k_gdelta: 512 where the launch leaves about
-// one per compute unit (256 workgroups of 256 threads have four waves per unit:
-// the first round's sums of 32 slices, 256 groups 46 -> 37 us with 512), 256 where
-// more than one would share a unit, which 512 threads' registers do not allow
-// (512 workgroups at 128 slices of 8000 values, 128 groups: 43 us, 49 with 512).
-static int gsum_threads(int64_t wgs) { return wgs <= 320 ? 512 : 256; }
+// Threads of a workgroup of k_gsum and k_gdelta: 512 up to one workgroup per
+// compute unit (256 workgroups of 256 threads have four waves per unit: the
+// first round's sums of 32 slices, 256 groups 46 -> 37 us with 512), 256 beyond: a
+// unit holds one workgroup of 512 (148 and 166 registers a lane), so the launch
+// would take a second round (288 workgroups, 72 slices of 8000 values and 128
+// groups: aggregate 21.9 us with 256, 27.5 with 512; 320, 40 slices of 8000 keys and
+// 256 groups, ten rounds: cluster 387 and 414).
+static int gsum_threads(int64_t wgs) { return wgs <= 256 ? 512 : 256; }
 
 template <int MODE>
 static hipError_t run_gsum(const Dims& d, const uint16_t* X, const int32_t* belong, double* part, int32_t* pcnt,

@@ -34,7 +34,10 @@ AGGREGATE = [
     (1, 1, 2048, 32, True),     # two parts
     (1, 1, 20011, 10, True),    # sixteen parts, the last one short
     (1, 3, 9001, 70, True),     # three blocks of groups, the last one of six
-    (2, 64, 2500, 33, False),   # 256 workgroups without a split
+    (2, 64, 2500, 33, False),   # 256 workgroups without a split, the most of 512 threads
+    (1, 257, 300, 20, False),   # 257 of 256 threads
+    (16, 8, 600, 70, False),    # 384, the last block of groups of six
+    (4, 8, 12000, 64, True),    # 64 in five parts
 ]
 
 
@@ -62,6 +65,25 @@ def test_forward_split(oracle_mod, dev, case):
     (O, bel, cnt, cen), names = launches(
         lambda: ga.forward(Q.to(dev), K.to(dev), V.to(dev), N, iters, 0.125, return_groups=True))
     assert names["sums_finish"][0] == 2, names
+    ref = oracle_mod.forward(*(inputs.as_float64(t) for t in (Q, K, V)), N, iters, 0.125, "bf16")
+    assert np.array_equal(bel.cpu().numpy(), ref["belong"])
+    assert np.array_equal(cnt.cpu().numpy(), ref["count"])
+    assert np.array_equal(cen.cpu().numpy().view(np.uint32), ref["centroid"].view(np.uint32))
+    # 2e-2 per row: the documented bound of the bf16 attention
+    err = np.linalg.norm(O.float().cpu().numpy() - ref["O"], axis=-1)
+    assert (err <= 2e-2 * np.linalg.norm(ref["O"], axis=-1)).all()
+
+
+@pytest.mark.parametrize("case", [(1, 64, 600, 180, 4), (1, 43, 500, 170, 3)], ids=lambda c: "-".join(map(str, c)))
+def test_forward_many_workgroups(oracle_mod, dev, case):
+    """More than 256 workgroups of the group sums: the first round's sums, the
+    later rounds' moved keys and the attention's value means by 256 threads."""
+    B, H, n, N, iters = case
+    print(f"\n[case] forward, many workgroups {case}", flush=True)
+    Q, K, V = inputs.make_qkv(B, H, n, 64, "bf16", n + N, 128, 0.05, 0.3)
+    (O, bel, cnt, cen), names = launches(
+        lambda: ga.forward(Q.to(dev), K.to(dev), V.to(dev), N, iters, 0.125, return_groups=True))
+    assert names["sums_delta"][0] == iters - 1 and "sums_finish" not in names, names
     ref = oracle_mod.forward(*(inputs.as_float64(t) for t in (Q, K, V)), N, iters, 0.125, "bf16")
     assert np.array_equal(bel.cpu().numpy(), ref["belong"])
     assert np.array_equal(cnt.cpu().numpy(), ref["count"])
