@@ -129,8 +129,7 @@ int run_cluster(const ga::Dims& d, const void* K, int32_t iters, const float* in
       GA_LAUNCH(t == 0 ? ga::launch_sums_full(d, K, belong, w, count, C, st)
                        : ga::launch_sums_delta(d, K, mc_cur, mc_next, w, count, C, st), "update launch");
     } else {
-      GA_LAUNCH(ga::launch_update_f32(d, (const float*)K, belong, count, C, (float*)w.R, w.nrm64, st),
-                "update launch");
+      GA_LAUNCH(ga::launch_update_f32(d, (const float*)K, belong, w, count, C, st), "update launch");
     }
   }
   return GA_OK;
@@ -142,7 +141,7 @@ int run_valuesum(const ga::Dims& d, const void* V, const int32_t* belong, float*
   if (d.dtype == GA_BF16) {
     GA_LAUNCH(ga::launch_valuesum_bf16(d, V, belong, w, vsum, st), "value-sum launch");
   } else {
-    GA_LAUNCH(ga::launch_valuesum_f32(d, (const float*)V, belong, vsum, st), "value-sum launch");
+    GA_LAUNCH(ga::launch_valuesum_f32(d, (const float*)V, belong, false, w, w.count, vsum, st), "value-sum launch");
   }
   return GA_OK;
 }
@@ -172,7 +171,7 @@ int run_forward(const ga::Dims& d, const void* Q, const void* K, const void* V, 
     GA_LAUNCH(ga::launch_valuesum_prep(d, V, a, cnt, scale, w, st), "value-sum launch");
     GA_LAUNCH(ga::launch_attend(d, Q, w.R, w.Vt, w.ginit, C, cnt, w.vsum, scale, O, st), "attention launch");
   } else {
-    GA_LAUNCH(ga::launch_valuesum_f32(d, (const float*)V, a, w.vsum, st), "value-sum launch");
+    GA_LAUNCH(ga::launch_valuesum_f32(d, (const float*)V, a, true, w, cnt, w.vsum, st), "value-sum launch");
     GA_LAUNCH(ga::launch_attend(d, Q, nullptr, nullptr, nullptr, C, cnt, w.vsum, scale, O, st),
               "attention launch");
   }

@@ -7,6 +7,8 @@
 #include <math.h>
 #include <stdint.h>
 
+#include <mutex>
+
 #include "ga_internal.h"
 
 namespace ga {
@@ -204,58 +206,152 @@ __global__ __launch_bounds__(256) void k_assign_f32(const float* __restrict__ K,
 }
 
 // ------------------------------------------------------------------ ordered sums
+__device__ __forceinline__ int wave_incl_scan(int x) {
+  const int lane = threadIdx.x & 63;
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const int t = __shfl_up(x, d);
+    if (lane >= d) x += t;
+  }
+  return x;
+}
+
+// Stable counting sort of one slice's keys by group; grid BH, 1024 threads.
+// LDS: per-wave 64-bit lane masks [16][N], counts [N], running offsets [N].
+// Within a 1024-key chunk, a key's rank among same-group keys is the number
+// of lower lanes in its wave with the same group (popcount of the OR-ed lane
+// mask) plus the members of that group in the lower waves of the chunk.
+// Entries of belong outside [0, N) are left out.
+__global__ __launch_bounds__(1024) void k_bucket(const int32_t* __restrict__ belong, int n, int N,
+                                                 int32_t* __restrict__ perm, int32_t* __restrict__ goff,
+                                                 int32_t* __restrict__ count) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  __shared__ int wsum[16];
+  unsigned long long* wmask = (unsigned long long*)smem;
+  int32_t* cnt = (int32_t*)(wmask + 16 * N);
+  int32_t* run = cnt + N;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int64_t bh = blockIdx.x;
+  const int32_t* a = belong + bh * n;
+
+  for (int g = tid; g < N; g += 1024) cnt[g] = 0;
+  for (int x = tid; x < 16 * N; x += 1024) wmask[x] = 0ull;
+  __syncthreads();
+  for (int i = tid; i < n; i += 1024) {
+    const int g = a[i];
+    if ((unsigned)g < (unsigned)N) atomicAdd(&cnt[g], 1);
+  }
+  __syncthreads();
+  const int v = tid < N ? cnt[tid] : 0;
+  const int incl = wave_incl_scan(v);
+  if (lane == 63) wsum[wave] = incl;
+  __syncthreads();
+  if (wave == 0) {
+    const int t = lane < 16 ? wsum[lane] : 0;
+    const int ti = wave_incl_scan(t);
+    if (lane < 16) wsum[lane] = ti - t;
+  }
+  __syncthreads();
+  if (tid < N) {
+    const int ex = incl - v + wsum[wave];
+    run[tid] = ex;
+    goff[bh * N + tid] = ex;
+    count[bh * N + tid] = v;
+  }
+  __syncthreads();
+
+  const unsigned long long below = (1ull << lane) - 1ull;
+  for (int base = 0; base < n; base += 1024) {
+    const int i = base + tid;
+    const int g = i < n ? a[i] : -1;
+    const bool ok = (unsigned)g < (unsigned)N;
+    if (ok) atomicOr(&wmask[wave * N + g], 1ull << lane);
+    __syncthreads();
+    unsigned long long m = 0ull;
+    int rank = 0;
+    if (ok) {
+      m = wmask[wave * N + g];
+      rank = __popcll(m & below);
+      int pre = 0;
+      for (int w2 = 0; w2 < wave; ++w2) pre += __popcll(wmask[w2 * N + g]);
+      perm[bh * n + run[g] + pre + rank] = i;
+    }
+    __syncthreads();
+    if (ok && rank == 0) {
+      atomicAdd(&run[g], __popcll(m));
+      wmask[wave * N + g] = 0ull;
+    }
+    __syncthreads();
+  }
+}
+
 // k_segsum: grid (ceil(N/4), BH), 256 threads: one wave per group, lane =
-// feature.  The wave scans the slice's groups 64 keys at a time, appends the
-// keys of its group to a list in LDS (a ballot gives their places, so the list
-// ascends) and, whenever 64 are there and at the end, adds their rows in that
-// order in fp64 (fp32 sums need not be exact, so the order is part of the
+// feature.  The wave adds the rows of its group's members in ascending key order
+// in fp64 (fp32 sums need not be exact, so the order is part of the
 // definition).  UPDATE: count, centroid = (float)(sum / count) (an empty group
 // keeps its centroid), representative and |r|^2; otherwise the fp32 rounding of
-// the value sum.  Entries of belong outside [0, N) are ignored.
+// the value sum.  SORTED: the members are perm[goff .. goff + count) (k_bucket);
+// otherwise the wave finds them itself: it scans the slice's groups 64 keys at
+// a time and appends the keys of its group to a list in LDS (a ballot gives
+// their places, so the list ascends), added whenever 64 are there and at the
+// end.  Entries of belong outside [0, N) are ignored.
 //
 // Bound by latency: kScanU loads of 64 groups are in flight in the scan, and a
-// batch of kSegU rows while the one before it is added (all 64 rows
-// of a full list at once: no faster, and 98 against 78 us at 128 slices of 8000
-// keys, 128 groups, where fewer waves are resident).  Sorting the keys by
-// group in a launch of its own (one workgroup per slice) and reading the sorted
-// list took 7 + 12 us a round at 32 slices of 2000 keys and 64 groups, 35 us for
-// the sort alone at 20000 keys.
+// batch of kSegU rows while the one before it is added (all 64 rows of a full
+// list at once: no faster, and 98 against 78 us at 128 slices of 8000 keys, 128
+// groups, where fewer waves are resident).  Groups of up to kSegU members load by
+// the quad, not whole batches (scan of 512 slices of 300 keys, 256 groups 43 -> 33
+// us; sorted, 512 slices of 1000, 512 groups 82 -> 67).  Which of the two: see
+// sums_sorted.
 constexpr int kSegU = 16;
+constexpr int kSegS = 4;
 constexpr int kScanU = 8;
-template <bool UPDATE>
-__global__ __launch_bounds__(256) void k_segsum(const float* __restrict__ X, const int32_t* __restrict__ belong, int n,
-                                                int N, int32_t* __restrict__ count, float* __restrict__ out,
+template <bool UPDATE, bool SORTED>
+__global__ __launch_bounds__(256) void k_segsum(const float* __restrict__ X, const int32_t* __restrict__ belong,
+                                                const int32_t* __restrict__ perm, const int32_t* __restrict__ goff,
+                                                int n, int N, int32_t* __restrict__ count, float* __restrict__ out,
                                                 float* __restrict__ R, double* __restrict__ nrm64) {
-  __shared__ int32_t list[4][128];
+  __shared__ int32_t list[SORTED ? 1 : 4][SORTED ? 1 : 128];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int g = blockIdx.x * 4 + wave;
   const int64_t bh = blockIdx.y;
   if (g >= N) return;
   const int64_t row = bh * N + g;
-  const int32_t* bel = belong + bh * n;
   const float* Xb = X + bh * (int64_t)n * 64 + lane;
-  int32_t* L = list[wave];
   double acc = 0.0;
-  int cnt = 0, held = 0;  // members seen, members in the list
-  // adds the rows of the list's first m (1 .. 64) members in order
-  auto sum = [&](int m) {
-    const int idx = L[min(lane, m - 1)];
-    float va[kSegU], vb[kSegU];
-    auto load = [&](int x, float (&v)[kSegU]) {  // past the end: the last member again, not added
+  int cnt = 0;  // members
+  // adds the rows idx of the lanes 0 .. m - 1 (1 .. 64) in order
+  auto sum = [&](int idx, int m) {
+    auto load = [&](int x, auto& v) {  // past the end: the last member again, not added
+      constexpr int U = sizeof(v) / sizeof(float);
 #pragma unroll
-      for (int u = 0; u < kSegU; ++u) v[u] = Xb[(int64_t)__builtin_amdgcn_readlane(idx, x + u) * 64];
+      for (int u = 0; u < U; ++u) v[u] = Xb[(int64_t)__builtin_amdgcn_readlane(idx, x + u) * 64];
     };
-    auto add = [&](int x, const float (&v)[kSegU]) {
-      if (x + kSegU <= m) {
+    auto add = [&](int x, const auto& v) {
+      constexpr int U = sizeof(v) / sizeof(float);
+      if (x + U <= m) {
 #pragma unroll
-        for (int u = 0; u < kSegU; ++u) acc += (double)v[u];
+        for (int u = 0; u < U; ++u) acc += (double)v[u];
       } else {
 #pragma unroll
-        for (int u = 0; u < kSegU; ++u)
+        for (int u = 0; u < U; ++u)
           if (x + u < m) acc += (double)v[u];
       }
     };
+    if (!SORTED && m <= 4 * kSegS) {  // few members: only as many loads as there are quads of them
+      float v0[kSegS], v1[kSegS], v2[kSegS], v3[kSegS];
+      load(0, v0);
+      if (m > kSegS) load(kSegS, v1);
+      if (m > 2 * kSegS) load(2 * kSegS, v2);
+      if (m > 3 * kSegS) load(3 * kSegS, v3);
+      add(0, v0);
+      if (m > kSegS) add(kSegS, v1);
+      if (m > 2 * kSegS) add(2 * kSegS, v2);
+      if (m > 3 * kSegS) add(3 * kSegS, v3);
+      return;
+    }
+    float va[kSegU], vb[kSegU];
     load(0, va);
     if (m > kSegU) load(kSegU, vb);
     add(0, va);
@@ -267,39 +363,65 @@ __global__ __launch_bounds__(256) void k_segsum(const float* __restrict__ X, con
     add(2 * kSegU, va);
     if (m > 3 * kSegU) add(3 * kSegU, vb);
   };
-  for (int base = 0; base < n; base += 64 * kScanU) {
-    int b[kScanU];
+  if constexpr (SORTED) {
+    cnt = __builtin_amdgcn_readfirstlane(count[row]);
+    const int32_t* P = perm + bh * n + __builtin_amdgcn_readfirstlane(goff[row]);
+    if (cnt <= kSegU) {
+      int x = 0;
+      for (; x + kSegS <= cnt; x += kSegS) {
+        float v[kSegS];
 #pragma unroll
-    for (int u = 0; u < kScanU; ++u) b[u] = bel[min(base + 64 * u + lane, n - 1)];
+        for (int u = 0; u < kSegS; ++u) v[u] = Xb[(int64_t)P[x + u] * 64];
 #pragma unroll
-    for (int u = 0; u < kScanU; ++u) {
-      const int key = base + 64 * u + lane;
-      const bool mine = key < n && b[u] == g;
-      const uint64_t mask = __ballot(mine);
-      if (mask == 0) continue;  // uniform
-      if (mine)
-        L[held + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
-                                                __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u))] = key;
-      held += (int)__popcll(mask);
-      if (held >= 64) {
-        cnt += 64;
-        held -= 64;
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        sum(64);
-        const int rest = L[64 + lane];  // at most 63 of these are members
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        L[lane] = rest;
+        for (int u = 0; u < kSegS; ++u) acc += (double)v[u];
+      }
+      for (; x < cnt; ++x) acc += (double)Xb[(int64_t)P[x] * 64];
+    } else {
+      int next = P[min(lane, cnt - 1)];
+      for (int x = 0; x < cnt; x += 64) {
+        const int idx = next;
+        next = P[min(x + 64 + lane, cnt - 1)];
+        sum(idx, min(64, cnt - x));
       }
     }
+  } else {
+    const int32_t* bel = belong + bh * n;
+    int32_t* L = list[wave];
+    int held = 0;  // members in the list
+    for (int base = 0; base < n; base += 64 * kScanU) {
+      int b[kScanU];
+#pragma unroll
+      for (int u = 0; u < kScanU; ++u) b[u] = bel[min(base + 64 * u + lane, n - 1)];
+#pragma unroll
+      for (int u = 0; u < kScanU; ++u) {
+        const int key = base + 64 * u + lane;
+        const bool mine = key < n && b[u] == g;
+        const uint64_t mask = __ballot(mine);
+        if (mask == 0) continue;  // uniform
+        if (mine)
+          L[held + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
+                                                  __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u))] = key;
+        held += (int)__popcll(mask);
+        if (held >= 64) {
+          cnt += 64;
+          held -= 64;
+          __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+          sum(L[lane], 64);
+          const int rest = L[64 + lane];  // at most 63 of these are members
+          __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+          L[lane] = rest;
+        }
+      }
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    cnt += held;
+    if (held > 0) sum(L[min(lane, held - 1)], held);
   }
-  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-  cnt += held;
-  if (held > 0) sum(held);
   if (!UPDATE) {
     out[row * 64 + lane] = (float)acc;
     return;
   }
-  if (lane == 0) count[row] = cnt;
+  if (!SORTED && lane == 0) count[row] = cnt;
   float c;
   if (cnt > 0) {
     c = (float)(acc / (double)cnt);
@@ -440,19 +562,64 @@ hipError_t launch_assign_f32(const Dims& d, const float* K, const float* R, cons
   return hipGetLastError();
 }
 
-hipError_t launch_update_f32(const Dims& d, const float* K, const int32_t* belong, int32_t* count, float* C, float* R,
-                             double* nrm64, hipStream_t st) {
-  TimedLaunch timed("update", st);
-  hipLaunchKernelGGL((k_segsum<true>), dim3((unsigned)((d.N + 3) / 4), (unsigned)d.BH), dim3(256), 0, st, K, belong,
-                     d.n, d.N, count, C, R, nrm64);
+// Whether the ordered sums sort the keys by group first.  The scan of k_segsum
+// reads a slice's groups once for every group: with few (group, key) pairs it is
+// hidden behind the rows' latency and saves the sort's launch, with many it is the
+// longest part.  Aggregate, us, scan : sort, at the edge and on both sides of it: 32
+// slices of 20000 keys, 128 groups 47 : 58, 256 groups 65 : 59, 1024 groups 170 :
+// 61; 32 of 2000, 256 groups 10 : 13, 512 groups 12.7 : 13.3, 1024 groups 21 : 15;
+// 512 of 300, 128 groups 20 : 22, 256 groups 33 : 33.  Beyond 4000 keys both grow
+// alike.
+static bool sums_sorted(const Dims& d) {
+  return d.BH * d.N * (d.n < 4000 ? d.n : 4000) >= 32000000;
+}
+
+static size_t bucket_lds(int N) { return (size_t)16 * N * 8 + (size_t)2 * N * 4; }
+
+// The slices' keys sorted by group into w.mrec's first half (perm; its second half
+// takes goff), which only the bf16 path uses otherwise.
+static hipError_t launch_sort(const Dims& d, const int32_t* belong, const Workspace& w, int32_t* count,
+                              hipStream_t st) {
+  static std::once_flag once;
+  std::call_once(once, [] {
+    (void)hipFuncSetAttribute((const void*)k_bucket, hipFuncAttributeMaxDynamicSharedMemorySize,
+                              (int)bucket_lds(kMaxGroups));
+  });
+  TimedLaunch timed("bucket", st);
+  hipLaunchKernelGGL(k_bucket, dim3((unsigned)d.BH), dim3(1024), bucket_lds(d.N), st, belong, d.n, d.N,
+                     (int32_t*)w.mrec, (int32_t*)w.mrec + d.BH * d.n, count);
   return hipGetLastError();
 }
 
-hipError_t launch_valuesum_f32(const Dims& d, const float* V, const int32_t* belong, float* vsum, hipStream_t st) {
-  TimedLaunch timed("valuesum", st);
-  hipLaunchKernelGGL((k_segsum<false>), dim3((unsigned)((d.N + 3) / 4), (unsigned)d.BH), dim3(256), 0, st, V, belong,
-                     d.n, d.N, (int32_t*)nullptr, vsum, (float*)nullptr, (double*)nullptr);
+template <bool UPDATE>
+static hipError_t launch_segsum(const Dims& d, bool sorted, const float* X, const int32_t* belong, const Workspace& w,
+                                int32_t* count, float* out, hipStream_t st) {
+  TimedLaunch timed(UPDATE ? "update" : "valuesum", st);
+  const auto kern = sorted ? k_segsum<UPDATE, true> : k_segsum<UPDATE, false>;
+  hipLaunchKernelGGL(kern, dim3((unsigned)((d.N + 3) / 4), (unsigned)d.BH), dim3(256), 0, st, X, belong,
+                     (const int32_t*)w.mrec, (const int32_t*)w.mrec + d.BH * d.n, d.n, d.N, count, out, (float*)w.R,
+                     w.nrm64);
   return hipGetLastError();
+}
+
+hipError_t launch_update_f32(const Dims& d, const float* K, const int32_t* belong, const Workspace& w, int32_t* count,
+                             float* C, hipStream_t st) {
+  const bool sorted = sums_sorted(d);
+  if (sorted) {
+    const hipError_t e = launch_sort(d, belong, w, count, st);
+    if (e != hipSuccess) return e;
+  }
+  return launch_segsum<true>(d, sorted, K, belong, w, count, C, st);
+}
+
+hipError_t launch_valuesum_f32(const Dims& d, const float* V, const int32_t* belong, bool updated, const Workspace& w,
+                               int32_t* count, float* vsum, hipStream_t st) {
+  const bool sorted = sums_sorted(d);
+  if (sorted && !updated) {
+    const hipError_t e = launch_sort(d, belong, w, count, st);
+    if (e != hipSuccess) return e;
+  }
+  return launch_segsum<false>(d, sorted, V, belong, w, count, vsum, st);
 }
 
 hipError_t launch_attend_f32(const Dims& d, const float* Q, const float* centroid, const int32_t* count,

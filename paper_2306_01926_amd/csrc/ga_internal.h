@@ -26,7 +26,8 @@ struct Workspace {
   float* ginit;      // [BH][Npad] score-accumulator init, log2(count)/(|scale| log2 e)
   double* S64;       // [BH][N][64] fp64 member sums carried across rounds (bf16 path)
   int32_t* mcount;   // [2][BH] moved-key records of rounds t with t % 2 = 0, 1
-  unsigned long long* mrec;  // [BH][n] records (key << 32 | old << 16 | new)
+  unsigned long long* mrec;  // [BH][n] records (key << 32 | old << 16 | new); fp32: the keys sorted by group
+                             // [BH][n] int32, then each group's first place in them [BH][N] int32
   double* Sp;        // [BH][kFusedP][N][64] per-partition fp64 sums of the fused update
   int32_t* cntp;     // [BH][kFusedP][N] per-partition member counts
   uint32_t* pbits;   // [BH][kFusedP][4] groups with members in each partition (bit g)
@@ -126,11 +127,14 @@ hipError_t launch_attend(const Dims& d, const void* Q, const void* R, const uint
 
 // fp32 path (ga_f32.hip): the assignment, the sums of each group's members in
 // ascending key order (centroids and representatives; values), the attention.
+// Both sums may sort the keys by group first, into w.mrec; updated: the last
+// launch_update_f32 on this workspace was for the same assignment and left count.
 hipError_t launch_assign_f32(const Dims& d, const float* K, const float* R, const double* nrm64, int32_t* belong,
                              bool first, hipStream_t st);
-hipError_t launch_update_f32(const Dims& d, const float* K, const int32_t* belong, int32_t* count, float* C, float* R,
-                             double* nrm64, hipStream_t st);
-hipError_t launch_valuesum_f32(const Dims& d, const float* V, const int32_t* belong, float* vsum, hipStream_t st);
+hipError_t launch_update_f32(const Dims& d, const float* K, const int32_t* belong, const Workspace& w, int32_t* count,
+                             float* C, hipStream_t st);
+hipError_t launch_valuesum_f32(const Dims& d, const float* V, const int32_t* belong, bool updated, const Workspace& w,
+                               int32_t* count, float* vsum, hipStream_t st);
 hipError_t launch_attend_f32(const Dims& d, const float* Q, const float* centroid, const int32_t* count,
                              const float* vsum, float scale, float* O, hipStream_t st);
 

@@ -72,6 +72,53 @@ def test_cluster_f32_ties_and_scales(oracle_mod, dev):
     assert_groups(got, oracle_mod.cluster(f64(Kt), 40, 3, "f32", init=init))
 
 
+def launched(f):
+    ga.timing_enable(True)
+    try:
+        r = f()
+        torch.cuda.synchronize()
+    finally:
+        ga.timing_enable(False)
+        names = ga.timing_collect()
+    return r, names
+
+
+@pytest.mark.parametrize("B,H,n,N,sort", [(4, 8, 2000, 499, False), (4, 8, 2003, 500, True), (2, 4, 4500, 1000, True),
+                                          (1, 1, 5000, 700, False)])
+def test_aggregate_f32_order(oracle_mod, dev, B, H, n, N, sort):
+    """The value sums on both sides of the rule that sorts the keys first: groups
+    of none to hundreds of members added in ascending order, values whose sums
+    depend on it, entries outside [0, N) ignored."""
+    print(f"\n[case] aggregate f32 {B} {H} {n} {N}", flush=True)
+    rng = np.random.default_rng(n)
+    V = (rng.standard_normal((B, H, n, 64)) * 2.0 ** rng.integers(-30, 30, (B, H, n, 64))).astype(np.float32)
+    belong = (N * rng.random((B, H, n)) ** 3).astype(np.int32)
+    belong[rng.random((B, H, n)) < 0.3] = 7
+    belong[0, 0, ::97], belong[-1, -1, 1::89] = -1, N
+    vs, names = launched(lambda: ga.aggregate(torch.from_numpy(V).to(dev), torch.from_numpy(belong).to(dev), N))
+    ref, _ = oracle_mod.aggregate(V.astype(np.float64), belong, N)
+    assert np.array_equal(vs.cpu().numpy().view(np.uint32), ref.astype(np.float32).view(np.uint32))
+    assert ("bucket" in names) == sort, sorted(names)
+
+
+def test_forward_f32_sorted(oracle_mod, dev):
+    """A forward whose updates sort the keys and whose value sums take the last
+    round's order; groups that end empty keep their centroid."""
+    print("\n[case] forward f32, sorted sums", flush=True)
+    B, H, n, N, iters = 8, 8, 1000, 512, 2
+    Q, K, V = inputs.make_qkv(B, H, n, 64, "f32", 9, 100, 0.05, 0.3)
+    K[:, :, 1::2] = K[:, :, ::2]
+    (O, *got), names = launched(lambda: ga.forward(Q.to(dev), K.to(dev), V.to(dev), N, iters, 0.125,
+                                                   return_groups=True))
+    assert names["bucket"][0] == iters, names
+    ref = oracle_mod.forward(f64(Q), f64(K), f64(V), N, iters, 0.125, "f32")
+    assert_groups(got, ref)
+    assert (ref["count"] == 0).any()
+    # 1e-4 per row: the documented bound of the fp32 attention
+    err = np.linalg.norm(O.cpu().numpy() - ref["O"], axis=-1)
+    assert (err <= 1e-4 * np.linalg.norm(ref["O"], axis=-1)).all()
+
+
 ATTEND = [
     # B, H, n, N, scale
     (1, 1, 1, 1, 0.125),
