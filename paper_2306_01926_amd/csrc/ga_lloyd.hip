@@ -942,7 +942,12 @@ __device__ __forceinline__ void lloyd_value_outputs(const LloydArgs& a, const Ll
 }
 
 // ------------------------------------------------------------ kernel
-template <int NB>
+// SOLO: one rank per slice.  A kernel of its own: with both forms in one, four
+// blocks spilled 10 registers (44 bytes of scratch a lane, written and read back
+// around the scoring loop in every round); apart 0, and 1 with one rank.
+// Forwards of 10 rounds and 128 groups: 128 slices of 8000 keys 518 -> 506 us, of
+// 1000 keys 160 -> 150.
+template <int NB, bool SOLO>
 __global__ __launch_bounds__(kLT) void k_lloyd(LloydArgs a) {
   extern __shared__ __align__(16) unsigned char smem[];
   __shared__ int s_nmov, s_nunc, s_xmov, s_flag;
@@ -951,8 +956,7 @@ __global__ __launch_bounds__(kLT) void k_lloyd(LloydArgs a) {
   const int bx = blockIdx.x, idx = bx >> 3;
   const int64_t s = (int64_t)(idx / a.P) * 8 + (bx & 7);
   const int r = idx % a.P;
-  const bool solo = a.P == 1;
-  if (solo && bx == 0 && tid == 0) *a.status = kLloydMark;  // (k_lloyd_reset's part where ranks meet)
+  if (SOLO && bx == 0 && tid == 0) *a.status = kLloydMark;  // (k_lloyd_reset's part where ranks meet)
   if (s >= a.BH) return;
   const int Go = lloyd_go(Npad, a.P);
   const LloydLds L = lloyd_layout(smem, Npad, a.P);
@@ -992,7 +996,7 @@ __global__ __launch_bounds__(kLT) void k_lloyd(LloydArgs a) {
     lds_barrier();
     const int nunc = s_nunc, nmov = s_nmov;
     float2 prev[kLFinU];
-    if (solo) lloyd_prev_c(a, s, r, Go, prev);  // (else the loads overlap barrier A)
+    if (SOLO) lloyd_prev_c(a, s, r, Go, prev);  // (else the loads overlap barrier A)
     // after the first round, with few moved keys (their sums take the direct
     // path, which uses no LDS scratch), the exact fallback and the moved-key
     // sums run side by side: both add exact values into the sums
@@ -1007,7 +1011,7 @@ __global__ __launch_bounds__(kLT) void k_lloyd(LloydArgs a) {
       lloyd_sums_moved(a, L, s, k0, nmov, Npad);
     // a round in which no key of the slice changed group is a fixed point, so
     // it is the last
-    if (solo) {
+    if (SOLO) {
       if (!first && nmov + s_xmov == 0) last = true;
       lloyd_finish<true>(a, L, s, r, Go, last, prev, &s_nmov, &s_nunc, &s_xmov);
       if (last) break;
@@ -1041,7 +1045,7 @@ __global__ __launch_bounds__(kLT) void k_lloyd(LloydArgs a) {
   for (int i = tid; i < Npad * kLSA; i += kLT) L.SA[i] = 0.0;
   lds_barrier();
   lloyd_sums_all(a.V, a, L, s, k0, nk, Npad, false);
-  if (!solo) {
+  if (!SOLO) {
     if (!slice_barrier(ctr, a.status, a.P, bar++, &s_flag)) return;
     lloyd_publish(a, L, s, r);
     if (!slice_barrier(ctr, a.status, a.P, bar++, &s_flag)) return;
@@ -1071,7 +1075,8 @@ namespace ga {
 namespace {
 
 using LloydFn = void (*)(LloydArgs);
-const LloydFn kLloydFns[4] = {k_lloyd<1>, k_lloyd<2>, k_lloyd<3>, k_lloyd<4>};
+const LloydFn kLloydFns[2][4] = {{k_lloyd<1, false>, k_lloyd<2, false>, k_lloyd<3, false>, k_lloyd<4, false>},
+                                 {k_lloyd<1, true>, k_lloyd<2, true>, k_lloyd<3, true>, k_lloyd<4, true>}};
 
 // Most ranks per slice: about one per 256 keys, at most 16, and at most
 // kLMaxWG workgroups in the launch (this also bounds the exchange buffer,
@@ -1082,19 +1087,19 @@ int lloyd_pcap(const Dims& d) {
   return (int)std::max<int64_t>(1, p);
 }
 
-// Compute units of the current device and the workgroups of `fn` (512
-// threads, `lds` bytes of dynamic LDS) each holds at once; cached.
-std::pair<int, int> lloyd_capacity(int nb, size_t lds) {
+// Compute units of the current device and the workgroups of the grouping kernel
+// (512 threads, `lds` bytes of dynamic LDS) each holds at once; cached.
+std::pair<int, int> lloyd_capacity(int nb, bool solo, size_t lds) {
   static std::mutex mu;
-  static std::map<std::tuple<int, int, size_t>, std::pair<int, int>> cache;
+  static std::map<std::tuple<int, int, bool, size_t>, std::pair<int, int>> cache;
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess) return {0, 0};
   std::lock_guard<std::mutex> lock(mu);
-  const auto key = std::make_tuple(dev, nb, lds);
+  const auto key = std::make_tuple(dev, nb, solo, lds);
   auto it = cache.find(key);
   if (it != cache.end()) return it->second;
   int cus = 0, occ = 0;
-  const void* fn = (const void*)kLloydFns[nb - 1];
+  const void* fn = (const void*)kLloydFns[solo][nb - 1];
   (void)hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lloyd_lds_bytes(32 * nb, 1));
   if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
       hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, fn, kLT, lds) != hipSuccess) {
@@ -1131,7 +1136,7 @@ LloydPlan plan_lloyd(const Dims& d) {
   // every workgroup of the launch resident at once
   for (; P >= 1; --P) {
     const size_t lds = lloyd_lds_bytes(Npad, P);
-    const auto cap = lloyd_capacity(p.nb, lds);
+    const auto cap = lloyd_capacity(p.nb, P == 1, lds);
     if ((int64_t)bh8 * 8 * P <= (int64_t)cap.first * cap.second) {
       p.lds = lds;
       break;
@@ -1204,7 +1209,7 @@ hipError_t launch_lloyd(const Dims& d, const void* K, const void* V, const float
   a.vts = vt_stride(d.N);
   const float sl2e = std::max(fabsf(scale) * 1.4426950408889634f, 1e-30f);
   a.inv_sl2e = 1.0f / sl2e;
-  hipLaunchKernelGGL(kLloydFns[p.nb - 1], dim3(p.grid), dim3(kLT), p.lds, st, a);
+  hipLaunchKernelGGL(kLloydFns[p.P == 1][p.nb - 1], dim3(p.grid), dim3(kLT), p.lds, st, a);
   return hipGetLastError();
 }
 
