@@ -473,3 +473,15 @@ def test_non_finite_representatives(oracle_mod, dtype, N, rounds, bad, monkeypat
     assert np.array_equal(bel.cpu().numpy(), ref["belong"])
     assert np.array_equal(cnt.cpu().numpy(), ref["count"])
     assert np.array_equal(cen.cpu().numpy(), ref["centroid"], equal_nan=True)
+
+
+def test_stream_handle(dev, monkeypatch):
+    """The current stream's handle, by torch's direct lookup and by the public way
+    that a torch without it takes: on the default and on another stream."""
+    for raw in (ga._raw_stream, None):
+        monkeypatch.setattr(ga, "_raw_stream", raw)
+        assert ga._stream_handle(dev) == torch.cuda.current_stream(dev).cuda_stream
+        side = torch.cuda.Stream(dev)
+        with torch.cuda.stream(side):
+            assert ga._stream_handle(dev) == side.cuda_stream
+            assert ga._stream_handle(torch.device("cuda")) == side.cuda_stream  # no index: the current device
