@@ -31,8 +31,9 @@ struct Workspace {
   double* Sp;        // [BH][kFusedP][N][64] per-partition fp64 sums of the fused update
   int32_t* cntp;     // [BH][kFusedP][N] per-partition member counts
   uint32_t* pbits;   // [BH][kFusedP][4] groups with members in each partition (bit g)
-  double* lxs;       // persistent grouping (ga_lloyd.hip): [lloyd_exchange_rows(d)][64] exchanged group sums
-  int32_t* lxc;      // [lloyd_exchange_rows(d)] exchanged member-count deltas
+  double* lxs;       // [lloyd_exchange_rows(d)][64] exchanged group sums of the persistent grouping (ga_lloyd.hip);
+                     // the partial sums of bf16 group sums split over workgroups (run_gsum)
+  int32_t* lxc;      // [lloyd_exchange_rows(d)] exchanged member-count deltas; the partial sums' counts
   int32_t* lxm;      // [BH][16] keys of each rank that changed group in a round
   uint32_t* lsync;   // [BH][32] barrier counters
   uint32_t* lstatus; // [64] status word (bit 0: a barrier gave up)
@@ -42,7 +43,9 @@ struct Workspace {
 // partition of a slice's keys, at most kFusedP per slice) forms the initial
 // representatives itself (no init launch), then sums the rows of its keys per
 // group into its own partition of Sp; launch_part_finish adds the partitions
-// into S64 and forms count, C, R, |r|^2 and the split.
+// into S64 and forms count, C, R, |r|^2 and the split.  For N > kFusedG a first
+// round that forms the initial representatives itself (first_round_inits) reads
+// init and writes C alone.
 constexpr int kFusedG = 128;
 constexpr int kFusedP = 8;
 struct FusedUpdate {
@@ -141,7 +144,9 @@ hipError_t launch_attend_f32(const Dims& d, const float* Q, const float* centroi
 // Persistent grouping (ga_lloyd.hip): every Lloyd round, the update and (if V
 // is given) the value sums in one launch, for bf16, N <= 128 and shapes whose
 // workgroups (P per slice) are all resident at once.  Writes belong, count, C,
-// the final R / nsplit / nrm64 in w, and vsum and/or Vt + ginit if given.
+// the final R in w, and vsum and/or Vt + ginit if given.  The exchanged
+// representatives' w.nsplit / w.nrm64 are the launch's own (untouched with one
+// rank per slice).
 size_t lloyd_exchange_rows(const Dims& d);  // rows (of 64 fp64) of w.lxs: B*H * (most ranks per slice) * Npad
 // w.lstatus after a persistent grouping launch: kLloydMark, | 1 if a
 // cross-workgroup wait gave up
