@@ -98,6 +98,18 @@ __device__ __forceinline__ float wave_max(float x) {
   return max2(__uint_as_float(q[0]), __uint_as_float(q[1]));
 }
 
+// The largest of the 64 lanes' words, in every lane.
+__device__ __forceinline__ uint32_t wave_max_bits(uint32_t x) {
+  x = max(x, (uint32_t)dpp<kXor1>((int)x));
+  x = max(x, (uint32_t)dpp<kXor2>((int)x));
+  x = max(x, (uint32_t)dpp<kHalfMirror>((int)x));
+  x = max(x, (uint32_t)dpp<kMirror>((int)x));
+  const auto p = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+  x = max(p[0], p[1]);
+  const u32x2 q = halves(x);
+  return max(q[0], q[1]);
+}
+
 // The smallest of the 64 lanes' scores and its index (the lowest among equals),
 // in every lane.
 __device__ __forceinline__ void wave_argmin(double& best, int& bj) {

@@ -235,11 +235,20 @@ __device__ __forceinline__ void exact_decide_queue(const uint16_t* __restrict__ 
   }
 }
 
-// The larger of two |r|^2, NaN if either is: with a NaN or an infinity the error
-// bound of the certified decisions is no finite number, so that every key of the
-// slice goes to the exact decision, where such a group never wins.  (The class
+// The largest |r|^2 of a slice is taken over fp32 bit patterns (rounding keeps
+// the order), which rank a NaN above every number: with a NaN or an infinity the
+// error bound of the certified decisions is no finite number, so that every key of
+// the slice goes to the exact decision, where such a group never wins.  (The class
 // minima of k_assign_bf16 pass a NaN score on and cannot be ranked.)
-__device__ __forceinline__ double norm_max(double a, double b) { return a > b || a != a ? a : b; }
+__device__ __forceinline__ uint32_t norm_bits(double nrm) { return __float_as_uint((float)nrm); }
+// ... of the four waves' threads, in every thread (red: four words of LDS).  Ends
+// with a barrier before the read.
+__device__ __forceinline__ float block_norm_max(uint32_t mx, uint32_t* red) {
+  mx = wave_max_bits(mx);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = mx;
+  __syncthreads();
+  return __uint_as_float(max(max(red[0], red[1]), max(red[2], red[3])));
+}
 
 // Stage -2R (swizzled, see swz) and the |r|^2 split of one slice into LDS and
 // return the slice's largest canonical |r|^2.  Padded groups (j >= N) get
@@ -247,17 +256,17 @@ __device__ __forceinline__ double norm_max(double a, double b) { return a > b ||
 // issues all of its loads before converting (NPAD_C > 0: Npad known at
 // compile time).  Ends with a barrier.
 template <int NPAD_C>
-__device__ __forceinline__ double stage_reps(const uint16_t* __restrict__ Rbh, const uint16_t* __restrict__ nsplit_bh,
+__device__ __forceinline__ float stage_reps(const uint16_t* __restrict__ Rbh, const uint16_t* __restrict__ nsplit_bh,
                                              const double* __restrict__ nrm_bh, int N, int Npad_rt, uint16_t* Rs,
-                                             uint16_t* Ns, double* red) {
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+                                             uint16_t* Ns, uint32_t* red) {
+  const int tid = threadIdx.x;
   const int Npad = NPAD_C > 0 ? NPAD_C : Npad_rt;
   const int j = tid;  // Npad <= 1024 rows: the split and |r|^2 of rows tid, tid + 256, ...
   u32x4 sp = {0x7f7fu, 0u, 0u, 0u};
-  double mx = 0.0;
+  uint32_t mx = 0;
   if (j < N) {
     sp = *(const u32x4*)(nsplit_bh + j * 8);
-    mx = nrm_bh[j];
+    mx = norm_bits(nrm_bh[j]);
   }
   if (NPAD_C > 0) {
     constexpr int IT = NPAD_C > 0 ? NPAD_C * 8 / 256 : 1;
@@ -309,13 +318,9 @@ __device__ __forceinline__ double stage_reps(const uint16_t* __restrict__ Rbh, c
   for (int jj = tid + 256; jj < Npad; jj += 256) {
     const u32x4 sp2 = jj < N ? *(const u32x4*)(nsplit_bh + jj * 8) : u32x4{0x7f7fu, 0u, 0u, 0u};
     *(u32x4*)(Ns + jj * 8) = sp2;
-    if (jj < N) mx = norm_max(mx, nrm_bh[jj]);
+    if (jj < N) mx = max(mx, norm_bits(nrm_bh[jj]));
   }
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) mx = norm_max(mx, __shfl_xor(mx, off));
-  if (lane == 0) red[wave] = mx;
-  __syncthreads();
-  return norm_max(norm_max(red[0], red[1]), norm_max(red[2], red[3]));
+  return block_norm_max(mx, red);
 }
 
 // First round with partition sums: the initial representatives straight from
@@ -325,10 +330,10 @@ __device__ __forceinline__ double stage_reps(const uint16_t* __restrict__ Rbh, c
 // group) goes to nrm_l and its split to Ns; C_bh, if given, receives C.  Ends
 // with a barrier; returns the slice's largest |r|^2.
 template <int NPAD>
-__device__ __forceinline__ double stage_init(const uint16_t* __restrict__ Kbh, const float* __restrict__ init_bh,
+__device__ __forceinline__ float stage_init(const uint16_t* __restrict__ Kbh, const float* __restrict__ init_bh,
                                              int n, int N, float* __restrict__ C_bh, uint16_t* Rs, uint16_t* Ns,
-                                             double* nrm_l, double* red) {
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+                                             double* nrm_l, uint32_t* red) {
+  const int tid = threadIdx.x;
   constexpr int IT = NPAD * 8 / 256;
 #pragma unroll
   for (int it = 0; it < IT; ++it) {
@@ -365,7 +370,7 @@ __device__ __forceinline__ double stage_init(const uint16_t* __restrict__ Kbh, c
     *(u32x4*)(Rs + swz(row, ch)) = v;
   }
   __syncthreads();
-  double mx = 0.0;
+  uint32_t mx = 0;
   if (tid < NPAD) {
     const int j = tid;
     double nrm = 0.0;
@@ -382,25 +387,21 @@ __device__ __forceinline__ double stage_init(const uint16_t* __restrict__ Kbh, c
         }
       }
       write_nsplit(nrm, Ns + j * 8);
-      mx = nrm;
+      mx = norm_bits(nrm);
     } else {
       *(u32x4*)(Ns + j * 8) = u32x4{0x7f7fu, 0u, 0u, 0u};
     }
     nrm_l[j] = nrm;
   }
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) mx = norm_max(mx, __shfl_xor(mx, off));
-  if (lane == 0) red[wave] = mx;
-  __syncthreads();
-  return norm_max(norm_max(red[0], red[1]), norm_max(red[2], red[3]));
+  return block_norm_max(mx, red);
 }
 
 // The first round of k_assign_bf16<true, true>: stage_init for any N, 256 threads; the
 // |r|^2 of 32 groups at a time by eight lanes each (norm8), to nrm_l as well.
-__device__ __forceinline__ double stage_init_wide(const uint16_t* __restrict__ Kbh, const float* __restrict__ init_bh,
+__device__ __forceinline__ float stage_init_wide(const uint16_t* __restrict__ Kbh, const float* __restrict__ init_bh,
                                                   int n, int N, int Npad, float* __restrict__ C_bh, uint16_t* Rs,
-                                                  uint16_t* Ns, double* nrm_l, double* red) {
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+                                                  uint16_t* Ns, double* nrm_l, uint32_t* red) {
+  const int tid = threadIdx.x;
   constexpr int IT = 8;  // 256 rows a step, their loads in flight together
   for (int i0 = tid; i0 < Npad * 8; i0 += 256 * IT) {
     float4 a[IT], b[IT];
@@ -453,7 +454,7 @@ __device__ __forceinline__ double stage_init_wide(const uint16_t* __restrict__ K
     }
   }
   __syncthreads();
-  double mx = 0.0;
+  uint32_t mx = 0;
   for (int g0 = 0; g0 < Npad; g0 += 32) {
     const int g = g0 + (tid >> 3), j = tid & 7;
     const u32x4 v = *(const u32x4*)(Rs + swz(g, j));
@@ -477,17 +478,13 @@ __device__ __forceinline__ double stage_init_wide(const uint16_t* __restrict__ K
     }
     if (g < N) {
       write_nsplit(nrm, Ns + g * 8);
-      mx = norm_max(mx, nrm);
+      mx = max(mx, norm_bits(nrm));
     } else {
       *(u32x4*)(Ns + g * 8) = u32x4{0x7f7fu, 0u, 0u, 0u};
     }
     nrm_l[g] = nrm;
   }
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) mx = norm_max(mx, __shfl_xor(mx, off));
-  if (lane == 0) red[wave] = mx;
-  __syncthreads();
-  return norm_max(norm_max(red[0], red[1]), norm_max(red[2], red[3]));
+  return block_norm_max(mx, red);
 }
 
 // Dynamic LDS of the assign kernels: region A = -2R as [Npad][64] bf16
@@ -851,7 +848,7 @@ __global__ __launch_bounds__(256) void k_assign_bf16(
     int32_t* __restrict__ mcount, unsigned long long* __restrict__ mrec, int n, int N, int tpw, float cm,
     float cp, FusedUpdate fu) {
   extern __shared__ __align__(16) unsigned char smem[];
-  __shared__ double red[4];
+  __shared__ uint32_t red[4];
   __shared__ AssignCounts cnt;
   __shared__ __align__(16) double kd[4][64];  // fp64 row of a queued key, per wave
   const int Npad = (N + 31) & ~31;
@@ -898,7 +895,7 @@ __global__ __launch_bounds__(256) void k_assign_bf16(
   // a launch of their own; workgroup 0 of the slice writes C and clears the
   // moved-key counters of the next rounds
   double* nrm_l = (double*)(smem + assign_nrm_at(Npad, tpw));
-  double nmax;
+  float nmax;
   if (INIT) {
     if (blockIdx.x == 0 && tid == 0) {
       mcount[bh] = 0;
@@ -910,7 +907,7 @@ __global__ __launch_bounds__(256) void k_assign_bf16(
     nmax = stage_reps<0>(R + bh * (int64_t)N * 64, nsplit + bh * N * 8, nrm64 + bh * N, N, Npad, L.Rs, L.Ns, red);
   }
   const double* nrm_x = INIT ? (const double*)nrm_l : nrm64 + bh * N;  // |r|^2 for the exact decisions
-  const float nmaxf = (float)nmax * (1.0f + 0x1p-20f);
+  const float nmaxf = nmax * (1.0f + 0x1p-20f);
   const float rmaxf = sqrtf(nmaxf) * (1.0f + 0x1p-20f);
   const Certify cf = {nmaxf, rmaxf, cm, cp};
 
@@ -1029,7 +1026,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
     float* __restrict__ knorm, int32_t* __restrict__ belong, int32_t* __restrict__ mcount,
     unsigned long long* __restrict__ mrec, int n, int N, int tpw, float cm, float cp, FusedUpdate fu) {
   extern __shared__ __align__(16) unsigned char smem[];
-  __shared__ double red[4];
+  __shared__ uint32_t red[4];
   __shared__ AssignCounts cnt;
   __shared__ __align__(16) double kd[4][kExactB * 64];  // fp64 rows of queued keys, per wave
   constexpr int Npad = NB * 32;
@@ -1058,13 +1055,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
     mcount[bh] = 0;
     mcount[gridDim.y + bh] = 0;
   }
-  const double nmax =
+  const float nmax =
       FUSED ? stage_init<Npad>(Kbh, fu.init ? fu.init + bh * (int64_t)N * 64 : nullptr, n, N,
                                blockIdx.x == 0 ? fu.C + bh * (int64_t)N * 64 : nullptr, L.Rs, L.Ns, nrm_l, red)
             : stage_reps<Npad>(R + bh * (int64_t)N * 64, nsplit + bh * N * 8, nrm64 + bh * N, N, Npad, L.Rs, L.Ns,
                                red);
   const double* nrm_x = FUSED ? (const double*)nrm_l : nrm64 + bh * N;  // |r|^2 for the exact decisions
-  const float nmaxf = (float)nmax * (1.0f + 0x1p-20f);
+  const float nmaxf = nmax * (1.0f + 0x1p-20f);
   const float rmaxf = sqrtf(nmaxf) * (1.0f + 0x1p-20f);
   const Certify cf = {nmaxf, rmaxf, cm, cp};
 
