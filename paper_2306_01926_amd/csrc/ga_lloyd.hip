@@ -293,6 +293,50 @@ __device__ __forceinline__ void lloyd_stage_init(const LloydArgs& a, const Lloyd
   }
 }
 
+// A representative with the bits of one of lower index never wins (equal scores,
+// the lowest index), but its exact tie sends every key nearest to the two to the
+// exact fallback, in padded or constant series most of them.  So where the first
+// round leaves a rank many uncertain keys, it is scored again with such groups
+// out of the way, and later rounds are too if there were any (a group without
+// keys keeps its representative): the group scores like a padded one.  Its |r|^2
+// split alone changes; the fallback reads R and |r|^2.  Equal rows have equal
+// |r|^2, so thread (g, quarter of the lower groups) compares those first, kRep at
+// a time.
+//
+// Clusterings of 8 slices of 1000 keys, 64 groups, five rounds, us: the last half of
+// the keys zero 786 -> 212, the last tenth 374 -> 85, all equal 474 -> 33.
+constexpr int kRep = 8;
+__device__ __forceinline__ void lloyd_mask_repeats(const LloydLds& L, int Npad, int N, int* found) {
+  const int tid = opaque_tid(), g = tid & 127, j0 = (tid >> 7) * (128 * 128 / kLT);
+  if (j0 >= Npad) return;  // uniform
+  const double nr = L.nrm[min(g, Npad - 1)];
+#pragma unroll 1
+  for (int j = j0; j < j0 + 128 * 128 / kLT; j += kRep) {  // (Npad is a multiple of 32)
+    uint32_t hit = 0;
+#pragma unroll
+    for (int u = 0; u < kRep; ++u) hit |= (L.nrm[j + u] == nr ? 1u : 0u) << u;
+    if (g >= N) hit = 0;
+    if (j + kRep > g) hit &= (1u << max(g - j, 0)) - 1u;
+#pragma unroll 1
+    for (; hit; hit &= hit - 1) {
+      const int h = j + __ffs(hit) - 1;
+      bool same = true;
+#pragma unroll 1
+      for (int c = 0; c < 8; ++c) {
+        const u32x4 x = *(const u32x4*)(L.Rs + swz(g, c)), y = *(const u32x4*)(L.Rs + swz(h, c));
+        same &= x[0] == y[0] && x[1] == y[1] && x[2] == y[2] && x[3] == y[3];
+      }
+      if (same) {
+        uint32_t z;  // 0, formed here: a constant would be kept in registers across the rounds
+        asm volatile("v_mov_b32 %0, 0" : "=v"(z));
+        *(u32x4*)(L.Ns + g * 8) = u32x4{z | 0x7f7fu, z, z, z};
+        *found = 1;
+        return;
+      }
+    }
+  }
+}
+
 // Later rounds: the slice's representatives published by their owners.
 __device__ __forceinline__ void lloyd_read_reps(const LloydArgs& a, const LloydLds& L, int64_t s) {
   constexpr int kU = 128 * 8 / kLT;  // 16-byte chunks of R per thread, N <= 128
@@ -380,9 +424,8 @@ __device__ __forceinline__ void lloyd_decide(float M1a, float M2a, int B1a, floa
   if (un) L.ent[kLCap - 1 - (bu + (int)__popcll(mu & below))] = (uint32_t)lk | ((uint32_t)oldv << 12);
 }
 
-// A wave takes every kLW-th tile of the rank, ascending in even rounds and the
-// same tiles descending (rev) in odd ones, so a round starts on the tile that
-// the wave read last: its rows (k0) stay in registers from round to round and
+// A wave takes every kLW-th tile of the rank, ascending and descending (rev) in
+// turn, so a round starts on the tile that the wave read last: its rows (k0) stay in registers from round to round and
 // the first tile of a round waits for no load (a wave with one tile never
 // reads it again).
 __device__ __forceinline__ int lloyd_tiles(int nk, int wv) {
@@ -484,12 +527,12 @@ __device__ __forceinline__ void lloyd_exact(const LloydArgs& a, const LloydLds& 
       if (b < nb) kd[b * 64 + lane] = (double)bf16_to_f32(Kbh[(int64_t)(k0 + (e[b] & 4095u)) * 64 + lane]);
     }
     int jb[kLExactB];
-    switch (nb) {
-      case 1: exact_argmin_keys<1>(kd, L.Rs, L.nrm, a.N, jb); break;
-      case 2: exact_argmin_keys<2>(kd, L.Rs, L.nrm, a.N, jb); break;
-      case 3: exact_argmin_keys<3>(kd, L.Rs, L.nrm, a.N, jb); break;
-      default: exact_argmin_keys<4>(kd, L.Rs, L.nrm, a.N, jb); break;
-    }
+    // (one or four: with a code for each number the kernel outgrows the instruction
+    // cache by more; the rows past nb are stale and their results unused)
+    if (nb == 1)
+      exact_argmin_keys<1>(kd, L.Rs, L.nrm, a.N, jb);
+    else
+      exact_argmin_keys<kLExactB>(kd, L.Rs, L.nrm, a.N, jb);
 #pragma unroll
     for (int b = 0; b < kLExactB; ++b) {
       if (b >= nb) break;
@@ -851,6 +894,7 @@ __device__ __forceinline__ void lloyd_finish(const LloydArgs& a, const LloydLds&
   uint32_t full = 0;     // bit u: the item's group has members
 #pragma unroll
   for (int u = 0; u < kLFinU; ++u) {
+    if (!SOLO && kLT * u >= Go * 32) break;  // uniform; most of the unrolled items of a rank with few groups
     const int idx = tid + kLT * u, lg = idx >> 5, c2 = idx & 31, g = r + a.P * lg;
     if (lg >= Go || g >= a.N) continue;
     const int cnt = L.cnt[lg] + L.dcA[g];
@@ -910,6 +954,7 @@ __device__ __forceinline__ void lloyd_finish(const LloydArgs& a, const LloydLds&
   // C (non-empty groups) and R
 #pragma unroll
   for (int u = 0; u < kLFinU; ++u) {
+    if (!SOLO && kLT * u >= Go * 32) break;
     const int idx = tid + kLT * u, lg = idx >> 5, c2 = idx & 31, g = r + a.P * lg;
     if (lg >= Go || g >= a.N) continue;
     if ((full >> u) & 1u) *(float2*)(Cbh + g * 64 + 2 * c2) = prev[u];
@@ -950,7 +995,7 @@ __device__ __forceinline__ void lloyd_value_outputs(const LloydArgs& a, const Ll
 template <int NB, bool SOLO>
 __global__ __launch_bounds__(kLT) void k_lloyd(LloydArgs a) {
   extern __shared__ __align__(16) unsigned char smem[];
-  __shared__ int s_nmov, s_nunc, s_xmov, s_flag;
+  __shared__ int s_nmov, s_nunc, s_xmov, s_flag, s_rep;
   constexpr int Npad = NB * 32;
   const int tid = threadIdx.x;
   const int bx = blockIdx.x, idx = bx >> 3;
@@ -968,6 +1013,7 @@ __global__ __launch_bounds__(kLT) void k_lloyd(LloydArgs a) {
     s_nmov = 0;
     s_nunc = 0;
     s_xmov = 0;
+    s_rep = 0;
   }
   // the first round's first tile: the rows are requested before the staging
   u32x4 kb0[4];
@@ -981,9 +1027,16 @@ __global__ __launch_bounds__(kLT) void k_lloyd(LloydArgs a) {
   for (int i = tid; i < Go; i += kLT) L.cnt[i] = 0;
   lds_barrier();
 
+  bool repeats = false;  // repeated representatives may be among them
+  bool rev = false;      // direction of the next pass over the tiles (lloyd_tiles)
   for (int t = 0; t < a.T; ++t) {
     const bool first = t == 0;
     bool last = t == a.T - 1;
+    if (repeats) {
+      lloyd_mask_repeats(L, Npad, a.N, &s_rep);
+      lds_barrier();
+      repeats = __builtin_amdgcn_readfirstlane(s_rep) != 0;
+    }
     // certification constants from the largest |r|^2 of the slice (padded groups hold 0)
     const int ol = opaque_tid() & 63;
     float nm = (float)L.nrm[min(ol, Npad - 1)];
@@ -992,9 +1045,17 @@ __global__ __launch_bounds__(kLT) void k_lloyd(LloydArgs a) {
     const LloydCert cf = lloyd_cert(nmaxf, sqrtf(nmaxf) * (1.0f + 0x1p-20f), a.cm, a.cp);
 
     // 1. assignment of the rank's keys and the sums of those that changed group
-    lloyd_assign<NB>(a, L, s, k0, nk, first, (t & 1) != 0, cf, kb0, &s_nmov, &s_nunc);
+    lloyd_assign<NB>(a, L, s, k0, nk, first, rev, cf, kb0, &s_nmov, &s_nunc);
+    rev = !rev;
     lds_barrier();
     const int nunc = s_nunc, nmov = s_nmov;
+    if (first && rev && nunc > 64 + nk / 16) {  // the round again, once: nothing but the queue is to be undone
+      repeats = true;
+      lds_barrier();
+      if (tid == 0) s_nunc = 0;
+      --t;
+      continue;
+    }
     float2 prev[kLFinU];
     if (SOLO) lloyd_prev_c(a, s, r, Go, prev);  // (else the loads overlap barrier A)
     // after the first round, with few moved keys (their sums take the direct

@@ -69,3 +69,60 @@ def test_one_rank_special_rounds(oracle_mod, dev, monkeypatch):
             assert np.array_equal(bel.cpu().numpy(), ref["belong"])
             assert np.array_equal(cnt.cpu().numpy(), ref["count"])
             assert np.array_equal(cen.cpu().numpy().view(np.uint32), ref["centroid"].view(np.uint32))
+
+
+REPEATS = [
+    # B, H, n, N, iters: one rank, one rank of four blocks, four ranks, sixteen, and a launch per round
+    (1, 3, 600, 50, 4), (1, 2, 1000, 128, 4), (1, 2, 1800, 100, 3), (1, 1, 8000, 128, 3), (1, 2, 900, 200, 3),
+]
+
+
+@pytest.mark.parametrize("case", REPEATS, ids=lambda c: "-".join(map(str, c)))
+@pytest.mark.parametrize("form", ["tail", "equal", "pairs", "init"])
+def test_repeated_representatives(oracle_mod, dev, case, form):
+    """Series whose strided keys repeat (zero padding, one value throughout, pairs)
+    and given centroids that do: exact ties, which the group of lowest index wins."""
+    B, H, n, N, iters = case
+    print(f"\n[case] repeats {case} {form}", flush=True)
+    _, K, _ = inputs.make_qkv(B, H, n, 64, "bf16", n + N, N, 0.05, 0.3)
+    init = None
+    if form == "tail":
+        K[:, :, n - n // 3:] = 0
+    elif form == "equal":
+        K[:] = K[:, :, 3:4].clone()
+    elif form == "pairs":
+        K[:, :, n // 2:] = K[:, :, :n - n // 2].clone()
+    else:
+        at = np.random.default_rng(N).integers(0, N // 3, N)
+        init = np.ascontiguousarray(inputs.as_float64(K)[:, :, at].astype(np.float32))
+    got = ga.cluster(K.to(dev), N, iters, init=None if init is None else torch.from_numpy(init).to(dev))
+    torch.cuda.synchronize()
+    ref = oracle_mod.cluster(inputs.as_float64(K), N, iters, "bf16", init=init)
+    for x, what in zip(got, ("belong", "count", "centroid")):
+        assert np.array_equal(x.cpu().numpy().view(np.uint32), ref[what].view(np.uint32)), what
+
+
+def test_padding_costs_no_multiple(dev):
+    """Zero-padded series on one rank: a tenth of the keys zero takes 1.3 times the
+    time without padding, and 5 to 6 times where every key near the repeated zero
+    representatives takes the exact decision.  The bound lies between."""
+    print("\n[case] cost of padding", flush=True)
+    _, K, _ = inputs.make_qkv(2, 4, 1000, 64, "bf16", 3, 64, 0.05, 0.3)
+    padded = K.clone()
+    padded[:, :, 900:] = 0
+
+    def time(x):
+        ts = []
+        for _ in range(20):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(10):
+                ga.cluster(x, 64, 5)
+            b.record()
+            b.synchronize()
+            ts.append(a.elapsed_time(b))
+        return sorted(ts)[len(ts) // 2]
+
+    K, padded = K.to(dev), padded.to(dev)
+    time(K)
+    assert time(padded) < 3 * time(K)
